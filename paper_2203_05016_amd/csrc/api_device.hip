@@ -141,6 +141,35 @@ int check_ydtype(const shflbw_matrix* A, shflbw_dtype ydtype)
                     : "ydtype must be SHFLBW_F16 or SHFLBW_F32 for a binary16 matrix");
 }
 
+// The convolution as gathers of runs of 8 (GeomConvRuns).  False when the tensor has no such
+// runs or is beyond the kernel's 24-bit and 32-bit offset arithmetic.
+template <bool CHWN>
+bool fill_conv_runs(const shflbw_matrix* A, GeomConvRuns<CHWN>& g, const void* in, void* out, int B, int C, int H, int W,
+                    int R, int S, int sh, int sw, int ph, int pw, int Ho, int Wo, int64_t in_total)
+{
+    if (CHWN ? B < 8 : (sw != 1 || Wo < 8 || W < 8 || pw > 1)) return false;
+    const int64_t RS = (int64_t)R * S;
+    const int64_t sst = CHWN ? 2 * (int64_t)B : 2, rst = W * sst, cst = H * rst;
+    // k / (R*S) by the high half of a product, the remainder / S by 16 bits of one: exact in these ranges
+    if (RS * A->K >= ((int64_t)1 << 32) || RS * S > 65536) return false;
+    if (cst >= (1 << 24) || C >= (1 << 24) || in_total >= ((int64_t)1 << 32) - 64) return false;
+    g.X = static_cast<const _Float16*>(in);
+    g.Y = out;
+    g.ldx = g.ldy = 0;
+    g.xbytes = (unsigned)in_total;
+    g.RS = (int)RS; g.S = S; g.H = H; g.W = W; g.B = B; g.Ho = Ho; g.Wo = Wo;
+    g.sh = sh; g.sw = sw; g.ph = ph; g.pw = pw;
+    g.m_RS = RS == 1 ? 0 : (unsigned)((((uint64_t)1 << 32) + RS - 1) / RS);
+    g.m_S = (unsigned)((65536 + S - 1) / S);
+    g.cst = (unsigned)cst; g.rst = (unsigned)rst; g.sst = (unsigned)sst;
+    g.ist = CHWN ? 0 : (unsigned)(C * cst);
+    g.osM = CHWN ? (long)Ho * Wo * B : (long)Ho * Wo;
+    g.osB = CHWN ? 0 : (long)A->M * Ho * Wo;
+    g.slots = ((CHWN ? B : Wo) + 7) / 8;
+    g.N = (CHWN ? (long)Ho * Wo : (long)B * Ho) * g.slots * 8;
+    return true;
+}
+
 // Picks the box of output positions one workgroup of the staged convolution
 // kernel owns, and fills the geometry part of its arguments.  Returns false
 // when no box fits (too many channels for the LDS, or a V the kernel does not
@@ -460,12 +489,19 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
         GeomLinear<true> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
         return dispatch_out(A, g, (long)N, ydtype, st);
     }
-    // rows of no particular alignment: whole 16-byte accesses from 8 columns on, where 24-bit offset
-    // arithmetic and a 32-bit range cover X
-    if (N >= 8) {
-        const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
-        if (A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64)
-            return run_rows(A, X, ldx, 0, Y, ldy, 0, (int)N, 1, xbytes, ydtype, st);
+    // rows of no particular alignment: whole 16-byte accesses where 24-bit offset arithmetic and a
+    // 32-bit range cover X
+    const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
+    if (A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64) {
+        if (N >= 8) return run_rows(A, X, ldx, 0, Y, ldy, 0, (int)N, 1, xbytes, ydtype, st);
+        if (xbytes >= 16) {
+            GeomNarrow g;
+            g.X = static_cast<const _Float16*>(X);
+            g.Y = Y;
+            g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
+            g.xbytes = (unsigned)xbytes;
+            return dispatch_out(A, g, (long)N, ydtype, st);
+        }
     }
     GeomLinear<false> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
     return dispatch_out(A, g, (long)N, ydtype, st);
@@ -560,7 +596,7 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         return shflbw_spmm(A, in, N, out, N, N, ydtype, stream);
     // The same on NCHW tensors is one such product per image; the gather kernel takes all images
     // in one launch, reading only the channels a group keeps instead of staging every channel of
-    // a box (32 images of 7x7, 2048 -> 512 channels: 22.4 us staged, 11.3 us gathered).
+    // a box (32 images of 7x7, 2048 -> 512 channels: 22.4 us staged, 9.6 us gathered).
     {
         const int64_t HW = (int64_t)H * W;
         const int64_t in_total = 2 * (int64_t)batch * C_in * HW;
@@ -568,6 +604,30 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
             stride_w == 1 && pad_h == 0 && pad_w == 0 && HW >= 8 && HW * 2 < (1 << 24) &&
             C_in < (1 << 24) && in_total < ((int64_t)1 << 32) - 64)
             return run_rows(A, in, HW, (long)C_in * HW, out, HW, (long)A->M * HW, (int)HW, batch, in_total, ydtype, st);
+    }
+    // Convolutions gathered in runs of 8 along the innermost dimension.  Left to the staged kernel (when
+    // it is not forced): products whose gathered bytes - every kept row of the unfolded matrix once per
+    // group - outweigh what its 2-byte LDS reads cost.  Batch-innermost tensors and V >= 64: never in
+    // what was measured (128 channels, 56x56, 3x3 / 2, V = 32, CHWN: 41.5 us staged, 13.2 gathered; 64 ->
+    // 128 channels, 56x56, dense, V = 32, CHWN: 59.9 / 37.0; 64 channels, 28x28, dense, V = 64: 21.6 /
+    // 14.1).  NCHW, us staged / gathered by density: V = 32, 256 channels, 14x14: 13.2 / 11.8 at 0.25,
+    // 18.9 / 18.8 at 0.5, 29.7 / 32.7 at 1; V = 32, 128 channels, 28x28: 15.7 / 12.5, 22.9 / 23.5 at 0.7,
+    // 28.2 / 30.8; V = 16, 128 channels, 28x28: 26.3 / 19.3 at 0.25, 47.3 / 55.2 at 1; V = 16 on images
+    // whose rows fill their slots badly (14 of 16 columns, 256 channels): 13.0 / 10.3 at 0.1, 17.8 / 18.7
+    // at 0.25, 24.9 / 28.7 at 0.5.
+    const double kept = (double)A->nnz / ((double)A->M * A->K);
+    const bool runs_pay = layout == SHFLBW_CHWN || A->V >= 64 || kept <= (A->V == 32 ? 0.55 : Wo < 16 ? 0.22 : 0.6);
+    if (A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) {
+        const int64_t in_total = 2 * (int64_t)batch * C_in * H * W;
+        if (layout == SHFLBW_CHWN) {
+            GeomConvRuns<true> g;
+            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total))
+                return dispatch_out(A, g, g.N, ydtype, st);
+        } else {
+            GeomConvRuns<false> g;
+            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total))
+                return dispatch_out(A, g, g.N, ydtype, st);
+        }
     }
     if (A->tune_kernel != 1 && A->tune_kernel != 3) {
         // the plan depends on the matrix and the geometry only: keep the last one

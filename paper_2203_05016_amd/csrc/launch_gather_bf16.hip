@@ -1,4 +1,5 @@
-// Gather-kernel launchers for bfloat16 operands.
+// Gather-kernel launchers for bfloat16 operands, linear layers.
+#define SHFLBW_LAUNCH_CONV 0
 #define SHFLBW_LAUNCH_BF true
 #define SHFLBW_LAUNCH_NAME run_gather_bf16
 #define SHFLBW_LAUNCH_OUT16 __bf16

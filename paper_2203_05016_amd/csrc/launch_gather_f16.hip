@@ -1,4 +1,5 @@
-// Gather-kernel launchers for binary16 operands.
+// Gather-kernel launchers for binary16 operands, linear layers.
+#define SHFLBW_LAUNCH_CONV 0
 #define SHFLBW_LAUNCH_BF false
 #define SHFLBW_LAUNCH_NAME run_gather_f16
 #define SHFLBW_LAUNCH_OUT16 _Float16
