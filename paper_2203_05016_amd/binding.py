@@ -17,7 +17,9 @@ NCHW, CHWN = 0, 1
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libshflbw.so")
+CALLS_PATH = os.path.join(_HERE, "_torch_calls.so")
 _lib = None
+_calls = None   # native calls on torch tensors (csrc/torch_calls.cpp), loaded with the first use on a GPU
 
 EXPORTS = [
     "shflbw_compress", "shflbw_pattern_search", "shflbw_destroy", "shflbw_info", "shflbw_row_indices",
@@ -87,6 +89,27 @@ def lib():
     return _lib
 
 
+def calls():
+    """The native calls on plain torch tensors, connected to the library.  Like the library
+    they are required: there is no other build of the plain case."""
+    global _calls
+    if _calls is None:
+        import importlib.machinery
+        import importlib.util
+        import torch
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("%s is missing: build it with `python -m paper_2203_05016_amd.build`" % CALLS_PATH)
+        loader = importlib.machinery.ExtensionFileLoader("_torch_calls", CALLS_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_torch_calls", loader))
+        loader.exec_module(m)
+        L = lib()
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        m.connect(address(L.shflbw_spmm), address(L.shflbw_conv2d), address(L.shflbw_layernorm_transpose),
+                  torch._C._cuda_getCurrentRawStream)
+        _calls = m
+    return _calls
+
+
 def status_string(status):
     return lib().shflbw_status_string(int(status)).decode()
 
@@ -137,6 +160,7 @@ class Matrix:
     def __init__(self, handle, bf16=False):
         self._h = handle
         self._dev = None
+        self._plan = None  # what the native calls need to know of the bound matrix
         self.bf16 = bf16   # operand format: bfloat16 instead of float16
         self._info = None  # what shflbw_info reports: fixed once the matrix is packed
         self._odt = None
@@ -202,6 +226,8 @@ class Matrix:
         _check(lib().shflbw_bind_device(self._h, ctypes.c_void_p(buf.data_ptr()),
                                         _stream_ptr(stream)))
         self._dev = buf
+        info = self.info()
+        self._plan = calls().plan(self._h.value, info["M"], info["K"], self.bf16, buf.device.index)
         return self
 
     def _require_on_bound_device(self, t, what):
@@ -218,6 +244,12 @@ class Matrix:
         matrix's operand format (float16, or bfloat16).  The C ABI has no K
         argument and sees only addresses, so shapes, strides and devices are
         checked here, before anything is enqueued."""
+        if Y is not None and stream is None and self._plan is not None:
+            rc = _calls.spmm(self._plan, X, Y)   # None: not the plain case, all checks below
+            if rc is not None:
+                if rc < 0:
+                    _check(rc)
+                return Y
         if X.dtype != self._operand_dtype() or X.dim() != 2 or X.stride(1) != 1 and X.shape[1] > 1:
             raise TypeError("X must be a 2-D %s tensor with unit column stride" % self._operand_dtype())
         info = self.info()
@@ -252,6 +284,12 @@ class Matrix:
     def conv2d(self, inp, R, S, stride=(1, 1), pad=(0, 0), layout="NCHW", out=None,
                out_dtype=None, stream=None):
         """Masked conv2d of a contiguous device tensor in the matrix's operand format."""
+        if out is not None and stream is None and self._plan is not None and layout in ("NCHW", "CHWN"):
+            rc = _calls.conv2d(self._plan, inp, R, S, stride, pad, layout == "CHWN", out)   # None: not the plain case
+            if rc is not None:
+                if rc < 0:
+                    _check(rc)
+                return out
         import torch
         if inp.dtype != self._operand_dtype() or not inp.is_contiguous() or inp.dim() != 4:
             raise TypeError("input must be a contiguous 4-D %s tensor" % self._operand_dtype())
@@ -313,6 +351,12 @@ def layernorm_transpose(x, gamma=None, beta=None, eps=1e-5, normalize=True, out=
     """shflbw_layernorm_transpose on device tensors: x (N tokens, K features)
     float16 or bfloat16 with unit feature stride; returns the (K, N) matrix
     shflbw_spmm takes as X."""
+    if out is not None and stream is None:
+        rc = (_calls or calls()).layernorm_transpose(x, gamma, beta, eps, normalize, out)   # None: not the plain case
+        if rc is not None:
+            if rc < 0:
+                _check(rc)
+            return out
     import torch
     if x.dtype not in (torch.float16, torch.bfloat16) or x.dim() != 2 or x.stride(1) != 1:
         raise TypeError("x must be a 2-D float16 or bfloat16 tensor with unit feature stride")

@@ -3,8 +3,9 @@
     python -m paper_2203_05016_amd.build
     python -m paper_2203_05016_amd.build --host-sanitized   # g++ ASan/UBSan build of the host-only sources
 
-The result is ``paper_2203_05016_amd/libshflbw.so``; it links against the HIP
-runtime only (no torch).
+The results are ``paper_2203_05016_amd/libshflbw.so``, which links against the HIP
+runtime only (no torch), and ``paper_2203_05016_amd/_torch_calls.so``, the binding's
+native calls on torch tensors (host code, g++).
 """
 import os
 import subprocess
@@ -24,6 +25,20 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
+TORCH_CALLS = os.path.join(HERE, "_torch_calls.so")
+
+
+def _torch_calls_command(out):
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+             os.path.join(CSRC, "torch_calls.cpp"), "-o", out] + sum([["-isystem", i] for i in includes], []) +
+            ["-L", libdir, "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"])
+
+
 def build(verbose=True, extra=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs, procs = [], []
@@ -35,17 +50,21 @@ def build(verbose=True, extra=()):
         cmd = [hipcc, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS + list(extra)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
         objs.append(obj)
+    calls_tmp = TORCH_CALLS + ".tmp.%d" % os.getpid()
+    procs.append(("torch_calls.cpp", subprocess.Popen(_torch_calls_command(calls_tmp), stdout=subprocess.PIPE,
+                                                      stderr=subprocess.STDOUT)))
     for src, p in procs:
         out = p.communicate()[0].decode()
         keep = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
         if p.returncode != 0:
             sys.stderr.write(out)
-            raise RuntimeError("hipcc failed on %s" % src)
+            raise RuntimeError("compiler failed on %s" % src)
         if verbose and keep:
             print("\n".join(keep))
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    os.replace(calls_tmp, TORCH_CALLS)
     if verbose:
         print("built %s in %.1f s" % (LIB, time.time() - t0))
     return LIB

@@ -90,7 +90,8 @@ int launch_slab(const shflbw_matrix* A, const void* X, long ldx, void* Y, long l
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    note_kernel(kernel_name("shflbw_slab_kernel", V, GW, sizeof(OutT) == 4, BF));
+    static const std::string& name = *new std::string(kernel_name("shflbw_slab_kernel", V, GW, sizeof(OutT) == 4, BF));
+    note_kernel(name.c_str());
     return SHFLBW_OK;
 }
 
@@ -319,11 +320,12 @@ int launch_conv_nt(const shflbw_matrix* A, ConvArgs& a, size_t lds_bytes, hipStr
                        stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    {
-        std::string name = kernel_name("shflbw_conv_kernel", V, NT, sizeof(OutT) == 4, BF);
-        if (SP) name.insert(name.size() - 1, ",4-byte staging");
-        note_kernel(name);
-    }
+    static const std::string& name = *new std::string([] {
+        std::string s = kernel_name("shflbw_conv_kernel", V, NT, sizeof(OutT) == 4, BF);
+        if (SP) s.insert(s.size() - 1, ",4-byte staging");
+        return s;
+    }());
+    note_kernel(name.c_str());
     return SHFLBW_OK;
 }
 

@@ -12,7 +12,7 @@
 
 namespace {
 thread_local std::string g_last_error;
-thread_local std::string g_last_kernel;
+thread_local const char* g_last_kernel = "";
 thread_local const void* g_base_override = nullptr;
 
 // Position of (stored row i of the group, step column j) inside one k-step's
@@ -73,7 +73,7 @@ int fail(int status, const std::string& detail)
     g_last_error = detail;
     return status;
 }
-void note_kernel(const std::string& name) { g_last_kernel = name; }
+void note_kernel(const char* name) { g_last_kernel = name; }
 const void* device_base(const shflbw_matrix* A) { return g_base_override ? g_base_override : A->dev_base; }
 void set_device_base_override(const void* base) { g_base_override = base; }
 }  // namespace shflbw
@@ -81,7 +81,7 @@ void set_device_base_override(const void* base) { g_base_override = base; }
 extern "C" {
 
 const char* shflbw_last_error(void) { return g_last_error.c_str(); }
-const char* shflbw_last_kernel(void) { return g_last_kernel.c_str(); }
+const char* shflbw_last_kernel(void) { return g_last_kernel; }
 
 const char* shflbw_status_string(int status)
 {

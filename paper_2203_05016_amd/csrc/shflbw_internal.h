@@ -93,7 +93,9 @@ static_assert((SLAB_ZERO_ROW + 1) * SLAB_ROW_BYTES / 16 <= (1 << 13), "LDS offse
 // different bank groups; bit 1 varies with the next row bit.
 constexpr int slab_swizzle(int r) { return ((r & 3) << 2) | (((r >> 2) & 1) << 1); }
 int fail(int status, const std::string& detail);  // records the thread-local text, returns status
-void note_kernel(const std::string& name);        // records what the calling thread launched last (shflbw_last_kernel)
+// records what the calling thread launched last (shflbw_last_kernel); keeps the pointer: name lives until the
+// process ends (each launcher builds its own once, not per launch)
+void note_kernel(const char* name);
 // Where the packed arrays of A live on the device for launches of the calling thread: the buffer given
 // to shflbw_bind_device, unless an entry point that brings its own device image has set an override.
 const void* device_base(const shflbw_matrix* A);
