@@ -508,6 +508,15 @@ struct GatherShape {
     static constexpr int REGION = (2 * STAGE > EPI) ? 2 * STAGE : EPI;
 };
 
+// Which workgroup takes which block of column tiles and which group.  Workgroups are dealt to the eight
+// XCDs in turn.  per_xcd = 0: blockIdx.x is the block of tiles, blockIdx.y the group.  Otherwise the grid is
+// 8 x per_xcd and XCD x takes items x*per_xcd .. of the list that runs over all groups of one
+// block of tiles before the next.
+struct GatherOrder {
+    int per_xcd, total;          // items of an XCD, and of the launch (tile blocks x groups, below 2^19)
+    unsigned long long m_G;      // ceil(2^40 / G)
+};
+
 template <class Geom>
 constexpr bool uses_list()
 {
@@ -520,8 +529,7 @@ constexpr bool uses_list()
 // takes a contiguous share of the group's k-steps; the partial accumulators of a row block meet in
 // the LDS, every wavefront of the tile adds up its share of them and stores its share of the rows.
 template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A, Geom geom,
-                                                                  int n_tiles)
+__global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
 {
     using S = GatherShape<V, WN>;
     constexpr int TK = S::TK, RB = S::RB, NT = S::NT, LPR = S::LPR, NLD = S::NLD;
@@ -542,11 +550,17 @@ __global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ti = wave / SPLIT, part = wave % SPLIT;
-    const int tile = (int)blockIdx.x * TILES + ti;
+    int tblock = blockIdx.x, g = blockIdx.y;
+    if (order.per_xcd) {
+        const unsigned w = blockIdx.x * (unsigned)order.per_xcd + blockIdx.y;
+        if (w >= (unsigned)order.total) return;   // uniform for the whole workgroup
+        tblock = (int)(((unsigned long long)w * order.m_G) >> 40);
+        g = (int)w - tblock * A.G;
+    }
+    const int tile = tblock * TILES + ti;
     // without SPLIT a whole wavefront leaves and no workgroup barrier is used; with SPLIT one whose
     // tile does not exist stays for the barriers, with no steps and nothing to store
     if (SPLIT == 1 && tile >= n_tiles) return;
-    const int g = blockIdx.y;
     const long n0 = (long)tile * WN;
     _Float16* my = smem + wave * S::REGION;
 
