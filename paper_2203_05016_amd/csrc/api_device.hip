@@ -69,6 +69,9 @@ int launch_slab(const shflbw_matrix* A, const void* X, long ldx, void* Y, long l
     a.X = static_cast<const _Float16*>(X);
     a.Y = Y;
     a.ldx = ldx; a.ldy = ldy; a.N = N;
+    // 4096 x 1024 by 8200 (rows of 16 400 bytes): 67 us streaming, 59 plain; 8192 x 8192 by 16376, V = 64: 784 and
+    // 754; by 8224 (a multiple of 64 bytes): 48 and 54
+    a.stream = (ldy * (long)sizeof(OutT) | (long)reinterpret_cast<uintptr_t>(Y)) % 64 == 0;
     a.K = A->K; a.C = A->slab_chunks;
     const long n_tiles = (N + SLAB_TN - 1) / SLAB_TN;
     a.n_tiles = (int)n_tiles;
@@ -129,6 +132,8 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     g.xbytes = (unsigned)xbytes;
     g.x_image = (long)x_image; g.y_image = (long)y_image;
     g.P = P; g.slots = (P + 7) / 8;
+    const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
+    g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob);
     g.N = (long)images * g.slots * 8;
     return dispatch_out(A, g, g.N, ydtype, stream);
 }
@@ -146,7 +151,7 @@ int check_ydtype(const shflbw_matrix* A, shflbw_dtype ydtype)
 // runs or is beyond the kernel's 24-bit and 32-bit offset arithmetic.
 template <bool CHWN>
 bool fill_conv_runs(const shflbw_matrix* A, GeomConvRuns<CHWN>& g, const void* in, void* out, int B, int C, int H, int W,
-                    int R, int S, int sh, int sw, int ph, int pw, int Ho, int Wo, int64_t in_total)
+                    int R, int S, int sh, int sw, int ph, int pw, int Ho, int Wo, int64_t in_total, int out_bytes)
 {
     if (CHWN ? B < 8 : (sw != 1 || Wo < 8 || W < 8 || pw > 1)) return false;
     const int64_t RS = (int64_t)R * S;
@@ -164,6 +169,11 @@ bool fill_conv_runs(const shflbw_matrix* A, GeomConvRuns<CHWN>& g, const void* i
     g.m_S = (unsigned)((65536 + S - 1) / S);
     g.cst = (unsigned)cst; g.rst = (unsigned)rst; g.sst = (unsigned)sst;
     g.ist = CHWN ? 0 : (unsigned)(C * cst);
+    // NCHW rows are short and follow each other: streaming whatever their length (64 images of 56x56, 64 ->
+    // 256 channels: 55 us against 72).  CHWN: by the bytes of a position's images (50 of them, 30x30, 64 -> 256
+    // channels: 17.0 streaming, 15.0 plain; 32 of them, 56x56 / 2: 11.1 and 11.6)
+    g.stream = !CHWN || stream_stores(out, (int64_t)B * out_bytes, out_bytes, (double)in_total,
+                                      (double)A->M * Ho * Wo * B * out_bytes);
     g.osM = CHWN ? (long)Ho * Wo * B : (long)Ho * Wo;
     g.osB = CHWN ? 0 : (long)A->M * Ho * Wo;
     g.slots = ((CHWN ? B : Wo) + 7) / 8;
@@ -486,6 +496,8 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
             g.Y = Y;
             g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
             g.xbytes = (unsigned)xbytes;
+            const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
+            g.stream = stream_stores(Y, ldy * ob, ob, 2.0 * A->K * N, (double)ob * A->M * N);
             return dispatch_out(A, g, (long)N, ydtype, st);
         }
         GeomLinear<true> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
@@ -502,6 +514,7 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
             g.Y = Y;
             g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
             g.xbytes = (unsigned)xbytes;
+            g.stream = 0;
             return dispatch_out(A, g, (long)N, ydtype, st);
         }
     }
@@ -623,11 +636,13 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         const int64_t in_total = 2 * (int64_t)batch * C_in * H * W;
         if (layout == SHFLBW_CHWN) {
             GeomConvRuns<true> g;
-            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total))
+            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total,
+                               ydtype == SHFLBW_F32 ? 4 : 2))
                 return dispatch_out(A, g, g.N, ydtype, st);
         } else {
             GeomConvRuns<false> g;
-            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total))
+            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total,
+                               ydtype == SHFLBW_F32 ? 4 : 2))
                 return dispatch_out(A, g, g.N, ydtype, st);
         }
     }

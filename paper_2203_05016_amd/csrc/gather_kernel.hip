@@ -142,18 +142,23 @@ struct GeomLinear {
     }
 };
 
-// CNT consecutive values to p, at the alignment of one value.  STREAM: a streaming store, for an output
-// that must not displace X and W in the L2.
-template <bool STREAM, typename OutT, int CNT>
-__device__ __forceinline__ void store_run(OutT* p, const OutT* vals)
+// CNT consecutive values to p, at the alignment of one value.  stream (the same for the whole launch): a
+// streaming store, for an output that must not displace X and W in the L2.
+template <typename OutT, int CNT>
+__device__ __forceinline__ void store_run(OutT* p, const OutT* vals, int stream)
 {
     typedef OutT vec_t __attribute__((ext_vector_type(CNT)));
     typedef vec_t run_t __attribute__((aligned(sizeof(OutT))));
     vec_t v;
 #pragma unroll
     for (int e = 0; e < CNT; ++e) v[e] = vals[e];
-    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<run_t*>(p));
-    else *reinterpret_cast<run_t*>(p) = v;
+    if (stream) {
+        asm volatile("");   // kept apart: merged with the other branch, the store loses its hint
+        __builtin_nontemporal_store(v, reinterpret_cast<run_t*>(p));
+        asm volatile("");
+    } else {
+        *reinterpret_cast<run_t*>(p) = v;
+    }
 }
 
 // The aligned linear layer again, with X behind a buffer descriptor: a load's
@@ -168,6 +173,7 @@ struct GeomLinearBuf {
     void* Y;
     long ldx, ldy, N;
     unsigned xbytes;          // (K-1)*ldx*2 + N*2: what the descriptor covers
+    int stream;               // streaming stores (the host's stream_stores)
     __amdgpu_buffer_rsrc_t xd;
     unsigned ldx2, ln2;
     // beyond every descriptor the host admits, and 16 bytes from there do not wrap
@@ -195,15 +201,7 @@ struct GeomLinearBuf {
     template <typename OutT, int CNT>
     __device__ __forceinline__ void store(int row, long n, const OutT* vals) const
     {
-        OutT* p = static_cast<OutT*>(Y) + (long)row * ldy + n;
-        if (n < N) {
-            typedef OutT vec_t __attribute__((ext_vector_type(CNT)));
-            vec_t v;
-#pragma unroll
-            for (int e = 0; e < CNT; ++e) v[e] = vals[e];
-            // the output is not read again by this kernel: keep it from displacing X and W in the L2
-            __builtin_nontemporal_store(v, reinterpret_cast<vec_t*>(p));
-        }
+        if (n < N) store_run<OutT, CNT>(static_cast<OutT*>(Y) + (long)row * ldy + n, vals, stream);
     }
 };
 
@@ -220,10 +218,6 @@ struct GeomLinearBuf {
 // the same terms in the same order, and stored twice with the same bits.  Measured on 4096 x
 // 1024 by 1024 x 2047 (V = 32, 75 %): 18.5 us against 65 us with element-wise loads and stores
 // (12.6 us at N = 2048: a row segment of 128 bytes spans two lines when it is not aligned).
-// 16-bit results leave with streaming stores (61 us against 74 with plain ones at N = 8191, where Y
-// displaces X in the L2; 18.9 and 18.9 at N = 2047), 32-bit results with plain ones: twice the lines are
-// written in part, and streaming does not give their halves time to meet (N = 2047: 31.7 -> 21.4 us,
-// N = 8191: 120 -> 102; 512 x 512 by 16381 at 90 %: 27.1 -> 13.8).
 // Loading odd offsets one value early, with the missing last value from the next lane, takes the
 // address unit's accesses from 62 to 20 per load and gains nothing (18.6 us; convolutions lose 1 us
 // to the extra instructions).
@@ -257,7 +251,7 @@ struct GeomRows : GeomLinearBuf {
             unsigned img, c;
             place(n, img, c);
             OutT* p = static_cast<OutT*>(Y) + (long)img * y_image + (long)row * ldy + c + ((unsigned)n & 7u);
-            store_run<sizeof(OutT) == 2, OutT, CNT>(p, vals);
+            store_run<OutT, CNT>(p, vals, stream);
         }
     }
 };
@@ -411,7 +405,7 @@ struct GeomConvRuns : GeomLinearBuf {
             int b, y, x;
             place(n, b, y, x);
             const long pos = CHWN ? ((long)y * Wo + x) * B + b : (long)b * osB + (long)y * Wo + x;
-            store_run<true, OutT, CNT>(static_cast<OutT*>(Y) + (long)row * osM + pos + (n & 7), vals);
+            store_run<OutT, CNT>(static_cast<OutT*>(Y) + (long)row * osM + pos + (n & 7), vals, stream);
         }
     }
 };

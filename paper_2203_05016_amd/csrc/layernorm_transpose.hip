@@ -54,8 +54,24 @@ struct LnArgs {
     int K;
     float eps;
     int normalize;
+    int stream;             // streaming stores, see ln_store
     int blocks_per_wg;      // 64-feature blocks one workgroup transposes (grid.y covers K)
+    int slices_per_wg;      // register-resident variant: 1024-feature slices one workgroup stores (grid.y covers K)
 };
+
+// Streaming where the row segments of 64 (128) bytes are whole 64-byte blocks of memory; plain where
+// two workgroups share a block, so that its parts meet in the L2 (8184 tokens of 1024 features: 16.0 us
+// streaming, 11.0 plain; 20 008 of 1024: 41 and 26; 8192 of 1024: 8.2 and 8.9).
+__device__ __forceinline__ void ln_store(uint16_t* p, ln_ushort8 v, int stream)
+{
+    if (stream) {
+        asm volatile("");   // kept apart: merged with the other branch, the store loses its hint
+        __builtin_nontemporal_store(v, reinterpret_cast<ln_ushort8*>(p));
+        asm volatile("");
+    } else {
+        *reinterpret_cast<ln_ushort8*>(p) = v;
+    }
+}
 
 template <bool BF>
 __device__ __forceinline__ float ln_widen(uint16_t v)
@@ -276,12 +292,11 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int kc = kc0 + h * 512 + lane * 8;
-                if (FULL) {
-                    v[t][h] = *reinterpret_cast<const ln_ushort8*>(a.x + n * a.ldx + kc);
-                } else {
-                    v[t][h] = ln_ushort8{0, 0, 0, 0, 0, 0, 0, 0};
-                    if (n < a.N && kc < K) v[t][h] = *reinterpret_cast<const ln_ushort8*>(a.x + n * a.ldx + kc);
-                }
+                // a token or feature that does not exist loads the last one instead (its values are neither
+                // summed, nor kept, nor stored: a conditional load would wait for the one before it)
+                const long nc = FULL || n < a.N ? n : a.N - 1;
+                const int cc = FULL || kc < K ? kc : K - 8;
+                v[t][h] = *reinterpret_cast<const ln_ushort8*>(a.x + nc * a.ldx + cc);
             }
         }
         if (NORM && kc0 == 0) {
@@ -389,8 +404,8 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
                     }
                 }
                 uint16_t* dst = a.out + (long)k * a.ldo + n;
-                __builtin_nontemporal_store(o0, reinterpret_cast<ln_ushort8*>(dst));
-                __builtin_nontemporal_store(o1, reinterpret_cast<ln_ushort8*>(dst + a.ldo));
+                ln_store(dst, o0, a.stream);
+                ln_store(dst + a.ldo, o1, a.stream);
             }
         }
     }
@@ -408,7 +423,9 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
 // activation; the streaming kernel reads a row once per workgroup that shares its
 // tokens, and 16-token blocks, whose 32-byte row segments halve the write rate, measured
 // 187 us against 112 on 8192 x 8192).
-template <bool BF, bool NORM, int PARTS>
+// SHARED: several workgroups (grid.y) share a token block; each takes the statistics for itself and
+// stores its own slices, which it reads again.
+template <bool BF, bool NORM, int PARTS, bool SHARED>
 __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnArgs a)
 {
     constexpr int TOK = 32, WAVES = 16, TPW = 2, KH = 4096, SL = 1024, NSL = KH / SL;
@@ -439,12 +456,10 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
 #pragma unroll
             for (int j = 0; j < 2 * NSL; ++j) {
                 const int kc = kh + j * 512 + lane * 8;
-                if (FULL) {
-                    v[t][j] = *reinterpret_cast<const ln_ushort8*>(a.x + n * a.ldx + kc);
-                } else {
-                    v[t][j] = ln_ushort8{0, 0, 0, 0, 0, 0, 0, 0};
-                    if (n < a.N && kc < K) v[t][j] = *reinterpret_cast<const ln_ushort8*>(a.x + n * a.ldx + kc);
-                }
+                // what does not exist loads the last token or feature (neither summed nor stored)
+                const long nc = FULL || n < a.N ? n : a.N - 1;
+                const int cc = FULL || kc < K ? kc : K - 8;
+                v[t][j] = *reinterpret_cast<const ln_ushort8*>(a.x + nc * a.ldx + cc);
             }
         }
         if (STATS) {
@@ -481,6 +496,44 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
     float mean[8], rstd[8];
     // 1.0 twice in the 16-bit format, for an absent gamma
     const unsigned one2 = BF ? 0x3f803f80u : 0x3c003c00u;
+    // the transposed rows k0 .. k0+1023 from LDS buffer `buf`
+    auto store_slice = [&](int k0, int buf) __attribute__((always_inline)) {
+        const unsigned* xw = reinterpret_cast<const unsigned*>(xs + buf * TOK * P) + tchunk * 8 * Q;
+#pragma unroll
+        for (int pass = 0; pass < SL / (WAVES * 2 * FP); ++pass) {
+            const int kl = (pass * WAVES + wave) * 2 * FP + 2 * kk2;   // feature inside the slice
+            const int k = k0 + kl;
+            if (k < K && n < a.N) {
+                unsigned w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = xw[e * Q + (kl >> 1)];
+                ln_ushort8 o0, o1;
+                if (NORM) {
+                    const unsigned gw = a.gamma ? *reinterpret_cast<const unsigned*>(a.gamma + k) : one2;
+                    const unsigned bw = a.beta ? *reinterpret_cast<const unsigned*>(a.beta + k) : 0u;
+                    float g0, g1, b0, b1;
+                    ln_add_pair<BF>(gw, 0.f, g0, g1);
+                    ln_add_pair<BF>(bw, 0.f, b0, b1);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        float lo, hi;
+                        ln_add_pair<BF>(w[e], -mean[e], lo, hi);
+                        o0[e] = ln_narrow<BF>(lo * rstd[e] * g0 + b0);
+                        o1[e] = ln_narrow<BF>(hi * rstd[e] * g1 + b1);
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        o0[e] = (uint16_t)(w[e] & 0xffffu);
+                        o1[e] = (uint16_t)(w[e] >> 16);
+                    }
+                }
+                uint16_t* dst = a.out + (long)k * a.ldo + n;
+                ln_store(dst, o0, a.stream);
+                ln_store(dst + a.ldo, o1, a.stream);
+            }
+        }
+    };
     // the part held in registers, slice by slice through the LDS, out as transposed rows
     auto emit = [&](int part) __attribute__((always_inline)) {
         const int kh = part * KH;
@@ -501,48 +554,52 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
         __syncthreads();
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl) {
-            // whole slices every time (a slice beyond K holds zeros and stores nothing), so
-            // that every wavefront meets every barrier
+            // whole slices every time (a slice beyond K stores nothing), so that every wavefront
+            // meets every barrier
             if (sl + 1 < NSL) stage(sl + 1);
-            const unsigned* xw = reinterpret_cast<const unsigned*>(xs + (sl & 1) * TOK * P) + tchunk * 8 * Q;
-#pragma unroll
-            for (int pass = 0; pass < SL / (WAVES * 2 * FP); ++pass) {
-                const int kl = (pass * WAVES + wave) * 2 * FP + 2 * kk2;   // feature inside the slice
-                const int k = kh + sl * SL + kl;
-                if (k < K && n < a.N) {
-                    unsigned w[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) w[e] = xw[e * Q + (kl >> 1)];
-                    ln_ushort8 o0, o1;
-                    if (NORM) {
-                        const unsigned gw = a.gamma ? *reinterpret_cast<const unsigned*>(a.gamma + k) : one2;
-                        const unsigned bw = a.beta ? *reinterpret_cast<const unsigned*>(a.beta + k) : 0u;
-                        float g0, g1, b0, b1;
-                        ln_add_pair<BF>(gw, 0.f, g0, g1);
-                        ln_add_pair<BF>(bw, 0.f, b0, b1);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            float lo, hi;
-                            ln_add_pair<BF>(w[e], -mean[e], lo, hi);
-                            o0[e] = ln_narrow<BF>(lo * rstd[e] * g0 + b0);
-                            o1[e] = ln_narrow<BF>(hi * rstd[e] * g1 + b1);
-                        }
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            o0[e] = (uint16_t)(w[e] & 0xffffu);
-                            o1[e] = (uint16_t)(w[e] >> 16);
-                        }
-                    }
-                    uint16_t* dst = a.out + (long)k * a.ldo + n;
-                    __builtin_nontemporal_store(o0, reinterpret_cast<ln_ushort8*>(dst));
-                    __builtin_nontemporal_store(o1, reinterpret_cast<ln_ushort8*>(dst + a.ldo));
-                }
-            }
+            store_slice(kh + sl * SL, sl & 1);
             __syncthreads();
         }
     };
 
+    // SHARED: slices [sl, end) from memory, the next one in flight while one is stored
+    auto emit_own = [&]() __attribute__((always_inline)) {
+        int sl = blockIdx.y * a.slices_per_wg;
+        const int all = (K + SL - 1) / SL, end = sl + a.slices_per_wg < all ? sl + a.slices_per_wg : all;
+        ln_ushort8 c[TPW][2];
+        auto request = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                const long nt = n0 + wave * TPW + t;
+                const long nc = nt < a.N ? nt : a.N - 1;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int kc = s * SL + h * 512 + lane * 8;
+                    c[t][h] = *reinterpret_cast<const ln_ushort8*>(a.x + nc * a.ldx + (kc < K ? kc : K - 8));
+                }
+            }
+        };
+        request(sl);
+        for (; sl < end; ++sl) {
+#pragma unroll
+            for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint2* dst = reinterpret_cast<uint2*>(xs + ((sl & 1) * TOK + wave * TPW + t) * P + h * 512 + lane * 8);
+                    const ln_ushort8& w = c[t][h];
+                    dst[0] = uint2{(unsigned)w[0] | ((unsigned)w[1] << 16), (unsigned)w[2] | ((unsigned)w[3] << 16)};
+                    dst[1] = uint2{(unsigned)w[4] | ((unsigned)w[5] << 16), (unsigned)w[6] | ((unsigned)w[7] << 16)};
+                }
+            if (sl + 1 < end) request(sl + 1);
+            __syncthreads();   // the slice is there; the buffer of the slice before last is free again
+            store_slice(sl * SL, sl & 1);
+        }
+    };
+
+    if (!NORM && SHARED) {
+        emit_own();
+        return;
+    }
     if (!NORM) {
         // nothing to wait for: each part goes out as it comes in
 #pragma unroll
@@ -575,6 +632,10 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 8; ++e) { mean[e] = st_mean[tchunk * 8 + e]; rstd[e] = st_rstd[tchunk * 8 + e]; }
+    if (SHARED) {
+        emit_own();
+        return;
+    }
     emit(PARTS - 1);   // the part the sweep left in the registers
 #pragma unroll
     for (int part = 0; part < PARTS - 1; ++part) {
@@ -613,6 +674,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
     a.out = static_cast<uint16_t*>(out);
     a.ldx = (long)ldx; a.ldo = (long)ldo; a.N = (long)N; a.K = K; a.eps = eps;
     a.normalize = normalize ? 1 : 0;
+    a.stream = ((uintptr_t)(ldo * 2) | reinterpret_cast<uintptr_t>(out)) % 64 == 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
     // LDS-resident variant when a block of tokens with all its features fits
     auto resident_bytes = [&](int tok, int& pitch) {
@@ -663,18 +725,31 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         // too wide for the LDS, narrow enough to go through the registers of sixteen wavefronts
         // in at most four parts
         typedef void (*register_fn)(LnArgs);
-#define SHFLBW_LN_REG(P) \
-    &layernorm_transpose_register_kernel<false, false, P>, &layernorm_transpose_register_kernel<false, true, P>, \
-    &layernorm_transpose_register_kernel<true, false, P>, &layernorm_transpose_register_kernel<true, true, P>
-        static const register_fn rtable[16] = {SHFLBW_LN_REG(1), SHFLBW_LN_REG(2), SHFLBW_LN_REG(3), SHFLBW_LN_REG(4)};
+#define SHFLBW_LN_REG(P, S) \
+    &layernorm_transpose_register_kernel<false, false, P, S>, &layernorm_transpose_register_kernel<false, true, P, S>, \
+    &layernorm_transpose_register_kernel<true, false, P, S>, &layernorm_transpose_register_kernel<true, true, P, S>
+        static const register_fn rtable[32] = {SHFLBW_LN_REG(1, false), SHFLBW_LN_REG(2, false), SHFLBW_LN_REG(3, false),
+                                               SHFLBW_LN_REG(4, false), SHFLBW_LN_REG(1, true),  SHFLBW_LN_REG(2, true),
+                                               SHFLBW_LN_REG(3, true),  SHFLBW_LN_REG(4, true)};
 #undef SHFLBW_LN_REG
         const int parts = (K + 4095) / 4096;
-        const int which = (parts - 1) * 4 + (dtype == SHFLBW_BF16 ? 2 : 0) + (a.normalize ? 1 : 0);
-        const register_fn fn = rtable[which];
-        const size_t bytes = (size_t)2 * 32 * (1024 + 4) * 2 + 2 * 32 * 4;
         const int64_t rwgs = (N + 31) / 32;
         if (rwgs > 0x7fffffffLL) return fail(SHFLBW_ERR_BAD_SHAPE, "grid too large");
-        static thread_local int raised_reg[16] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
+        // Few tokens: the slices of a token block are shared by several workgroups, each of which takes the
+        // statistics for itself (its reads of the other slices come from the L2), as long as there is at
+        // most one workgroup per CU.  One workgroup per 32 tokens leaves most CUs idle: 848 tokens of 5800
+        // features 23.2 -> 17.4 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
+        // 15.0 -> 10.1, 64 of 16 384 51 -> 17.
+        const int slices = (K + 1023) / 1024;
+        int shares = rwgs > 0 && rwgs < 256 ? (int)(256 / rwgs) : 1;
+        if (shares > slices) shares = slices;
+        a.slices_per_wg = (slices + shares - 1) / shares;
+        const unsigned ry = (unsigned)((slices + a.slices_per_wg - 1) / a.slices_per_wg);
+        const int which = (ry > 1 ? 16 : 0) + (parts - 1) * 4 + (dtype == SHFLBW_BF16 ? 2 : 0) + (a.normalize ? 1 : 0);
+        const register_fn fn = rtable[which];
+        const size_t bytes = (size_t)2 * 32 * (1024 + 4) * 2 + 2 * 32 * 4;
+        static thread_local int raised_reg[32] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1,
+                                                  -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
         int dev = 0;
         hipError_t ea = hipGetDevice(&dev);
         if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(ea));
@@ -683,7 +758,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
             if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(ea));
             raised_reg[which] = dev;
         }
-        hipLaunchKernelGGL(fn, dim3((unsigned)rwgs), dim3(1024), bytes, st, a);
+        hipLaunchKernelGGL(fn, dim3((unsigned)rwgs, ry), dim3(1024), bytes, st, a);
         hipError_t el = hipGetLastError();
         if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(el));
         return SHFLBW_OK;

@@ -100,6 +100,20 @@ void note_kernel(const char* name);
 // to shflbw_bind_device, unless an entry point that brings its own device image has set an override.
 const void* device_base(const shflbw_matrix* A);
 void set_device_base_override(const void* base);  // nullptr = none; thread-local
+// Whether a kernel's results leave with streaming stores (pitch: bytes between output rows).  They do not
+// displace the operands in the L2s, but a 64-byte block that two row segments share is then written to
+// memory in parts, which is slower than the displacement for all but large operands.  x_bytes, y_bytes:
+// operands and results of the launch.  us streaming / plain, rows that are not multiples of 64 bytes:
+//   gather, 16 bits: 2048 x 2048 by 4008, V = 64, 90 % 13.8 / 11.5; 4096 x 1024 by 2040 15.5 / 14.3; 1x1 on
+//     30x30 images 8.7 / 7.8; but 4096 x 1024 by 8191 61 / 74, 1024 x 4096 by 8200 40 / 49
+//   gather, 32 bits: 4096 x 1024 by 2040 22.7 / 16.3; 4096 x 1024 by 8191 120 / 102; but 1024 x 4096 by 8200
+//     (67 MB of X) 46 / 55
+// and multiples of 64 bytes: 4096 x 1024 by 2080 17.6 / 18.2, 1x1 on 56x56 images 7.7 / 8.8.
+inline bool stream_stores(const void* y, int64_t pitch, int out_bytes, double x_bytes, double y_bytes)
+{
+    if ((pitch | (int64_t)reinterpret_cast<uintptr_t>(y)) % 64 == 0) return true;
+    return out_bytes == 4 ? x_bytes > 32e6 : x_bytes + y_bytes > 40e6;
+}
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 }  // namespace shflbw
 

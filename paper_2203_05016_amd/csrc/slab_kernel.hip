@@ -57,6 +57,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "gather_kernel.hip"
 
@@ -95,6 +96,7 @@ struct SlabArgs {
     int n_tiles, gblocks;     // 128-column tiles, blocks of GW groups
     int gb_side;              // 0, or the group-block side of the blocks an XCD works on at a time (divides gblocks, and 32)
     int spin_limit;           // polls per bounded wait
+    int stream;               // streaming stores: rows of Y begin at multiples of 64 bytes
     int uniform_steps;        // k-steps of every group when they all have the same number, else -1
     int* status;              // set to non-zero by a wavefront whose wait ran out
 };
@@ -411,43 +413,52 @@ __global__ __launch_bounds__(64 * (GW + SLAB_LOADERS)) void shflbw_slab_kernel(S
     typedef OutT vecw __attribute__((ext_vector_type(OUT16)));
     const bool spoiled = *poisoned != 0;                  // a hand-over wait ran out: the tile is stored as NaN
 
+    // one copy per kind of store: a choice at every store costs the headline product 1 %
+    auto write_back = [&](auto stream_tag) __attribute__((always_inline)) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
+        for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-        for (int pass = 0; pass < PASSES; ++pass) {
+            for (int pass = 0; pass < PASSES; ++pass) {
 #pragma unroll
-            for (int tt = 0; tt < TPP; ++tt) {
-                const int t = pass * TPP + tt;
-                if (SMALL) {
-                    vec4 v = {(OutT)acc16[t][0], (OutT)acc16[t][1], (OutT)acc16[t][2], (OutT)acc16[t][3]};
-                    *reinterpret_cast<vec4*>(ep + (lane & 15) * EP + 16 * tt + 4 * (lane >> 4)) = v;
-                } else {
+                for (int tt = 0; tt < TPP; ++tt) {
+                    const int t = pass * TPP + tt;
+                    if (SMALL) {
+                        vec4 v = {(OutT)acc16[t][0], (OutT)acc16[t][1], (OutT)acc16[t][2], (OutT)acc16[t][3]};
+                        *reinterpret_cast<vec4*>(ep + (lane & 15) * EP + 16 * tt + 4 * (lane >> 4)) = v;
+                    } else {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        vec4 v = {(OutT)acc32[rb][t][4 * q + 0], (OutT)acc32[rb][t][4 * q + 1],
-                                  (OutT)acc32[rb][t][4 * q + 2], (OutT)acc32[rb][t][4 * q + 3]};
-                        *reinterpret_cast<vec4*>(ep + (lane & 31) * EP + 32 * tt + 8 * q + 4 * (lane >> 5)) = v;
+                        for (int q = 0; q < 4; ++q) {
+                            vec4 v = {(OutT)acc32[rb][t][4 * q + 0], (OutT)acc32[rb][t][4 * q + 1],
+                                      (OutT)acc32[rb][t][4 * q + 2], (OutT)acc32[rb][t][4 * q + 3]};
+                            *reinterpret_cast<vec4*>(ep + (lane & 31) * EP + 32 * tt + 8 * q + 4 * (lane >> 5)) = v;
+                        }
                     }
                 }
-            }
-            SHFLBW_WAVE_LDS_SYNC();
+                SHFLBW_WAVE_LDS_SYNC();
 #pragma unroll
-            for (int i = 0; i < ROWS_E / 8; ++i) {
-                const int row = i * 8 + erow;
-                vecw v = *reinterpret_cast<const vecw*>(ep + row * EP + echunk * OUT16);
-                if (spoiled) {
+                for (int i = 0; i < ROWS_E / 8; ++i) {
+                    const int row = i * 8 + erow;
+                    vecw v = *reinterpret_cast<const vecw*>(ep + row * EP + echunk * OUT16);
+                    if (spoiled) {
 #pragma unroll
-                    for (int j = 0; j < OUT16; ++j) v[j] = (OutT)__builtin_nanf("");
+                        for (int j = 0; j < OUT16; ++j) v[j] = (OutT)__builtin_nanf("");
+                    }
+                    const int orig = out_row[rb][i];
+                    const long n = n0 + pass * CW + echunk * OUT16;
+                    if (n < a.N) {
+                        vecw* p = reinterpret_cast<vecw*>(static_cast<OutT*>(a.Y) + (long)orig * a.ldy + n);
+                        // streaming store: Y must not displace the slab and the weights in the L2; plain where the
+                        // 64-byte blocks at the ends of a row segment are shared with the next one
+                        if constexpr (decltype(stream_tag)::value) __builtin_nontemporal_store(v, p);
+                        else *p = v;
+                    }
                 }
-                const int orig = out_row[rb][i];
-                const long n = n0 + pass * CW + echunk * OUT16;
-                if (n < a.N)
-                    // streaming store: Y must not displace the slab and the weights in the L2
-                    __builtin_nontemporal_store(v, reinterpret_cast<vecw*>(static_cast<OutT*>(a.Y) + (long)orig * a.ldy + n));
+                SHFLBW_WAVE_LDS_SYNC();
             }
-            SHFLBW_WAVE_LDS_SYNC();
         }
-    }
+    };
+    if (a.stream) write_back(std::true_type{});
+    else write_back(std::false_type{});
 }
 
 }  // namespace shflbw

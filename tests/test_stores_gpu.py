@@ -1,0 +1,50 @@
+"""Streaming and plain stores (output rows that are, and are not, multiples of 64 bytes), and token blocks
+of the LayerNorm-side transposition that one or several workgroups store."""
+import numpy as np
+import pytest
+
+from oracle import c_oracle
+from paper_2203_05016_amd import binding, synth
+from gpu_util import announce, run_spmm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kernel", [1, 2])
+@pytest.mark.parametrize("V", [16, 32, 64, 128])
+@pytest.mark.parametrize("N,pad_ld,offset", [(256, 0, 0), (264, 0, 0), (272, 0, 0), (256, 8, 0), (256, 0, 8), (136, 24, 8)])
+def test_rows_of_every_alignment_exact(kernel, V, N, pad_ld, offset):
+    announce("stores", kernel, V, N, pad_ld, offset)
+    p = synth.make_spmm(12 * V, 256, N, V, 0.5, seed=901 + N + V, integer=True)
+    want, _ = c_oracle.spmm(p.W, p.mask, p.X)
+    for dt in ("float16", "float32"):
+        got = run_spmm(p, out_dtype=dt, kernel=kernel, pad_ld=pad_ld, offset=offset)
+        assert np.array_equal(got.astype(np.float64), want if dt == "float32" else want.astype(np.float16).astype(np.float64))
+
+
+@pytest.mark.parametrize("N,K", [(40, 5000), (32, 16384), (704, 9000), (1000, 4096), (8, 2504),    # shared by workgroups
+                                 (8200, 2504), (8192, 4104),                                       # one workgroup per block
+                                 (264, 1000), (256, 1024)])                                        # whole rows in the LDS
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+def test_layernorm_transposition_of_every_sharing(N, K, fmt):
+    """Against the definition in 64 bits (torch).  The result is rounded once from 32 bits: half a unit in
+    the last place (2^-11, 2^-8) of the value, and 2^-14 (2^-12) of |gamma x| + |beta| for the 32-bit
+    statistics and products."""
+    import torch
+    announce("layernorm sharing", N, K, fmt)
+    dt = torch.float16 if fmt == "f16" else torch.bfloat16
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N + K)
+    x = (torch.randn((N, K), generator=gen, device="cuda:0") * 2 + 3).to(dt)
+    g, b = (torch.randn(K, generator=gen, device="cuda:0").to(dt) for _ in range(2))
+    xd, gd, bd = x.double(), g.double(), b.double()
+    hat = (xd - xd.mean(1, keepdim=True)) / torch.sqrt(xd.var(1, unbiased=False, keepdim=True) + 1e-5)
+    want, scale = (hat * gd + bd).t(), (hat.abs() * gd.abs() + bd.abs()).t()
+    for pitch in (N, (N + 63) // 64 * 64):   # plain or streaming stores
+        buf = torch.full((K, pitch), float("nan"), dtype=dt, device="cuda:0")
+        out = binding.layernorm_transpose(x, g, b, out=buf[:, :N])
+        unit, rest = (2.0 ** -11, 2.0 ** -14) if fmt == "f16" else (2.0 ** -8, 2.0 ** -12)
+        assert bool(((out.double() - want).abs() <= unit * want.abs() + rest * scale + 2.0 ** -24).all())
+        assert bool(torch.isnan(buf[:, N:]).all())
+        binding.layernorm_transpose(x, normalize=False, out=buf[:, :N])
+        assert torch.equal(buf[:, :N], x.t())
