@@ -183,8 +183,8 @@ int shflbw_set_wait_limit(shflbw_matrix* A, int tries);
  *  Y  device, M x N of ydtype (the matrix's wdtype, or SHFLBW_F32), leading dimension
  *     ldy >= N.  Must not overlap X.
  * N == 0 is a no-op.  Groups without kept columns produce zero rows.
- * Fast path: N, ldx, ldy multiples of 8 and 16-byte aligned bases; other
- * shapes take a slower element-wise path with the same result.
+ * Fastest: N, ldx, ldy multiples of 8 and 16-byte aligned bases (rows of Y
+ * multiples of 64 bytes); other shapes give the same result more slowly.
  */
 int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int64_t ldy,
                 int64_t N, shflbw_dtype ydtype, void* stream);
@@ -219,11 +219,13 @@ int shflbw_spmm_unbound(const shflbw_matrix* A, const void* X, int64_t ldx, void
  *  in   device, the matrix's wdtype: [batch][C_in][H][W] (NCHW) or [C_in][H][W][batch] (CHWN).
  *  out  device, ydtype (the matrix's wdtype, or SHFLBW_F32): [batch][C_out][H_out][W_out] or [C_out][H_out][W_out][batch],
  *       H_out = (H + 2*pad_h - R)/stride_h + 1, W_out likewise.
- * A workgroup copies the part of the input its output positions can touch into
- * LDS once and gathers from there; inputs with too many channels for that take
- * the per-wave gather kernel.
+ * Tensors with runs of 8 along the innermost dimension (CHWN: 8 images or more;
+ * NCHW: unit stride along x, 8 output columns or more, at most one column of
+ * padding) take the per-wave gather kernel; others, and dense or fine-grained
+ * NCHW products, a kernel whose workgroups copy the part of the input their
+ * output positions can touch into LDS once and gather from there.
  * A 1x1 convolution with unit stride and no padding is the linear-layer
- * product itself (CHWN: one matrix; NCHW with H*W a multiple of 4: one per
+ * product itself (CHWN: one matrix; NCHW with H*W of 8 or more: one per
  * image, all in one launch) and runs as shflbw_spmm does.
  */
 int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out,
