@@ -289,7 +289,6 @@ bool plan_conv(const shflbw_matrix* A, int B, int C, int H, int W, int R, int S,
     a.gblocks = gblocks;
     a.in_bytes_total = (unsigned)in_total;
     a.gpb = gpb;
-    a.uniform_steps = A->uniform_steps;
     {
         const int tiles = (th * tw * tb + 31) / 32;
         const int spare = CONV_GW / gpb;   // wavefronts per group
@@ -313,7 +312,9 @@ int launch_conv_nt(const shflbw_matrix* A, ConvArgs& a, size_t lds_bytes, hipStr
 {
     if constexpr (!SP)
         if (a.stage_pairs == 1) return launch_conv_nt<V, NT, OutT, BF, true>(A, a, lds_bytes, stream);
+    // what belongs to the matrix itself and not to its sizes, for which alone a plan is kept
     a.A = view_of(A);
+    a.uniform_steps = A->uniform_steps;
     // the attribute is raised once per kernel and device, to the most any box can ask for
     static thread_local int raised_on = -1;
     int dev = 0;
@@ -647,14 +648,17 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         }
     }
     if (A->tune_kernel != 1 && A->tune_kernel != 3) {
-        // the plan depends on the matrix and the geometry only: keep the last one
-        struct PlanKey { const shflbw_matrix* A; int64_t nnz; int v[14]; };
-        static thread_local PlanKey last_key = {nullptr, 0, {0}};
+        // the plan depends on the sizes below only (not on which matrix has them): keep the last one
+        struct PlanKey {
+            int64_t nnz;
+            int K, V, M, batch, C, H, W, R, S, sh, sw, ph, pw, layout;   // no padding: compared as bytes
+        };
+        static_assert(sizeof(PlanKey) == 8 + 14 * 4, "compared as bytes");
+        static thread_local PlanKey last_key = {};
         static thread_local bool last_ok = false;
         static thread_local ConvArgs last_args;
         static thread_local size_t last_lds = 0;
-        const PlanKey key = {A, A->nnz, {A->K, A->V, A->G, batch, C_in, H, W, R * 65536 + S,
-                                         stride_h * 65536 + stride_w, pad_h, pad_w, (int)layout, A->M, 0}};
+        const PlanKey key = {A->nnz, A->K, A->V, A->M, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, (int)layout};
         if (memcmp(&key, &last_key, sizeof key) != 0) {
             last_ok = plan_conv(A, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo,
                                 layout == SHFLBW_CHWN, last_args, last_lds);
