@@ -5,7 +5,6 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
-#include <string>
 
 #include "gather_kernel.hip"
 #include "slab_kernel.hip"
@@ -31,16 +30,14 @@ __global__ void clear_status_kernel(int* word)
 
 int hip_fail(hipError_t e, const char* what)
 {
-    return fail(SHFLBW_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
+    return fail(SHFLBW_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// "name<V,second,operand format,output format>" for shflbw_last_kernel
-std::string kernel_name(const char* base, int V, int second, bool f32_out, bool bf)
+// "name<V,second,operand format,output format and more>" for shflbw_last_kernel
+KernelName kernel_name(const char* base, int V, int second, bool f32_out, bool bf, const char* more = "")
 {
-    char buf[128];
-    snprintf(buf, sizeof buf, "%s<%d,%d,%s,%s>", base, V, second, bf ? "bf16" : "f16",
-             f32_out ? "f32 out" : (bf ? "bf16 out" : "f16 out"));
-    return buf;
+    return KernelName("%s<%d,%d,%s,%s%s>", base, V, second, bf ? "bf16" : "f16", f32_out ? "f32 out" : bf ? "bf16 out" : "f16 out",
+                      more);
 }
 
 PackedView view_of(const shflbw_matrix* A)
@@ -93,8 +90,8 @@ int launch_slab(const shflbw_matrix* A, const void* X, long ldx, void* Y, long l
                        stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    static const std::string& name = *new std::string(kernel_name("shflbw_slab_kernel", V, GW, sizeof(OutT) == 4, BF));
-    note_kernel(name.c_str());
+    static const KernelName name = kernel_name("shflbw_slab_kernel", V, GW, sizeof(OutT) == 4, BF);
+    note_kernel(name.text);
     return SHFLBW_OK;
 }
 
@@ -331,12 +328,8 @@ int launch_conv_nt(const shflbw_matrix* A, ConvArgs& a, size_t lds_bytes, hipStr
                        stream, a);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
-    static const std::string& name = *new std::string([] {
-        std::string s = kernel_name("shflbw_conv_kernel", V, NT, sizeof(OutT) == 4, BF);
-        if (SP) s.insert(s.size() - 1, ",4-byte staging");
-        return s;
-    }());
-    note_kernel(name.c_str());
+    static const KernelName name = kernel_name("shflbw_conv_kernel", V, NT, sizeof(OutT) == 4, BF, SP ? ",4-byte staging" : "");
+    note_kernel(name.text);
     return SHFLBW_OK;
 }
 
@@ -529,9 +522,9 @@ int shflbw_spmm_unbound(const shflbw_matrix* A, const void* X, int64_t ldx, void
     using namespace shflbw;
     if (!A) return fail(SHFLBW_ERR_NULL_ARG, "A is NULL");
     if (A->dev_bytes > STATIC_IMAGE_BYTES)
-        return fail(SHFLBW_ERR_BAD_SHAPE, "packed matrix of " + std::to_string(A->dev_bytes) +
-                    " bytes exceeds the library's static device image of " + std::to_string(STATIC_IMAGE_BYTES) +
-                    " bytes (SHFLBW_UNBOUND_MAX_BYTES): bind it to a buffer of your own and call shflbw_spmm");
+        return fail(SHFLBW_ERR_BAD_SHAPE, "packed matrix of %zu bytes exceeds the library's static device image of %zu "
+                    "bytes (SHFLBW_UNBOUND_MAX_BYTES): bind it to a buffer of your own and call shflbw_spmm",
+                    A->dev_bytes, STATIC_IMAGE_BYTES);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");

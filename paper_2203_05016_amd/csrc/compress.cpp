@@ -3,15 +3,15 @@
 // vectors stitched into V x TK tiles in matrix-core operand order.
 // No HIP calls here: everything in this file works without a GPU.
 #include <algorithm>
+#include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <new>
-#include <string>
 
 #include "shflbw_internal.h"
 
 namespace {
-thread_local std::string g_last_error;
+thread_local char g_last_error[512] = "";
 thread_local const char* g_last_kernel = "";
 thread_local const void* g_base_override = nullptr;
 
@@ -68,9 +68,12 @@ void arrange_step(const int32_t* c, int len, int V, int* slot_of)
 }  // namespace
 
 namespace shflbw {
-int fail(int status, const std::string& detail)
+int fail(int status, const char* format, ...)
 {
-    g_last_error = detail;
+    va_list args;
+    va_start(args, format);
+    vsnprintf(g_last_error, sizeof g_last_error, format, args);
+    va_end(args);
     return status;
 }
 void note_kernel(const char* name) { g_last_kernel = name; }
@@ -80,7 +83,7 @@ void set_device_base_override(const void* base) { g_base_override = base; }
 
 extern "C" {
 
-const char* shflbw_last_error(void) { return g_last_error.c_str(); }
+const char* shflbw_last_error(void) { return g_last_error; }
 const char* shflbw_last_kernel(void) { return g_last_kernel; }
 
 const char* shflbw_status_string(int status)
@@ -129,9 +132,7 @@ int shflbw_compress(const void* W, int ldw, const uint8_t* mask, const int32_t* 
         for (int i = 0; i < M; ++i) {
             int r = perm ? perm[i] : i;
             if (r < 0 || r >= M || seen[r]) {
-                char buf[96];
-                snprintf(buf, sizeof buf, "perm[%d] = %d is out of range or repeated", i, r);
-                return fail(SHFLBW_ERR_BAD_PERM, buf);
+                return fail(SHFLBW_ERR_BAD_PERM, "perm[%d] = %d is out of range or repeated", i, r);
             }
             seen[r] = 1;
             A->row_indices[i] = r;
@@ -147,12 +148,10 @@ int shflbw_compress(const void* W, int ldw, const uint8_t* mask, const int32_t* 
                     const uint8_t* mi = mask + (size_t)rows[i] * K;
                     for (int k = 0; k < K; ++k)
                         if ((m0[k] != 0) != (mi[k] != 0)) {
-                            char buf[160];
-                            snprintf(buf, sizeof buf,
-                                     "group %d: stored row %d (original row %d) differs from the "
-                                     "group's first row at column %d",
-                                     g, g * V + i, rows[i], k);
-                            return fail(SHFLBW_ERR_BAD_PATTERN, buf);
+                            return fail(SHFLBW_ERR_BAD_PATTERN,
+                                        "group %d: stored row %d (original row %d) differs from the "
+                                        "group's first row at column %d",
+                                        g, g * V + i, rows[i], k);
                         }
                 }
                 for (int k = 0; k < K; ++k)

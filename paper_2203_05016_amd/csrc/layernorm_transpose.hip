@@ -28,7 +28,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <string>
 #include <type_traits>
 
 #include "shflbw.h"
@@ -710,15 +709,15 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         static thread_local int raised_on[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
         int dev = 0;
         hipError_t ea = hipGetDevice(&dev);
-        if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(ea));
+        if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(ea));
         if (raised_on[which] != dev) {
             ea = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(ea));
+            if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(ea));
             raised_on[which] = dev;
         }
         hipLaunchKernelGGL(fn, dim3((unsigned)rwgs), dim3(1024), bytes, st, a, pitch);
         hipError_t el = hipGetLastError();
-        if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(el));
+        if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(el));
         return SHFLBW_OK;
     }
     if (K <= 16384) {
@@ -752,15 +751,15 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
                                                   -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
         int dev = 0;
         hipError_t ea = hipGetDevice(&dev);
-        if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipGetDevice: ") + hipGetErrorString(ea));
+        if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(ea));
         if (raised_reg[which] != dev) {
             ea = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(ea));
+            if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(ea));
             raised_reg[which] = dev;
         }
         hipLaunchKernelGGL(fn, dim3((unsigned)rwgs, ry), dim3(1024), bytes, st, a);
         hipError_t el = hipGetLastError();
-        if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(el));
+        if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(el));
         return SHFLBW_OK;
     }
     // split the features over grid.y until there are about two workgroups per CU
@@ -780,6 +779,6 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         else hipLaunchKernelGGL((layernorm_transpose_kernel<false, false>), sgrid, sblock, 0, st, a);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(SHFLBW_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
+    if (e != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(e));
     return SHFLBW_OK;
 }

@@ -3,8 +3,9 @@
 #ifndef SHFLBW_INTERNAL_H
 #define SHFLBW_INTERNAL_H
 
+#include <cstdarg>
 #include <cstdint>
-#include <string>
+#include <cstdio>
 #include <vector>
 
 #include "shflbw.h"
@@ -92,7 +93,20 @@ static_assert((SLAB_ZERO_ROW + 1) * SLAB_ROW_BYTES / 16 <= (1 << 13), "LDS offse
 // two bits so that four consecutive rows - every quad of a dense matrix - land in four
 // different bank groups; bit 1 varies with the next row bit.
 constexpr int slab_swizzle(int r) { return ((r & 3) << 2) | (((r >> 2) & 1) << 1); }
-int fail(int status, const std::string& detail);  // records the thread-local text, returns status
+// Records the thread-local text (printf form, cut at 511 characters) and returns status.  Allocates nothing: the
+// entry points have C linkage, and an exception must not leave them.
+int fail(int status, const char* format, ...) __attribute__((format(printf, 2, 3)));
+// What shflbw_last_kernel reports for one instantiation; made once, held until the process ends.
+struct KernelName {
+    char text[128];
+    __attribute__((format(printf, 2, 3))) explicit KernelName(const char* format, ...)
+    {
+        va_list args;
+        va_start(args, format);
+        vsnprintf(text, sizeof text, format, args);
+        va_end(args);
+    }
+};
 // records what the calling thread launched last (shflbw_last_kernel); keeps the pointer: name lives until the
 // process ends (each launcher builds its own once, not per launch)
 void note_kernel(const char* name);
