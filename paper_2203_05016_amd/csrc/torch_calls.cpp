@@ -86,6 +86,18 @@ bool int_pair(PyObject* o, int& a, int& b)
            small_int(PyTuple_GET_ITEM(o, 1), b);
 }
 
+// Releases the interpreter lock for as long as it lives, and holds it again when an exception passes by.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <class F>
+int unlocked(F&& f)
+{
+    Unlocked u;
+    return f();
+}
+
 template <class F>
 PyObject* guarded(F&& f)
 {
@@ -117,11 +129,9 @@ PyObject* spmm(PyObject*, PyObject* const* args, Py_ssize_t n)
         void* y = Y->data_ptr();
         void* stream;
         if (!current_stream(stream)) return nullptr;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = g_spmm(p->A, x, ldx, y, ldy, N, (shflbw_dtype)yd, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(rc);
+        return PyLong_FromLong(unlocked([&] {
+            return g_spmm(p->A, x, ldx, y, ldy, N, (shflbw_dtype)yd, stream);
+        }));
     });
 }
 
@@ -156,12 +166,10 @@ PyObject* conv2d(PyObject*, PyObject* const* args, Py_ssize_t n)
         void* y = out->data_ptr();
         void* stream;
         if (!current_stream(stream)) return nullptr;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = g_conv2d(p->A, x, y, (int)B, (int)C, (int)H, (int)W, R, S, sh, sw, ph, pw, chwn ? SHFLBW_CHWN : SHFLBW_NCHW,
-                      (shflbw_dtype)yd, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(rc);
+        return PyLong_FromLong(unlocked([&] {
+            return g_conv2d(p->A, x, y, (int)B, (int)C, (int)H, (int)W, R, S, sh, sw, ph, pw, chwn ? SHFLBW_CHWN : SHFLBW_NCHW,
+                            (shflbw_dtype)yd, stream);
+        }));
     });
 }
 
@@ -194,11 +202,9 @@ PyObject* layernorm_transpose(PyObject*, PyObject* const* args, Py_ssize_t n)
         const int64_t ldx = N > 1 ? x->stride(0) : K, ldo = K > 1 ? out->stride(0) : N;
         void* stream;
         if (!current_stream(stream)) return nullptr;
-        int rc;
-        Py_BEGIN_ALLOW_THREADS
-        rc = g_layernorm(xp, ldx, g, b, eps, normalize, y, ldo, N, (int)K, dt == at::kBFloat16 ? SHFLBW_BF16 : SHFLBW_F16, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(rc);
+        return PyLong_FromLong(unlocked([&] {
+            return g_layernorm(xp, ldx, g, b, eps, normalize, y, ldo, N, (int)K, dt == at::kBFloat16 ? SHFLBW_BF16 : SHFLBW_F16, stream);
+        }));
     });
 }
 

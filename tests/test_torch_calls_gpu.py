@@ -84,3 +84,30 @@ def test_conv2d_and_layernorm_plain_case_and_what_is_handed_back():
     for args in ((t, g.float(), b, 1e-5, True, out), (t, g[:63], b, 1e-5, True, out), (t.cpu(), g, b, 1e-5, True, out),
                  (t, g, b, 1, True, out), (t, g, b, 1e-5, 1, out), (t, g, b, 1e-5, True, out[:, :23]), (t.t(), g, b, 1e-5, True, out)):
         assert native.layernorm_transpose(*args) is None
+
+
+def test_an_exception_out_of_the_library_is_handed_back():
+    """The interpreter lock is held again when a C++ exception passes by (libstdc++'s own function that
+    throws std::bad_alloc stands in for the library's entry points)."""
+    import ctypes
+    import torch
+    announce("torch calls, exception")
+    p = synth.make_spmm(64, 96, 40, 32, 0.5, seed=11)
+    A = binding.compress(p.W, p.mask, p.perm, 32).bind_device("cuda:0")
+    native, L = binding.calls(), binding.lib()
+    X, Y = to_device(p.X), torch.empty((64, 40), dtype=torch.float16, device="cuda:0")
+    img, out = torch.zeros((1, 96, 2, 4), dtype=torch.float16, device="cuda:0"), torch.empty((1, 64, 2, 4), dtype=torch.float16, device="cuda:0")
+    t, tt = torch.zeros((40, 64), dtype=torch.float16, device="cuda:0"), torch.empty((64, 40), dtype=torch.float16, device="cuda:0")
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    throws = address(ctypes.CDLL("libstdc++.so.6")._ZSt17__throw_bad_allocv)
+    raw_stream = torch._C._cuda_getCurrentRawStream
+    native.connect(throws, throws, throws, raw_stream)
+    try:
+        for _ in range(3):
+            assert native.spmm(A._plan, X, Y) is None
+            assert native.conv2d(A._plan, img, 1, 1, (1, 1), (0, 0), False, out) is None
+            assert native.layernorm_transpose(t, None, None, 1e-5, True, tt) is None
+    finally:
+        native.connect(address(L.shflbw_spmm), address(L.shflbw_conv2d), address(L.shflbw_layernorm_transpose), raw_stream)
+    assert native.spmm(A._plan, X, Y) == 0
+    assert np.array_equal(to_host(Y), to_host(A.spmm(X)))
