@@ -19,7 +19,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libshflbw.so")
 CALLS_PATH = os.path.join(_HERE, "_torch_calls.so")
 _lib = None
-_calls = None   # native calls on torch tensors (csrc/torch_calls.cpp), loaded with the first use on a GPU
+_calls = None   # native calls on torch tensors (csrc/torch_calls.cpp), loaded with the first use; False: none
 
 EXPORTS = [
     "shflbw_compress", "shflbw_pattern_search", "shflbw_destroy", "shflbw_info", "shflbw_row_indices",
@@ -90,24 +90,36 @@ def lib():
 
 
 def calls():
-    """The native calls on plain torch tensors, connected to the library.  Like the library
-    they are required: there is no other build of the plain case."""
+    """The native calls on plain torch tensors, connected to the library; False where there are none
+    for this interpreter and this torch.  They make the same checks as the Python code below, faster; the
+    library they call is the same."""
     global _calls
     if _calls is None:
-        import importlib.machinery
-        import importlib.util
-        import torch
-        if not os.path.exists(CALLS_PATH):
-            raise RuntimeError("%s is missing: build it with `python -m paper_2203_05016_amd.build`" % CALLS_PATH)
-        loader = importlib.machinery.ExtensionFileLoader("_torch_calls", CALLS_PATH)
-        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_torch_calls", loader))
-        loader.exec_module(m)
-        L = lib()
-        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-        m.connect(address(L.shflbw_spmm), address(L.shflbw_conv2d), address(L.shflbw_layernorm_transpose),
-                  torch._C._cuda_getCurrentRawStream)
-        _calls = m
+        try:
+            _calls = _load_calls()
+        except ImportError as e:
+            import warnings
+            warnings.warn("native calls not in use (%s); build them with `python -m paper_2203_05016_amd.build`" % e)
+            _calls = False
     return _calls
+
+
+def _load_calls():
+    import importlib.machinery
+    import importlib.util
+    import torch
+    if not os.path.exists(CALLS_PATH):
+        raise ImportError("%s is missing" % CALLS_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("_torch_calls", CALLS_PATH)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_torch_calls", loader))
+    loader.exec_module(m)
+    if m.TORCH_VERSION != str(torch.__version__):
+        raise ImportError("built for torch %s, this is %s" % (m.TORCH_VERSION, torch.__version__))
+    L = lib()
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    m.connect(address(L.shflbw_spmm), address(L.shflbw_conv2d), address(L.shflbw_layernorm_transpose),
+              torch._C._cuda_getCurrentRawStream)
+    return m
 
 
 def status_string(status):
@@ -226,8 +238,8 @@ class Matrix:
         _check(lib().shflbw_bind_device(self._h, ctypes.c_void_p(buf.data_ptr()),
                                         _stream_ptr(stream)))
         self._dev = buf
-        info = self.info()
-        self._plan = calls().plan(self._h.value, info["M"], info["K"], self.bf16, buf.device.index)
+        native, info = calls(), self.info()
+        self._plan = native.plan(self._h.value, info["M"], info["K"], self.bf16, buf.device.index) if native else None
         return self
 
     def _require_on_bound_device(self, t, what):
@@ -351,8 +363,8 @@ def layernorm_transpose(x, gamma=None, beta=None, eps=1e-5, normalize=True, out=
     """shflbw_layernorm_transpose on device tensors: x (N tokens, K features)
     float16 or bfloat16 with unit feature stride; returns the (K, N) matrix
     shflbw_spmm takes as X."""
-    if out is not None and stream is None:
-        rc = (_calls or calls()).layernorm_transpose(x, gamma, beta, eps, normalize, out)   # None: not the plain case
+    if out is not None and stream is None and (_calls or calls()):
+        rc = _calls.layernorm_transpose(x, gamma, beta, eps, normalize, out)   # None: not the plain case
         if rc is not None:
             if rc < 0:
                 _check(rc)

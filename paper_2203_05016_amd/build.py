@@ -5,7 +5,7 @@
 
 The results are ``paper_2203_05016_amd/libshflbw.so``, which links against the HIP
 runtime only (no torch), and ``paper_2203_05016_amd/_torch_calls.so``, the binding's
-native calls on torch tensors (host code, g++).
+native calls on torch tensors (host code, g++; left out where torch or its headers are missing).
 """
 import os
 import subprocess
@@ -29,12 +29,21 @@ TORCH_CALLS = os.path.join(HERE, "_torch_calls.so")
 
 
 def _torch_calls_command(out):
+    """The compiler's command line, or None without torch or the headers of torch or Python: the
+    library needs neither, and the binding does without the native calls."""
     import sysconfig
-    import torch
-    from torch.utils import cpp_extension
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        return None
     libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
     includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    for header in ("ATen/core/Tensor.h", "Python.h"):
+        if not any(os.path.exists(os.path.join(i, header)) for i in includes):
+            return None
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+             "-DSHFLBW_TORCH_VERSION=\"%s\"" % torch.__version__,
              os.path.join(CSRC, "torch_calls.cpp"), "-o", out] + sum([["-isystem", i] for i in includes], []) +
             ["-L", libdir, "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"])
 
@@ -51,8 +60,9 @@ def build(verbose=True, extra=()):
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
         objs.append(obj)
     calls_tmp = TORCH_CALLS + ".tmp.%d" % os.getpid()
-    procs.append(("torch_calls.cpp", subprocess.Popen(_torch_calls_command(calls_tmp), stdout=subprocess.PIPE,
-                                                      stderr=subprocess.STDOUT)))
+    calls_command = _torch_calls_command(calls_tmp)
+    if calls_command:
+        procs.append(("torch_calls.cpp", subprocess.Popen(calls_command, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     for src, p in procs:
         out = p.communicate()[0].decode()
         keep = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
@@ -64,7 +74,12 @@ def build(verbose=True, extra=()):
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
     os.replace(tmp, LIB)
-    os.replace(calls_tmp, TORCH_CALLS)
+    if calls_command:
+        os.replace(calls_tmp, TORCH_CALLS)
+    else:
+        if os.path.exists(TORCH_CALLS):   # of another torch
+            os.remove(TORCH_CALLS)
+        print("no torch or no headers: built without %s" % os.path.basename(TORCH_CALLS))
     if verbose:
         print("built %s in %.1f s" % (LIB, time.time() - t0))
     return LIB

@@ -251,4 +251,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_torch_calls", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__torch_calls(void) { return PyModule_Create(&module); }
+// The caller compares TORCH_VERSION with the torch it runs on before any call: tensors are read in its own layout.
+PyMODINIT_FUNC PyInit__torch_calls(void)
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "TORCH_VERSION", SHFLBW_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
