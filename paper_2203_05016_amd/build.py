@@ -7,6 +7,7 @@ The results are ``paper_2203_05016_amd/libshflbw.so``, which links against the H
 runtime only (no torch), and ``paper_2203_05016_amd/_torch_calls.so``, the binding's
 native calls on torch tensors (host code, g++; left out where torch or its headers are missing).
 """
+import contextlib
 import os
 import subprocess
 import sys
@@ -48,35 +49,55 @@ def _torch_calls_command(out):
             ["-L", libdir, "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"])
 
 
+@contextlib.contextmanager
+def _temporary(path):
+    """A name beside path to build it under; what is still there afterwards (a step failed) is removed."""
+    tmp = path + ".tmp.%d" % os.getpid()
+    try:
+        yield tmp
+    finally:
+        with contextlib.suppress(FileNotFoundError):
+            os.remove(tmp)
+
+
+def _run_all(jobs, verbose):
+    """Runs the (name, command) jobs side by side; raises on a failure, when all have ended (none writes later)."""
+    procs = [(name, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)) for name, cmd in jobs]
+    try:
+        for name, p in procs:
+            out = p.communicate()[0].decode()
+            keep = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
+            if p.returncode != 0:
+                sys.stderr.write(out)
+                raise RuntimeError("compiler failed on %s" % name)
+            if verbose and keep:
+                print("\n".join(keep))
+    finally:
+        for _, p in procs:
+            if p.returncode is None:
+                p.communicate()
+
+
 def build(verbose=True, extra=()):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    objs, procs = [], []
+    objs, jobs = [], []
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     t0 = time.time()
     for src in SOURCES:
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS + list(extra)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
+        jobs.append((src, [hipcc, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS + list(extra)))
         objs.append(obj)
-    calls_tmp = TORCH_CALLS + ".tmp.%d" % os.getpid()
-    calls_command = _torch_calls_command(calls_tmp)
-    if calls_command:
-        procs.append(("torch_calls.cpp", subprocess.Popen(calls_command, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
-    for src, p in procs:
-        out = p.communicate()[0].decode()
-        keep = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
-        if p.returncode != 0:
-            sys.stderr.write(out)
-            raise RuntimeError("compiler failed on %s" % src)
-        if verbose and keep:
-            print("\n".join(keep))
-    tmp = LIB + ".tmp.%d" % os.getpid()
-    subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
-    os.replace(tmp, LIB)
-    if calls_command:
-        os.replace(calls_tmp, TORCH_CALLS)
-    else:
+    with _temporary(LIB) as lib_tmp, _temporary(TORCH_CALLS) as calls_tmp:
+        calls_command = _torch_calls_command(calls_tmp)
+        if calls_command:
+            jobs.append(("torch_calls.cpp", calls_command))
+        _run_all(jobs, verbose)
+        subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", lib_tmp] + objs)
+        os.replace(lib_tmp, LIB)
+        if calls_command:
+            os.replace(calls_tmp, TORCH_CALLS)
+    if not calls_command:
         if os.path.exists(TORCH_CALLS):   # of another torch
             os.remove(TORCH_CALLS)
         print("no torch or no headers: built without %s" % os.path.basename(TORCH_CALLS))
@@ -95,12 +116,12 @@ def build_host_sanitized():
     UndefinedBehaviorSanitizer, as a library of its own for the CPU tests.  Returns
     (path of the library, path of the sanitizer runtime to preload)."""
     os.makedirs(os.path.dirname(HOST_SANITIZED_LIB), exist_ok=True)
-    tmp = HOST_SANITIZED_LIB + ".tmp.%d" % os.getpid()
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer",
-                           "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
-                           "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                           "-o", tmp] + [os.path.join(CSRC, f) for f in HOST_SOURCES])
-    os.replace(tmp, HOST_SANITIZED_LIB)
+    with _temporary(HOST_SANITIZED_LIB) as tmp:
+        subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer",
+                               "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                               "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                               "-o", tmp] + [os.path.join(CSRC, f) for f in HOST_SOURCES])
+        os.replace(tmp, HOST_SANITIZED_LIB)
     runtime = subprocess.check_output(["g++", "-print-file-name=libasan.so"]).decode().strip()
     return HOST_SANITIZED_LIB, os.path.realpath(runtime)
 
