@@ -525,12 +525,22 @@ constexpr bool uses_list()
     else return false;
 }
 
+// Wavefronts a SIMD must be able to hold.  V = 64, aligned rows, whole tiles of 64 columns: four (128 registers), two
+// workgroups of eight per CU; left alone the compiler takes 130 with 16-bit results, for one workgroup.
+template <int V, int WN, int WAVES, class Geom, int SPLIT>
+constexpr int gather_min_waves()
+{
+    if (V == 64 && WN == 64 && SPLIT == 1 && std::is_same<Geom, GeomLinearBuf>::value) return 4;
+    return (WAVES + 3) / 4;   // one workgroup
+}
+
 // SPLIT = 1: the wavefronts of a workgroup own different column tiles of one group.
 // SPLIT > 1 (too few tiles to fill the chip): SPLIT neighbouring wavefronts share one tile, each
 // takes a contiguous share of the group's k-steps; the partial accumulators of a row block meet in
 // the LDS, every wavefront of the tile adds up its share of them and stores its share of the rows.
 template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
+__global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, WAVES, Geom, SPLIT>()))
+void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
 {
     using S = GatherShape<V, WN>;
     constexpr int TK = S::TK, RB = S::RB, NT = S::NT, LPR = S::LPR, NLD = S::NLD;
@@ -598,28 +608,34 @@ __global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A,
                 for (int r = 0; r < 16; ++r) acc32[rb][t][r] = 0.f;
     }
 
-    // Original rows for the write-back, requested now so that its stores do not wait for them (with the
-    // step bounds that need no load: 1024 x 1024 by 4096 8.0 -> 7.4 us, 4096 x 4096 by 64 6.35 -> 5.95).
-    // Not where registers are short: more than two row blocks, or a geometry that keeps more than an
-    // offset per lane (unaligned rows and convolutions lose 1 to 3 %).
-    constexpr bool EARLY_ROWS = RB <= 2 && std::is_same<Geom, GeomLinearBuf>::value;
+    // Original rows for the write-back.  Those of the first EARLY row blocks are requested now, so that the
+    // stores do not wait for them (with the step bounds that need no load: 1024 x 1024 by 4096 8.0 -> 7.4 us,
+    // 4096 x 4096 by 64 6.35 -> 5.95), those of the second one of two after the last step.  Where registers
+    // allow it: four row blocks have none to spare, nor have geometries that keep more than an offset per lane
+    // (unaligned rows and convolutions lose 1 to 3 %).  Two row blocks early, V = 64 with 16-bit results, are
+    // a wavefront less per SIMD, which costs more than the wait: 8192 x 2048 by 4096 at 90 % 31.6 us without,
+    // 34.2 with both, 29.7 with one; 4096 x 1024 by 8192 20.7 / 21.5 / 18.0; 1024 x 1024 by 8192 9.1 / 8.5 / 8.4.
+    constexpr bool ROWS_AHEAD = RB <= 2 && std::is_same<Geom, GeomLinearBuf>::value;
+    constexpr int EARLY = !ROWS_AHEAD ? 0 : RB == 2 && SPLIT == 1 && sizeof(OutT) == 2 ? 1 : RB;
     constexpr int OPV = 16 / (int)sizeof(OutT);                      // values per 16 bytes
     // a store instruction of 16 bytes per lane: lanes per row and rows, without and with SPLIT
     constexpr int LPR_S = SPLIT > 1 ? WN / OPV : WN / ((int)sizeof(OutT) / 2) / OPV, RPI_S = 64 / LPR_S;
     constexpr int STORES_S = SPLIT > 1 ? (S::ROWS_E / RPI_S + SPLIT - 1) / SPLIT : S::ROWS_E / RPI_S;
-    int out_row[EARLY_ROWS ? RB : 1][STORES_S];
+    int out_row[ROWS_AHEAD ? RB : 1][STORES_S];
     const int32_t* rows_g = A.row_indices + (long)g * V;
     auto row_of = [&](int i) __attribute__((always_inline)) {         // stored row of this lane in its i-th store of a row block
         return SPLIT > 1 ? (part + i * SPLIT) * RPI_S + lane / LPR_S : i * RPI_S + lane / LPR_S;
     };
-    if constexpr (EARLY_ROWS) {
+    auto request_rows = [&](int rb) __attribute__((always_inline)) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
+        for (int i = 0; i < STORES_S; ++i) {
+            const int r = row_of(i);
+            out_row[rb][i] = rows_g[rb * 32 + (r < S::ROWS_E ? r : 0)];
+        }
+    };
+    if constexpr (ROWS_AHEAD) {
 #pragma unroll
-            for (int i = 0; i < STORES_S; ++i) {
-                const int r = row_of(i);
-                out_row[rb][i] = rows_g[rb * 32 + (r < S::ROWS_E ? r : 0)];
-            }
+        for (int rb = 0; rb < EARLY; ++rb) request_rows(rb);
     }
 
     // ---- pipeline registers
@@ -816,6 +832,10 @@ __global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A,
     }
     if (s0 < nsteps_r) batch(s0, std::false_type{}, std::false_type{});
     }
+    if constexpr (ROWS_AHEAD) {
+#pragma unroll
+        for (int rb = EARLY; rb < RB; ++rb) request_rows(rb);
+    }
     SHFLBW_WAVE_LDS_SYNC();
 
     if constexpr (SPLIT > 1) {
@@ -867,7 +887,7 @@ __global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A,
                     OutT tmp[OPV];
 #pragma unroll
                     for (int e = 0; e < OPV; ++e) tmp[e] = v[e];
-                    const int orig = EARLY_ROWS ? out_row[EARLY_ROWS ? rb : 0][i] : rows_g[rb * 32 + row];
+                    const int orig = ROWS_AHEAD ? out_row[ROWS_AHEAD ? rb : 0][i] : rows_g[rb * 32 + row];
                     geom.template store<OutT, OPV>(orig, n0 + lane % LPR_S * OPV, tmp);
                 }
             }
@@ -920,7 +940,7 @@ __global__ __launch_bounds__(64 * WAVES) void shflbw_gather_kernel(PackedView A,
                 OutT tmp[OPV];
 #pragma unroll
                 for (int e = 0; e < OPV; ++e) tmp[e] = v[e];
-                const int orig = EARLY_ROWS ? out_row[EARLY_ROWS ? rb : 0][i] : rows_g[rb * 32 + row];
+                const int orig = ROWS_AHEAD ? out_row[ROWS_AHEAD ? rb : 0][i] : rows_g[rb * 32 + row];
                 geom.template store<OutT, OPV>(orig, n0 + pass * CW + echunk * OPV, tmp);
             }
             SHFLBW_WAVE_LDS_SYNC();
