@@ -525,13 +525,17 @@ constexpr bool uses_list()
     else return false;
 }
 
-// Wavefronts a SIMD must be able to hold.  V = 64, aligned rows, whole tiles of 64 columns: four (128 registers), two
-// workgroups of eight per CU; left alone the compiler takes 130 with 16-bit results, for one workgroup.
-template <int V, int WN, int WAVES, class Geom, int SPLIT>
+// Wavefronts a SIMD must be able to hold.  Left alone, the compiler counts on one workgroup per CU: with four
+// wavefronts or fewer in it, a SIMD to each, it keeps the accumulators in registers of their own (V = 128: 328
+// registers, one wavefront per SIMD).  Two are asked for, and four (128 registers) for V = 64, which takes
+// up to 132 otherwise, two workgroups of eight becoming one (not for the split by 8, of which there is no more
+// than one workgroup per CU).  Us before -> after, splits by 2 and 4: 3x3, 56x56, 12 images, CHWN, 64 -> 128
+// channels, dense, V = 128: 24.9 -> 15.7; 3x3 / 2, 56x56, CHWN, 128 channels, V = 128 at 50 %: 17.4 -> 11.6;
+// 3x3, 56x56, 64 channels, V = 64 at 75 %: 12.8 -> 11.5; aligned products -1 to +2 %.
+template <int V, int WN, class Geom, int SPLIT>
 constexpr int gather_min_waves()
 {
-    if (V == 64 && WN == 64 && SPLIT == 1 && std::is_same<Geom, GeomLinearBuf>::value) return 4;
-    return (WAVES + 3) / 4;   // one workgroup
+    return V == 64 && WN == 64 && SPLIT < 8 && !std::is_same<Geom, GeomConv>::value ? 4 : 2;
 }
 
 // SPLIT = 1: the wavefronts of a workgroup own different column tiles of one group.
@@ -539,7 +543,7 @@ constexpr int gather_min_waves()
 // takes a contiguous share of the group's k-steps; the partial accumulators of a row block meet in
 // the LDS, every wavefront of the tile adds up its share of them and stores its share of the rows.
 template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, WAVES, Geom, SPLIT>()))
+__global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, Geom, SPLIT>()))
 void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
 {
     using S = GatherShape<V, WN>;

@@ -8,4 +8,12 @@ GATHER(32, 64, 8, _Float16, GeomLinearBuf, 1)
 GATHER(64, 64, 8, _Float16, GeomLinearBuf, 1)
 GATHER(64, 64, 8, float, GeomLinearBuf, 1)
 GATHER(128, 64, 8, _Float16, GeomLinearBuf, 1)
+GATHER(64, 64, 2, float, GeomLinearBuf, 2)
+GATHER(128, 64, 2, _Float16, GeomRows, 2)
+GATHER(64, 64, 8, _Float16, GeomConvRuns<false>, 1)
+GATHER(64, 64, 2, _Float16, GeomConvRuns<false>, 2)
+GATHER(64, 64, 4, _Float16, GeomConvRuns<false>, 4)
+GATHER(64, 64, 4, float, GeomConvRuns<true>, 4)
+GATHER(128, 64, 2, _Float16, GeomConvRuns<false>, 2)
+GATHER(128, 64, 4, _Float16, GeomConvRuns<true>, 4)
 }  // namespace shflbw

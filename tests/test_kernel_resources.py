@@ -18,6 +18,14 @@ WANTED = {
     (64, 64, 1, "16", "GeomLinearBuf"): 4,
     (64, 64, 1, "f32", "GeomLinearBuf"): 4,
     (128, 64, 1, "16", "GeomLinearBuf"): 2,
+    (64, 64, 2, "f32", "GeomLinearBuf"): 4,
+    (128, 64, 2, "16", "GeomRows"): 2,
+    (64, 64, 1, "16", "GeomConvRuns<false>"): 4,
+    (64, 64, 2, "16", "GeomConvRuns<false>"): 4,
+    (64, 64, 4, "16", "GeomConvRuns<false>"): 4,
+    (64, 64, 4, "f32", "GeomConvRuns<true>"): 4,
+    (128, 64, 2, "16", "GeomConvRuns<false>"): 2,
+    (128, 64, 4, "16", "GeomConvRuns<true>"): 2,
 }
 
 
