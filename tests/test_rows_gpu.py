@@ -46,3 +46,19 @@ def test_1x1_convolution_of_odd_images_exact(H, W, V, batch):
             torch.cuda.synchronize()
             assert "shflbw_gather_kernel" in binding.last_kernel()
             assert np.array_equal(to_host(out).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("batch,H,W,V,C", [(136, 8, 8, 32, 40), (160, 7, 7, 64, 72), (1100, 3, 3, 16, 64)])
+def test_1x1_convolution_of_many_images_exact(batch, H, W, V, C):
+    """More than 128 blocks of column tiles, with and without a number that eight divides: each XCD takes a
+    range of them."""
+    import torch
+    announce("rows, 1x1, many images", batch, H, W, V)
+    p = synth.make_conv(batch, C, H, W, 2 * V, 1, 1, V, 0.5, seed=451 + V, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (1, 1), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    out = torch.full((batch, 2 * V, H, W), float("nan"), dtype=torch.float32, device="cuda:0")
+    A.conv2d(to_device(p.conv["input"]), 1, 1, out=out)
+    torch.cuda.synchronize()
+    assert "split k-steps by 2" in binding.last_kernel() or batch == 1100
+    assert np.array_equal(to_host(out).astype(np.float64), want)
