@@ -129,6 +129,7 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     g.xbytes = (unsigned)xbytes;
     g.x_image = (long)x_image; g.y_image = (long)y_image;
     g.P = P; g.slots = (P + 7) / 8;
+    g.m_slots = g.slots == 1 ? 0xffffffffu : (unsigned)(((uint64_t)1 << 32) / (unsigned)g.slots);
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
     g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob);
     g.N = (long)images * g.slots * 8;

@@ -36,3 +36,20 @@ def test_k_steps_are_shared_where_that_pays(V, M, K, N, sparsity, shares):
     assert ("split k-steps by %d" % shares if shares > 1 else "whole tiles") in name, name
     want, _ = c_oracle.spmm(p.W, p.mask, p.X)
     assert np.array_equal(to_host(out).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("batch,H,W", [(1, 2, 4), (7, 3, 3), (5, 8, 1), (3, 1, 9), (70, 4, 5), (2, 61, 67), (513, 3, 3)])
+def test_images_of_any_number_of_slots(batch, H, W):
+    """One slot per image (8 positions), two (9), an exact number, and many images: the quotient that finds a
+    slot's image, with streaming and with plain stores."""
+    import torch
+    announce("choice, slots", batch, H, W)
+    p = synth.make_conv(batch, 24, H, W, 64, 1, 1, 32, 0.5, seed=971 + H * W, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (1, 1), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, 32).bind_device("cuda:0")
+    x = to_device(p.conv["input"])
+    for dt in (torch.float16, torch.float32):
+        out = torch.full((batch, 64, H, W), float("nan"), dtype=dt, device="cuda:0")
+        A.conv2d(x, 1, 1, out=out)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(out).astype(np.float64), want)
