@@ -641,7 +641,10 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     // (unaligned rows and convolutions lose 1 to 3 %).  Two row blocks early, V = 64 with 16-bit results, are
     // a wavefront less per SIMD, which costs more than the wait: 8192 x 2048 by 4096 at 90 % 31.6 us without,
     // 34.2 with both, 29.7 with one; 4096 x 1024 by 8192 20.7 / 21.5 / 18.0; 1024 x 1024 by 8192 9.1 / 8.5 / 8.4.
-    constexpr bool ROWS_AHEAD = RB <= 2 && std::is_same<Geom, GeomLinearBuf>::value;
+    // Two row blocks of 128 columns with 32-bit results take each row when it is stored: with the rows at hand the
+    // streaming stores come faster than they drain (8192 x 8192 by 4096 at 95 % 58.3 us, 61.7 with the rows at hand,
+    // 4096 x 4096 by 4096 at 90 % 29.1 and 30.9; but 8192 x 4096 by 8200, rows of no whole 64-byte blocks, 160 and 149).
+    constexpr bool ROWS_AHEAD = RB <= 2 && std::is_same<Geom, GeomLinearBuf>::value && !(RB == 2 && WN == 128 && sizeof(OutT) == 4);
     constexpr int EARLY = !ROWS_AHEAD ? 0 : RB == 2 && SPLIT == 1 && sizeof(OutT) == 2 ? 1 : RB;
     constexpr int OPV = 16 / (int)sizeof(OutT);                      // values per 16 bytes
     // a store instruction of 16 bytes per lane: lanes per row and rows, without and with SPLIT
