@@ -118,6 +118,9 @@ int dispatch_out(const shflbw_matrix* A, const Geom& geom, long N, shflbw_dtype 
     return run_gather_f16(A, geom, N, ydtype, stream);
 }
 
+// what stream_stores calls reads
+double reads_of(const shflbw_matrix* A) { return (double)A->nnz / ((double)A->M * A->V); }
+
 // `images` products over rows of P columns each (GeomRows)
 int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image, void* Y, int64_t ldy,
              int64_t y_image, int P, int images, int64_t xbytes, shflbw_dtype ydtype, hipStream_t stream)
@@ -131,7 +134,7 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     g.P = P; g.slots = (P + 7) / 8;
     g.m_slots = g.slots == 1 ? 0xffffffffu : (unsigned)(((uint64_t)1 << 32) / (unsigned)g.slots);
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
-    g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob);
+    g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob, reads_of(A), images > 1);
     g.N = (long)images * g.slots * 8;
     return dispatch_out(A, g, g.N, ydtype, stream);
 }
@@ -171,7 +174,7 @@ bool fill_conv_runs(const shflbw_matrix* A, GeomConvRuns<CHWN>& g, const void* i
     // 256 channels: 55 us against 72).  CHWN: by the bytes of a position's images (50 of them, 30x30, 64 -> 256
     // channels: 17.0 streaming, 15.0 plain; 32 of them, 56x56 / 2: 11.1 and 11.6)
     g.stream = !CHWN || stream_stores(out, (int64_t)B * out_bytes, out_bytes, (double)in_total,
-                                      (double)A->M * Ho * Wo * B * out_bytes);
+                                      (double)A->M * Ho * Wo * B * out_bytes, reads_of(A));
     g.osM = CHWN ? (long)Ho * Wo * B : (long)Ho * Wo;
     g.osB = CHWN ? 0 : (long)A->M * Ho * Wo;
     g.slots = ((CHWN ? B : Wo) + 7) / 8;
@@ -492,7 +495,7 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
             g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
             g.xbytes = (unsigned)xbytes;
             const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
-            g.stream = stream_stores(Y, ldy * ob, ob, 2.0 * A->K * N, (double)ob * A->M * N);
+            g.stream = stream_stores(Y, ldy * ob, ob, 2.0 * A->K * N, (double)ob * A->M * N, reads_of(A));
             return dispatch_out(A, g, (long)N, ydtype, st);
         }
         GeomLinear<true> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};

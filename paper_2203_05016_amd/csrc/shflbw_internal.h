@@ -114,19 +114,26 @@ void note_kernel(const char* name);
 // to shflbw_bind_device, unless an entry point that brings its own device image has set an override.
 const void* device_base(const shflbw_matrix* A);
 void set_device_base_override(const void* base);  // nullptr = none; thread-local
-// Whether a kernel's results leave with streaming stores (pitch: bytes between output rows).  They do not
-// displace the operands in the L2s, but a 64-byte block that two row segments share is then written to
-// memory in parts, which is slower than the displacement for all but large operands.  x_bytes, y_bytes:
-// operands and results of the launch.  us streaming / plain, rows that are not multiples of 64 bytes:
-//   gather, 16 bits: 2048 x 2048 by 4008, V = 64, 90 % 13.8 / 11.5; 4096 x 1024 by 2040 15.5 / 14.3; 1x1 on
-//     30x30 images 8.7 / 7.8; but 4096 x 1024 by 8191 61 / 74, 1024 x 4096 by 8200 40 / 49
-//   gather, 32 bits: 4096 x 1024 by 2040 22.7 / 16.3; 4096 x 1024 by 8191 120 / 102; but 1024 x 4096 by 8200
-//     (67 MB of X) 46 / 55
-// and multiples of 64 bytes: 4096 x 1024 by 2080 17.6 / 18.2, 1x1 on 56x56 images 7.7 / 8.8.
-inline bool stream_stores(const void* y, int64_t pitch, int out_bytes, double x_bytes, double y_bytes)
+// Whether the gather kernel's results leave with streaming stores (pitch: bytes between output rows; x_bytes, y_bytes:
+// operands and results of the launch; reads: kept columns per row of a group, over its rows, which is what is gathered
+// per value that is stored).  They do not displace the operands in the L2s, but a 64-byte block that two row segments
+// share is then written to memory in parts.  With rows of whole blocks: always (4096 x 1024 by 2080 17.6 us streaming,
+// 18.2 plain; 1x1 on 56x56 images 7.7 / 8.8).  Else, 16-bit results, us streaming / plain, K = 1024 where not said:
+//   results of a few MB stay in the L2s: 1024 x 1024 by 2040, V = 64 at 90 % 5.5 / 4.8; 4096 by 1000, V = 32 at 90 %
+//     5.7 / 5.3; but with operands beyond the L2s, 1x1, 512 channels, 28x28, V = 32 at 50 % (8 reads) 7.7 / 8.5
+//   9 to 14 MB: 2048 by 3000, V = 32 at 90 % 8.1 / 8.4, V = 64 at 75 % 9.3 / 10.0, V = 128 at 90 % 8.2 / 8.6, V = 64 at
+//     90 % 7.7 / 7.4; but rows of images, 1x1, 64 -> 256 channels, 28x28, V = 64 at 50 % (0.5) 7.2 / 6.6
+//   more, and images: by what is read.  4096 by 3000, V = 16 at 90 % (6.4 reads) 14.8 / 16.3; 4096 by 8191, V = 32 at 75 % (8) 61 /
+//     74; but 4096 by 2040, V = 64 at 75 % (4) 13.5 / 10.2; 4096 by 6008, V = 32 at 90 % (3.2) 28.1 / 21.4, V = 128 at
+//     90 % (0.8) 26.2 / 21.7; CHWN, 50 images of 30x30, 3x3, 64 -> 256 channels (4.5) 17.0 / 15.0
+// 32-bit results: 4096 by 2040 22.7 / 16.3; 4096 by 8191 120 / 102; but 1024 x 4096 by 8200 (67 MB of X) 46 / 55.
+inline bool stream_stores(const void* y, int64_t pitch, int out_bytes, double x_bytes, double y_bytes, double reads, bool images = false)
 {
     if ((pitch | (int64_t)reinterpret_cast<uintptr_t>(y)) % 64 == 0) return true;
-    return out_bytes == 4 ? x_bytes > 32e6 : x_bytes + y_bytes > 40e6;
+    if (out_bytes == 4) return x_bytes > 32e6;
+    if (y_bytes < 9e6) return x_bytes + y_bytes > 25e6 && reads >= 2;
+    if (y_bytes < 14e6 && !images) return x_bytes + y_bytes > 15e6;
+    return reads >= 6;
 }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 }  // namespace shflbw
