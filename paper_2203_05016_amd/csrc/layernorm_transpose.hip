@@ -61,14 +61,23 @@ struct LnArgs {
 // Streaming where the row segments of 64 (128) bytes are whole 64-byte blocks of memory; plain where
 // two workgroups share a block, so that its parts meet in the L2 (8184 tokens of 1024 features: 16.0 us
 // streaming, 11.0 plain; 20 008 of 1024: 41 and 26; 8192 of 1024: 8.2 and 8.9).
-__device__ __forceinline__ void ln_store(uint16_t* p, ln_ushort8 v, int stream)
+template <bool STREAM>
+__device__ __forceinline__ void ln_store(uint16_t* p, ln_ushort8 v)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<ln_ushort8*>(p));
+    else *reinterpret_cast<ln_ushort8*>(p) = v;
+}
+// f with std::true_type or std::false_type, once for many stores: a choice at each of them keeps the loop around
+// them from being unrolled (32 768 tokens of 256 features, transposed only: 5.9 us against 5.2)
+template <class F>
+__device__ __forceinline__ void ln_with_stores(int stream, F&& f)
 {
     if (stream) {
-        asm volatile("");   // kept apart: merged with the other branch, the store loses its hint
-        __builtin_nontemporal_store(v, reinterpret_cast<ln_ushort8*>(p));
+        asm volatile("");   // kept apart: merged with the other branch, the stores lose their hint
+        f(std::true_type{});
         asm volatile("");
     } else {
-        *reinterpret_cast<ln_ushort8*>(p) = v;
+        f(std::false_type{});
     }
 }
 
@@ -281,15 +290,16 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
 #pragma unroll
     for (int t = 0; t < TPW; ++t) { s1[t] = 0.f; s2[t] = 0.f; pivot[t] = 0.f; }
     const bool all_tokens = n0 + TOK <= a.N;
-    // one sweep of 1024 features; FULL = every token and feature of it exists
-    auto sweep = [&](int kc0, auto full_tag) __attribute__((always_inline)) {
+    // one sweep of HALVES times 512 features; FULL = every token and feature of it exists
+    auto sweep = [&](int kc0, auto full_tag, auto halves_tag) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full_tag)::value;
-        ln_ushort8 v[TPW][2];
+        constexpr int HALVES = decltype(halves_tag)::value;
+        ln_ushort8 v[TPW][HALVES];
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
             const long n = n0 + wave * TPW + t;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < HALVES; ++h) {
                 const int kc = kc0 + h * 512 + lane * 8;
                 // a token or feature that does not exist loads the last one instead (its values are neither
                 // summed, nor kept, nor stored: a conditional load would wait for the one before it)
@@ -307,7 +317,7 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < HALVES; ++h) {
                 const int kc = kc0 + h * 512 + lane * 8;
                 if (FULL || kc < K) {
                     unsigned w[4];
@@ -339,10 +349,14 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
             }
         }
     };
-    for (int kc0 = 0; kc0 < K; kc0 += 2 * 64 * 8) {
-        if (all_tokens && kc0 + 2 * 64 * 8 <= K) sweep(kc0, std::true_type{});
-        else sweep(kc0, std::false_type{});
-    }
+    // 512 features or fewer: the second half would load the last ones over and over (32 768 tokens of 256, transposed
+    // only, 5.9 us without this, 4.5 with it)
+    if (K <= 64 * 8) sweep(0, std::false_type{}, std::integral_constant<int, 1>{});
+    else
+        for (int kc0 = 0; kc0 < K; kc0 += 2 * 64 * 8) {
+            if (all_tokens && kc0 + 2 * 64 * 8 <= K) sweep(kc0, std::true_type{}, std::integral_constant<int, 2>{});
+            else sweep(kc0, std::false_type{}, std::integral_constant<int, 2>{});
+        }
     if (NORM) {
 #pragma unroll
         for (int t = 0; t < TPW; ++t) {
@@ -377,36 +391,39 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_resident_kernel(LnAr
     const unsigned* xw = reinterpret_cast<const unsigned*>(xs) + tchunk * 8 * (P / 2);
     const int Q = P / 2;
     if (n < a.N) {
+        ln_with_stores(a.stream, [&](auto stream_tag) __attribute__((always_inline)) {
+            constexpr bool STREAM = decltype(stream_tag)::value;
 #pragma unroll 2
-        for (int kb = wave * 2 * FP; kb < K; kb += WAVES * 2 * FP) {
-            const int k = kb + 2 * kk2;      // K is even: the pair exists or does not
-            if (k < K) {
-                unsigned w[8];
+            for (int kb = wave * 2 * FP; kb < K; kb += WAVES * 2 * FP) {
+                const int k = kb + 2 * kk2;      // K is even: the pair exists or does not
+                if (k < K) {
+                    unsigned w[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) w[e] = xw[e * Q + (k >> 1)];
-                ln_ushort8 o0, o1;
-                if (NORM) {
-                    const float2 g = *reinterpret_cast<const float2*>(gam + k);
-                    const float2 b = *reinterpret_cast<const float2*>(bet + k);
+                    for (int e = 0; e < 8; ++e) w[e] = xw[e * Q + (k >> 1)];
+                    ln_ushort8 o0, o1;
+                    if (NORM) {
+                        const float2 g = *reinterpret_cast<const float2*>(gam + k);
+                        const float2 b = *reinterpret_cast<const float2*>(bet + k);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        float lo, hi;
-                        ln_add_pair<BF>(w[e], -mean[e], lo, hi);
-                        o0[e] = ln_narrow<BF>(lo * rstd[e] * g.x + b.x);
-                        o1[e] = ln_narrow<BF>(hi * rstd[e] * g.y + b.y);
+                        for (int e = 0; e < 8; ++e) {
+                            float lo, hi;
+                            ln_add_pair<BF>(w[e], -mean[e], lo, hi);
+                            o0[e] = ln_narrow<BF>(lo * rstd[e] * g.x + b.x);
+                            o1[e] = ln_narrow<BF>(hi * rstd[e] * g.y + b.y);
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            o0[e] = (uint16_t)(w[e] & 0xffffu);
+                            o1[e] = (uint16_t)(w[e] >> 16);
+                        }
                     }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        o0[e] = (uint16_t)(w[e] & 0xffffu);
-                        o1[e] = (uint16_t)(w[e] >> 16);
-                    }
+                    uint16_t* dst = a.out + (long)k * a.ldo + n;
+                    ln_store<STREAM>(dst, o0);
+                    ln_store<STREAM>(dst + a.ldo, o1);
                 }
-                uint16_t* dst = a.out + (long)k * a.ldo + n;
-                ln_store(dst, o0, a.stream);
-                ln_store(dst + a.ldo, o1, a.stream);
             }
-        }
+        });
     }
 }
 
@@ -496,7 +513,7 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
     // 1.0 twice in the 16-bit format, for an absent gamma
     const unsigned one2 = BF ? 0x3f803f80u : 0x3c003c00u;
     // the transposed rows k0 .. k0+1023 from LDS buffer `buf`
-    auto store_slice = [&](int k0, int buf) __attribute__((always_inline)) {
+    auto store_slice_as = [&](int k0, int buf, auto stream_tag) __attribute__((always_inline)) {
         const unsigned* xw = reinterpret_cast<const unsigned*>(xs + buf * TOK * P) + tchunk * 8 * Q;
 #pragma unroll
         for (int pass = 0; pass < SL / (WAVES * 2 * FP); ++pass) {
@@ -528,10 +545,13 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
                     }
                 }
                 uint16_t* dst = a.out + (long)k * a.ldo + n;
-                ln_store(dst, o0, a.stream);
-                ln_store(dst + a.ldo, o1, a.stream);
+                ln_store<decltype(stream_tag)::value>(dst, o0);
+                ln_store<decltype(stream_tag)::value>(dst + a.ldo, o1);
             }
         }
+    };
+    auto store_slice = [&](int k0, int buf) __attribute__((always_inline)) {
+        ln_with_stores(a.stream, [&](auto stream_tag) __attribute__((always_inline)) { store_slice_as(k0, buf, stream_tag); });
     };
     // the part held in registers, slice by slice through the LDS, out as transposed rows
     auto emit = [&](int part) __attribute__((always_inline)) {
@@ -742,6 +762,12 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         const int slices = (K + 1023) / 1024;
         int shares = rwgs > 0 && rwgs < 256 ? (int)(256 / rwgs) : 1;
         if (shares > slices) shares = slices;
+        // with a LayerNorm every share reads all slices first: worth it when that at least halves what is left to each
+        // (us one / shared: 4000 tokens of 3000 features, 2 of 3 slices each, 12.4 / 14.2; of 5120, 3 of 5, 24.2 / 24.8;
+        // 4096 of 4096, 2 of 4, 14.9 / 13.4).  Nor by two where a token has more than 8 slices and the output rows are
+        // whole 64-byte blocks (4096 tokens of 16 384 features 69.5 / 71.8, transposed only 45 / 48; of 8192, 33.6 / 34.0
+        // and 24.0 / 22.4)
+        if ((a.normalize && 2 * ((slices + shares - 1) / shares) > slices) || (a.stream && slices > 8 && shares < 3)) shares = 1;
         a.slices_per_wg = (slices + shares - 1) / shares;
         const unsigned ry = (unsigned)((slices + a.slices_per_wg - 1) / a.slices_per_wg);
         const int which = (ry > 1 ? 16 : 0) + (parts - 1) * 4 + (dtype == SHFLBW_BF16 ? 2 : 0) + (a.normalize ? 1 : 0);
