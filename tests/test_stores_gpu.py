@@ -31,7 +31,10 @@ def test_rows_of_every_alignment_exact(kernel, V, N, pad_ld, offset):
 def test_layernorm_transposition_of_every_sharing(N, K, fmt):
     """Against the definition in 64 bits (torch).  The result is rounded once from 32 bits: half a unit in
     the last place (2^-11, 2^-8) of the value, and 2^-14 (2^-12) of |gamma x| + |beta| for the 32-bit
-    statistics and products."""
+    products and deviation.  The mean is the token's first value plus a 32-bit sum of K differences from it, K / 64
+    of them one after the other in each lane and 6 more additions: off by no more than (K / 64 + 8) 2^-24 times the
+    mean difference, which moves every result by that much times |gamma| over the deviation - all that there is
+    where a value lies next to the mean (25 million results of 9216 features meet it)."""
     import torch
     announce("layernorm sharing", N, K, fmt)
     dt = torch.float16 if fmt == "f16" else torch.bfloat16
@@ -42,11 +45,13 @@ def test_layernorm_transposition_of_every_sharing(N, K, fmt):
     xd, gd, bd = x.double(), g.double(), b.double()
     hat = (xd - xd.mean(1, keepdim=True)) / torch.sqrt(xd.var(1, unbiased=False, keepdim=True) + 1e-5)
     want, scale = (hat * gd + bd).t(), (hat.abs() * gd.abs() + bd.abs()).t()
+    mean_off = (K / 64 + 8) * 2.0 ** -24 * (xd - xd[:, :1]).abs().mean(1) / torch.sqrt(xd.var(1, unbiased=False) + 1e-5)
+    from_mean = gd.abs()[:, None] * mean_off[None, :]
     for pitch in (N, (N + 63) // 64 * 64):   # plain or streaming stores
         buf = torch.full((K, pitch), float("nan"), dtype=dt, device="cuda:0")
         out = binding.layernorm_transpose(x, g, b, out=buf[:, :N])
         unit, rest = (2.0 ** -11, 2.0 ** -14) if fmt == "f16" else (2.0 ** -8, 2.0 ** -12)
-        assert bool(((out.double() - want).abs() <= unit * want.abs() + rest * scale + 2.0 ** -24).all())
+        assert bool(((out.double() - want).abs() <= unit * want.abs() + rest * scale + from_mean + 2.0 ** -24).all())
         assert bool(torch.isnan(buf[:, N:]).all())
         binding.layernorm_transpose(x, normalize=False, out=buf[:, :N])
         assert torch.equal(buf[:, :N], x.t())
