@@ -613,10 +613,29 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     {
         const int64_t HW = (int64_t)H * W;
         const int64_t in_total = 2 * (int64_t)batch * C_in * HW;
+        // Images of four positions, us staged / gathered: 64 images, 512 -> 512 channels, V = 32: 10.3 / 6.6
+        // unpruned, 7.3 / 3.7 at 75 %.  Tiles enough for every CU gain nothing from being split, and then
+        // groups that keep many rows are staged: 256 images, 1024 -> 2048, 50 %, V = 32 13.1 / 19.0; 1024 of
+        // 512 -> 512, 50 %, V = 32 9.1 / 11.1; 1024 of 256 -> 1024, V = 64 11.8 / 13.2 unpruned, 10.3 / 9.1 at
+        // 50 %, V = 16 23.8 / 19.0 at 50 %.
+        const bool dense_quads = A->V <= 64 && (N + 63) / 64 * A->G >= 1024 && 2.5 * A->nnz > (double)A->M * A->K &&
+                                 A->nnz >= (int64_t)160 * A->M;
         if (A->tune_kernel == 0 && layout == SHFLBW_NCHW && R == 1 && S == 1 && stride_h == 1 &&
-            stride_w == 1 && pad_h == 0 && pad_w == 0 && HW >= 8 && HW * 2 < (1 << 24) &&
-            C_in < (1 << 24) && in_total < ((int64_t)1 << 32) - 64)
-            return run_rows(A, in, HW, (long)C_in * HW, out, HW, (long)A->M * HW, (int)HW, batch, in_total, ydtype, st);
+            stride_w == 1 && pad_h == 0 && pad_w == 0 && (HW >= 8 || (HW == 4 && !dense_quads)) && HW * 2 < (1 << 24) &&
+            C_in < (1 << 24) && in_total < ((int64_t)1 << 32) - 64) {
+            if (HW >= 8)
+                return run_rows(A, in, HW, (long)C_in * HW, out, HW, (long)A->M * HW, (int)HW, batch, in_total, ydtype, st);
+            GeomQuads g;
+            g.X = static_cast<const _Float16*>(in);
+            g.Y = out;
+            g.ldx = g.ldy = HW;
+            g.N = (long)N;
+            g.xbytes = (unsigned)in_total;
+            g.stream = 0;
+            g.x_image = (unsigned)(2 * (int64_t)C_in * HW);
+            g.y_image = (long)A->M * HW;
+            return dispatch_out(A, g, g.N, ydtype, st);
+        }
     }
     // Convolutions gathered in runs of 8 along the innermost dimension.  Left to the staged kernel (when
     // it is not forced): products whose gathered bytes - every kept row of the unfolded matrix once per

@@ -53,3 +53,49 @@ def test_images_of_any_number_of_slots(batch, H, W):
         A.conv2d(x, 1, 1, out=out)
         torch.cuda.synchronize()
         assert np.array_equal(to_host(out).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("V", [16, 32, 64, 128])
+@pytest.mark.parametrize("batch,C,H,W", [(1, 40, 2, 2), (2, 64, 4, 1), (3, 96, 1, 4), (17, 200, 2, 2), (300, 64, 2, 2)])
+def test_1x1_on_images_of_four_positions(V, batch, C, H, W):
+    """Two images per lane, the second of which may not exist; NaN right before or after the tensor."""
+    import torch
+    announce("choice, four positions", V, batch, C, H, W)
+    p = synth.make_conv(batch, C, H, W, 2 * V, 1, 1, V, 0.5, seed=981 + batch + V, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (1, 1), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    n = p.conv["input"].size
+    flat = torch.full((n + 1,), float("nan"), dtype=torch.float16, device="cuda:0")
+    for base in (0, 1):
+        flat.fill_(float("nan"))
+        x = flat[base:base + n].view(p.conv["input"].shape)
+        x.copy_(to_device(p.conv["input"]))
+        for dt in (torch.float16, torch.float32):
+            buf = torch.full((batch * 2 * V * 4 + 8,), float("nan"), dtype=dt, device="cuda:0")
+            out = buf[4:-4].view(batch, 2 * V, H, W)
+            A.conv2d(x, 1, 1, out=out)
+            torch.cuda.synchronize()
+            assert "shflbw_gather_kernel" in binding.last_kernel()
+            assert np.array_equal(to_host(out).astype(np.float64), want)
+            assert bool(torch.isnan(buf[:4]).all()) and bool(torch.isnan(buf[-4:]).all())
+
+
+@pytest.mark.parametrize("V,batch,C,sparsity,staged", [
+    (32, 512, 192, 0.0, False),      # 256 tiles
+    (16, 2048, 192, 0.0, True),
+    (16, 2048, 192, 0.5, False),
+    (64, 2048, 192, 0.0, True),
+    (128, 2048, 192, 0.0, False),
+])
+def test_1x1_on_many_images_of_four_positions(V, batch, C, sparsity, staged):
+    import torch
+    announce("choice, many images of four", V, batch, sparsity)
+    M = 8 * V
+    p = synth.make_conv(batch, C, 2, 2, M, 1, 1, V, sparsity, seed=983 + V, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (1, 1), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    out = torch.full((batch, M, 2, 2), float("nan"), dtype=torch.float32, device="cuda:0")
+    A.conv2d(to_device(p.conv["input"]), 1, 1, out=out)
+    torch.cuda.synchronize()
+    assert ("shflbw_conv_kernel" in binding.last_kernel()) == staged, binding.last_kernel()
+    assert np.array_equal(to_host(out).astype(np.float64), want)
