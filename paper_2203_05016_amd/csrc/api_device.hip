@@ -639,7 +639,7 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     }
     // Convolutions gathered in runs of 8 along the innermost dimension.  Left to the staged kernel (when
     // it is not forced): products whose gathered bytes - every kept row of the unfolded matrix once per
-    // group - outweigh what its 2-byte LDS reads cost.  Batch-innermost tensors and V >= 64: never in
+    // group - outweigh what its 2-byte LDS reads cost and whose input box fits the LDS.  Batch-innermost tensors and V >= 64: never in
     // what was measured (128 channels, 56x56, 3x3 / 2, V = 32, CHWN: 41.5 us staged, 13.2 gathered; 64 ->
     // 128 channels, 56x56, dense, V = 32, CHWN: 59.9 / 37.0; 64 channels, 28x28, dense, V = 64: 21.6 /
     // 14.1).  NCHW, us staged / gathered by density: V = 32, 256 channels, 14x14: 13.2 / 11.8 at 0.25,
@@ -649,20 +649,21 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     // at 0.25, 24.9 / 28.7 at 0.5.
     const double kept = (double)A->nnz / ((double)A->M * A->K);
     const bool runs_pay = layout == SHFLBW_CHWN || A->V >= 64 || kept <= (A->V == 32 ? 0.55 : Wo < 16 ? 0.22 : 0.6);
-    if (A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) {
-        const int64_t in_total = 2 * (int64_t)batch * C_in * H * W;
-        if (layout == SHFLBW_CHWN) {
-            GeomConvRuns<true> g;
-            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total,
-                               ydtype == SHFLBW_F32 ? 4 : 2))
-                return dispatch_out(A, g, g.N, ydtype, st);
-        } else {
-            GeomConvRuns<false> g;
-            if (fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, in_total,
-                               ydtype == SHFLBW_F32 ? 4 : 2))
-                return dispatch_out(A, g, g.N, ydtype, st);
-        }
-    }
+    const auto gather_runs = [&](auto& g, int* status) {
+        if (!fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo,
+                            2 * (int64_t)batch * C_in * H * W, ydtype == SHFLBW_F32 ? 4 : 2))
+            return false;
+        *status = dispatch_out(A, g, g.N, ydtype, st);
+        return true;
+    };
+    const auto try_runs = [&](int* status) {
+        GeomConvRuns<true> chwn;
+        GeomConvRuns<false> nchw;
+        return layout == SHFLBW_CHWN ? gather_runs(chwn, status) : gather_runs(nchw, status);
+    };
+    int status = SHFLBW_OK;
+    if ((A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) && try_runs(&status))
+        return status;
     if (A->tune_kernel != 1 && A->tune_kernel != 3) {
         // the plan depends on the sizes below only (not on which matrix has them): keep the last one
         struct PlanKey {
@@ -691,6 +692,9 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         if (A->tune_kernel == 2)
             return fail(SHFLBW_ERR_BAD_OPTION,
                         "staged convolution kernel needs an input box that fits the LDS");
+        // beyond the LDS the element-wise geometry is hundreds of times dearer than the runs (8 images of 14x14,
+        // 2048 -> 128 channels, 3x3, unpruned, V = 32: 3400 us / 64)
+        if (!runs_pay && try_runs(&status)) return status;
     }
     GeomConv g;
     g.in = static_cast<const _Float16*>(in);

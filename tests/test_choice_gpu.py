@@ -99,3 +99,19 @@ def test_1x1_on_many_images_of_four_positions(V, batch, C, sparsity, staged):
     torch.cuda.synchronize()
     assert ("shflbw_conv_kernel" in binding.last_kernel()) == staged, binding.last_kernel()
     assert np.array_equal(to_host(out).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("V,side", [(16, 14), (32, 14)])
+def test_input_box_beyond_the_lds_is_gathered_in_runs(V, side):
+    """A density that would be staged, with too many channels for that: not the element-wise geometry."""
+    import torch
+    announce("choice, too many channels to stage", V, side)
+    p = synth.make_conv(2, 2048, side, side, 2 * V, 3, 3, V, 0.0, seed=985 + V, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 3, 3, (1, 1), (1, 1))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    out = torch.full((2, 2 * V, side, side), float("nan"), dtype=torch.float32, device="cuda:0")
+    A.conv2d(to_device(p.conv["input"]), 3, 3, (1, 1), (1, 1), out=out)
+    torch.cuda.synchronize()
+    # few tiles: the runs share their k-steps between wavefronts, the element-wise geometry never does
+    assert "gather" in binding.last_kernel() and "split k-steps by" in binding.last_kernel(), binding.last_kernel()
+    assert np.array_equal(to_host(out).astype(np.float64), want)
