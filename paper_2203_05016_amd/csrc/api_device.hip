@@ -148,6 +148,40 @@ int check_ydtype(const shflbw_matrix* A, shflbw_dtype ydtype)
                     : "ydtype must be SHFLBW_F16 or SHFLBW_F32 for a binary16 matrix");
 }
 
+// Up to which kept share a convolution is gathered in runs of 8 (below) rather than staged, by the length of
+// the innermost dimension (Wo of NCHW results, the batch of CHWN): every kept row of the unfolded matrix is
+// fetched once per group, in whole runs, and staging costs 2-byte LDS reads whatever is kept.  What decides is
+// how full the last run is and how many groups fetch.  us staged / gathered, 3x3, by kept share:
+//   V = 32, 128 -> 128 channels, 16x16 (full runs)        1: 15.9 / 12.8
+//   V = 32, 256 -> 256, 9x9 (one of 8 in the last run)    .5: 16.5 / 17.5   .35: 13.4 / 13.4
+//   V = 32, 256 -> 256, 12x12                             .5: 17.3 / 14.8   .25: 12.2 / 9.3
+//   V = 32, 256 -> 256, 14x14 (six of 8)                  .5: 17.4 / 18.0   .25: 12.3 / 11.0
+//   V = 32, 128 -> 128, 28x28 (4 groups)                  .5: 18.8 / 17.7   1: 28.0 / 30.0
+//   V = 32, 128 -> 256, 28x28 (8 groups)                  .5: 26.1 / 32.8   .15: 17.1 / 14.2
+//   V = 16, 256 -> 256, 9x9                               .25: 11.8 / 15.2   .1: 8.8 / 8.5
+//   V = 16, 256 -> 256, 14x14                             .25: 17.8 / 18.5   .15: 14.5 / 12.7
+//   V = 16, 128 -> 128, 17x17                             .25: 12.7 / 14.0   .15: 10.9 / 9.4
+//   V = 16, 128 -> 128, 28x28 (8 groups)                  1: 47.4 / 56.5   .5: 32.7 / 32.4
+//   V = 16, 128 -> 256, 28x28 (16 groups)                 .5: 51.0 / 61.8   .35: 44.9 / 37.1
+//   CHWN, V = 16, 128 -> 128, 28x28, batch 9              .5: 17.5 / 19.4   .35: 15.8 / 15.3
+//   CHWN, V = 16, 128 -> 128, 28x28, batch 10             1: 26.8 / 16.6
+//   CHWN, V = 32, 256 -> 256, 14x14, batch 25             .5: 19.9 / 20.9   .35: 16.9 / 16.0
+// V >= 64 fetches rows for so many results that gathering won everywhere but at 9x9 unpruned (4 %).
+double runs_limit(int V, int groups, bool chwn, int innermost)
+{
+    const int last = innermost % 8;
+    if (V >= 64) return 1;
+    if (chwn) return last != 1 ? 1 : V == 16 && innermost > 16 ? 0.6 : 0.45;
+    if (last == 0) return V == 32 ? 1 : 0.85;
+    if (V == 32) {
+        if (last == 1) return 0.4;
+        if (groups <= 4) return 0.65;
+        return innermost > 16 ? 0.22 : last <= 4 ? 0.65 : 0.45;
+    }
+    if (innermost < 16) return last <= 2 ? 0.12 : 0.22;
+    return last == 1 && innermost < 24 ? 0.22 : innermost >= 24 && groups <= 8 ? 0.6 : 0.4;
+}
+
 // The convolution as gathers of runs of 8 (GeomConvRuns).  False when the tensor has no such
 // runs or is beyond the kernel's 24-bit and 32-bit offset arithmetic.
 template <bool CHWN>
@@ -637,18 +671,10 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
             return dispatch_out(A, g, g.N, ydtype, st);
         }
     }
-    // Convolutions gathered in runs of 8 along the innermost dimension.  Left to the staged kernel (when
-    // it is not forced): products whose gathered bytes - every kept row of the unfolded matrix once per
-    // group - outweigh what its 2-byte LDS reads cost and whose input box fits the LDS.  Batch-innermost tensors and V >= 64: never in
-    // what was measured (128 channels, 56x56, 3x3 / 2, V = 32, CHWN: 41.5 us staged, 13.2 gathered; 64 ->
-    // 128 channels, 56x56, dense, V = 32, CHWN: 59.9 / 37.0; 64 channels, 28x28, dense, V = 64: 21.6 /
-    // 14.1).  NCHW, us staged / gathered by density: V = 32, 256 channels, 14x14: 13.2 / 11.8 at 0.25,
-    // 18.9 / 18.8 at 0.5, 29.7 / 32.7 at 1; V = 32, 128 channels, 28x28: 15.7 / 12.5, 22.9 / 23.5 at 0.7,
-    // 28.2 / 30.8; V = 16, 128 channels, 28x28: 26.3 / 19.3 at 0.25, 47.3 / 55.2 at 1; V = 16 on images
-    // whose rows fill their slots badly (14 of 16 columns, 256 channels): 13.0 / 10.3 at 0.1, 17.8 / 18.7
-    // at 0.25, 24.9 / 28.7 at 0.5.
+    // Convolutions gathered in runs of 8 along the innermost dimension: forced, chosen by runs_limit, or
+    // the choice left when the staged kernel's input box does not fit the LDS.
     const double kept = (double)A->nnz / ((double)A->M * A->K);
-    const bool runs_pay = layout == SHFLBW_CHWN || A->V >= 64 || kept <= (A->V == 32 ? 0.55 : Wo < 16 ? 0.22 : 0.6);
+    const bool runs_pay = kept <= runs_limit(A->V, A->G, layout == SHFLBW_CHWN, layout == SHFLBW_CHWN ? batch : Wo);
     const auto gather_runs = [&](auto& g, int* status) {
         if (!fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo,
                             2 * (int64_t)batch * C_in * H * W, ydtype == SHFLBW_F32 ? 4 : 2))

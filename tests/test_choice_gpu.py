@@ -115,3 +115,40 @@ def test_input_box_beyond_the_lds_is_gathered_in_runs(V, side):
     # few tiles: the runs share their k-steps between wavefronts, the element-wise geometry never does
     assert "gather" in binding.last_kernel() and "split k-steps by" in binding.last_kernel(), binding.last_kernel()
     assert np.array_equal(to_host(out).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("layout,V,batch,C,side,C_out,sparsity,staged", [
+    ("NCHW", 32, 8, 64, 16, 64, 0.0, False),      # full runs
+    ("NCHW", 32, 8, 64, 9, 64, 0.5, True),        # one element in the last run
+    ("NCHW", 32, 8, 64, 9, 64, 0.75, False),
+    ("NCHW", 32, 8, 64, 28, 64, 0.5, False),      # few groups
+    ("NCHW", 32, 8, 64, 28, 256, 0.5, True),      # eight groups fetch every kept row
+    ("NCHW", 32, 8, 64, 14, 256, 0.5, True),
+    ("NCHW", 32, 8, 64, 12, 256, 0.5, False),
+    ("NCHW", 16, 8, 64, 9, 64, 0.8, True),
+    ("NCHW", 16, 8, 64, 14, 64, 0.8, False),
+    ("NCHW", 16, 8, 64, 17, 64, 0.7, True),
+    ("NCHW", 16, 8, 64, 20, 64, 0.65, False),
+    ("NCHW", 16, 8, 32, 28, 64, 0.5, False),
+    ("NCHW", 16, 8, 32, 28, 256, 0.5, True),
+    ("NCHW", 64, 8, 64, 9, 64, 0.0, False),
+    ("CHWN", 16, 9, 64, 6, 64, 0.5, True),        # one image in the last run
+    ("CHWN", 16, 17, 64, 6, 64, 0.5, False),
+    ("CHWN", 32, 17, 64, 6, 64, 0.5, True),
+    ("CHWN", 32, 10, 64, 6, 64, 0.0, False),
+])
+def test_convolutions_are_staged_where_runs_are_badly_filled(layout, V, batch, C, side, C_out, sparsity, staged):
+    import torch
+    announce("choice, runs", layout, V, batch, side, C_out, sparsity)
+    p = synth.make_conv(batch, C, side, side, C_out, 3, 3, V, sparsity, seed=987 + V + side, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 3, 3, (1, 1), (1, 1))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    x = to_device(p.conv["input"])
+    if layout == "CHWN":
+        x = x.permute(1, 2, 3, 0).contiguous()
+    got = A.conv2d(x, 3, 3, (1, 1), (1, 1), layout=layout, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert ("shflbw_conv_kernel" in binding.last_kernel()) == staged, binding.last_kernel()
+    if layout == "CHWN":
+        got = got.permute(3, 0, 1, 2)
+    assert np.array_equal(to_host(got.contiguous()).astype(np.float64), want)
