@@ -19,6 +19,10 @@ pytestmark = pytest.mark.gpu
     (32, 64, 512, 64 * 704, 0.5, 2),        # 1408 tiles of 16
     (32, 64, 1024, 64 * 896 + 8, 0.5, 2),   # 1794 tiles of 32
     (64, 128, 1024, 64 * 896, 0.5, 1),      # 1792 tiles of 32, V = 64
+    (16, 64, 512, 64 + 8, 0.9, 2),          # 8 tiles of 2
+    (32, 64, 256, 64 + 8, 0.5, 4),          # 4 tiles of 4
+    (16, 64, 512, 64 * 160, 0.9, 1),        # 640 tiles of 2, V = 16
+    (32, 64, 512, 64 * 320, 0.9, 2),        # 640 tiles of 2
 ])
 def test_k_steps_are_shared_where_that_pays(V, M, K, N, sparsity, shares):
     import torch
