@@ -73,7 +73,8 @@ def test_automatic_choice_is_within_a_fifth_of_the_best_forced_kernel(shape):
     auto, auto_name = _time(A, Xs, Ys, 0)
     best_name = min(forced, key=forced.get)
     print("auto %s %.1f us; forced: %s" % (auto_name, auto, ", ".join("%s %.1f" % kv for kv in forced.items())), flush=True)
-    assert auto <= 1.2 * forced[best_name], "automatic choice %s takes %.1f us, %s takes %.1f us" % (
+    # the same kernel timed twice says nothing about the choice
+    assert auto_name == best_name or auto <= 1.2 * forced[best_name], "automatic choice %s takes %.1f us, %s takes %.1f us" % (
         auto_name, auto, best_name, forced[best_name])
     A.device_status()
     del A, Xs, Ys
