@@ -527,7 +527,7 @@ def main():
             r1 = measure_spmm(q, args.steps, args.warmup, cold=True, kernel=1)
             extra["skinny_%dx%dx%d_s%.2f" % (M, K, N, sp)] = dict(r, whole_tile_gather_ms=r1["ms"])
         extra["conv_shapes_batch32_V32_s0.75"] = measure_conv_shapes(50, 5)
-        # config 4's tensor with the other group sizes (all through the staged kernel), and V = 128
+        # config 4's tensor with the other group sizes (V = 16 through the staged kernel, the others gathered in runs), and V = 128
         # on a large layer through the shared-slab kernel
         for V in (16, 64, 128):
             r = measure_conv(synth.config(3, V=V), args.steps, args.warmup)

@@ -225,7 +225,7 @@ int shflbw_spmm_unbound(const shflbw_matrix* A, const void* X, int64_t ldx, void
  * NCHW products, a kernel whose workgroups copy the part of the input their
  * output positions can touch into LDS once and gather from there.
  * A 1x1 convolution with unit stride and no padding is the linear-layer
- * product itself (CHWN: one matrix; NCHW with H*W of 8 or more: one per
+ * product itself (CHWN: one matrix; NCHW with H*W of 4, 8 or more: one per
  * image, all in one launch) and runs as shflbw_spmm does.
  */
 int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out,

@@ -757,7 +757,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         // Few tokens: the slices of a token block are shared by several workgroups, each of which takes the
         // statistics for itself (its reads of the other slices come from the L2), as long as there is at
         // most one workgroup per CU.  One workgroup per 32 tokens leaves most CUs idle: 848 tokens of 5800
-        // features 23.2 -> 17.4 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
+        // features 22.5 -> 16.1 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
         // 15.0 -> 10.1, 64 of 16 384 51 -> 17.
         const int slices = (K + 1023) / 1024;
         int shares = rwgs > 0 && rwgs < 256 ? (int)(256 / rwgs) : 1;
