@@ -1,25 +1,29 @@
 // Per-wavefront gather kernel for the Shfl-BW product on gfx950 (CDNA4).
 //
-// One wavefront owns one row group (V stored rows) x WN output columns and
-// runs Algorithm 1's loop on its own, with no workgroup barrier:
-//   BulkLoadMeta  - the column indices of a k-step are fetched 2*PD steps
-//                   ahead of their use, one 16-byte load per lane;
-//   StitchTile    - the TK activation rows named by those indices are loaded
-//                   (16 bytes per lane, coalesced along N) PD steps ahead into
-//                   registers, then written to the wavefront's private LDS
-//                   tile; the weight tile is one 16-byte load per lane from
-//                   the packed array, already in operand order;
-//   WarpMMA       - the activation tile is read back transposed
-//                   (ds_read_b64_tr_b16) as the first matrix-core operand and
-//                   multiplied with the weight operand, fp32 accumulation;
-//   ReorderedWriteBack - accumulators go through LDS so that every stored
-//                   row leaves as full 16-byte-per-lane row segments, to the
-//                   row named by row_indices.
+// One wavefront owns one row group (V stored rows) x WN output columns and runs Algorithm 1's loop on its own
+// (sharing weights with its workgroup's other wavefronts, or steps, where that pays: SHARES below):
+//   BulkLoadMeta  - the column indices are fetched 64 at a time, one to two batches ahead, and become a list of
+//                   row offsets in the LDS, private to the wavefront;
+//   StitchTile    - the TK activation rows of a k-step are loaded (16 bytes per lane, coalesced along N) two steps
+//                   ahead into registers and turned into matrix-core operands there: pairs of rows, then trades
+//                   between the lanes that hold the other rows of the operand;
+//   WarpMMA       - the operands are multiplied with the weight operand (16 bytes per lane from the packed array,
+//                   already in operand order, straight from memory or by way of the LDS), fp32 accumulation;
+//   ReorderedWriteBack - accumulators go through LDS so that every stored row leaves as full 16-byte-per-lane
+//                   row segments, to the row named by row_indices.
 //
-// The product is computed as (X^T tile) x (W^T tile), i.e. the instruction's
-// row dimension runs over output columns n and its column dimension over the
-// group's rows: each lane then holds 4 consecutive n of one row, which packs
-// into one 8-byte LDS write in the epilogue.
+// The product is computed as (X^T tile) x (W^T tile), i.e. the instruction's row dimension runs over output
+// columns n and its column dimension over the group's rows: a lane's accumulators are columns of one row, and which
+// columns is free (operands(), quad_col()): four neighbouring ones make one LDS write in the epilogue.
+//
+// What bounds it: a load of 16 bytes per lane takes the address unit 16 cycles where every four lanes stay inside a 64-byte
+// block and about 32 where they do not (130 and 60 GB/s per CU, whatever the length of a row segment; 8 bytes per lane cost
+// as much as 16), so a step of 64 columns costs a CU 32 cycles for X and 16 per row block for weights that are
+// not shared, beside 8 matrix-core cycles per row block; and below 10 us the chain launch -> column indices -> rows ->
+// products -> partial sums -> stores (1.2 us between launches, 0.9 to the first indices, 0.4 to the first rows, 0.5 to 1
+// at the end).  Passing the rows through the LDS for the transposition, as this kernel did before, cost 36 LDS cycles per step
+// and 64 columns and a write-read latency per step: 8192 x 8192 by 16384, V = 64 at 75 %, 713 -> 593 us with the weights
+// shared; 4096 x 1024 by 2047 18.4 -> 16.4; 1024 x 1024 by 4096 7.15 -> 7.05.
 //
 // Operand and accumulator lane maps (checked on hardware):
 //   v_mfma_f32_32x32x16_f16  A: lane l = row l%32, k = 8*(l/32)+e
@@ -27,7 +31,7 @@
 //                            D: lane l, reg r = row 8*(r/4)+4*(l/32)+r%4, col l%32
 //   v_mfma_f32_16x16x32_f16  A: lane l = row l%16, k = 8*(l/16)+e; B alike;
 //                            D: lane l, reg r = row 4*(l/16)+r, col l%16
-//   ds_read_b64_tr_b16: inside each block of 16 lanes, result element e of
+//   ds_read_b64_tr_b16 (the slab kernel's): inside each block of 16 lanes, result element e of
 //     lane i is element i%4 of the 8 bytes addressed by lane 4*e + i/4; with
 //     lanes 4q..4q+3 pointing at 16 consecutive n of row k_q, lane i ends up
 //     with column n_i of rows k_0..k_3.
@@ -83,6 +87,13 @@ __device__ __forceinline__ floatx4 mma16(half8 a, half8 b, floatx4 c)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   \
     } while (0)
 
+// 8 consecutive 16-bit values in registers, two to a register
+typedef unsigned run_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ run_t load_run(__amdgpu_buffer_rsrc_t d, unsigned off)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(d, (int)off, 0, 0);
+}
+
 struct PackedView {
     const int32_t* row_indices;
     const int32_t* step_ptr;
@@ -95,7 +106,9 @@ struct PackedView {
 // A geometry answers two questions: which 8 activation values sit at
 // (reduction index k, output columns n..n+7), and where do output values
 // (original row, columns n..n+cnt-1) go, with streaming stores or plain ones
-// where it has the choice (CHOICE).
+// where it has the choice (CHOICE).  init(n) fixes the lane's columns; a reduction index comes as an
+// entry of the wavefront's list, which entry() makes of the column index; FINISH: finish8() turns
+// what load8() returned into the values.
 
 // Linear layer: X[K][N] and Y[M][N] row-major.  ALIGNED: N, ldx, ldy are
 // multiples of 8 and both bases are 16-byte aligned.
@@ -104,22 +117,25 @@ struct GeomLinear {
     const _Float16* X;
     void* Y;
     long ldx, ldy, N;
+    long n0;                                // the lane's first column
+    static constexpr bool FINISH = false, CONV = false, CHOICE = false;
+    typedef int entry_t;
 
-    __device__ __forceinline__ void init(long) {}
-
-    __device__ __forceinline__ half8 load8(int col, long n) const
+    __device__ __forceinline__ void init(long n) { n0 = n; }
+    __device__ __forceinline__ entry_t entry(int col, bool exists) const { return exists ? col : -1; }
+    __device__ __forceinline__ run_t load8(entry_t col, int&) const
     {
-        half8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (col < 0) return v;
-        const _Float16* p = X + (long)col * ldx + n;
+        half8 v = {};
+        if (col < 0) return __builtin_bit_cast(run_t, v);
+        const _Float16* p = X + (long)col * ldx + n0;
         if (ALIGNED) {
-            if (n < N) v = *reinterpret_cast<const half8*>(p);
+            if (n0 < N) v = *reinterpret_cast<const half8*>(p);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                if (n + e < N) v[e] = p[e];
+                if (n0 + e < N) v[e] = p[e];
         }
-        return v;
+        return __builtin_bit_cast(run_t, v);
     }
 
     template <bool STREAM, int CNT, typename OutT>
@@ -174,8 +190,8 @@ struct GeomLinearBuf {
     unsigned ldx2, ln2;
     // beyond every descriptor the host admits, and 16 bytes from there do not wrap
     static constexpr unsigned PAST_END = 0xffffffe0u;
-    static constexpr bool FINISH = false;   // load8 returns the values as they are used
-    static constexpr bool LIST = false;     // load8 takes column indices as they are stored
+    static constexpr bool FINISH = false;   // load returns the values as they are used
+    static constexpr bool CONV = false;     // the list's entries take divisions
     static constexpr bool CHOICE = true;    // of streaming and plain stores
 
     __device__ __forceinline__ void init(long n)
@@ -185,14 +201,16 @@ struct GeomLinearBuf {
         ln2 = n < N ? (unsigned)n * 2u : PAST_END;
     }
 
-    // zero (the same for the whole wavefront): read zeros whatever the column, at the price of
-    // scalar instructions only
-    __device__ __forceinline__ half8 load8(int col, bool zero, int&) const
+    // row of X as the kernel's list holds it: its byte offset, past the end for one that does not exist
+    typedef unsigned entry_t;
+    __device__ __forceinline__ entry_t entry(int col, bool exists) const
     {
-        // a lane beyond N keeps its offset past the end whatever the column
-        unsigned off = __umul24((unsigned)col, ldx2) + ln2;
-        off = (col < 0 || ln2 == PAST_END || zero) ? PAST_END : off;
-        return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(xd, (int)off, 0, 0));
+        return exists && col >= 0 ? __umul24((unsigned)col, ldx2) : PAST_END;
+    }
+    // a row or a lane past the end stays there: the sum saturates
+    __device__ __forceinline__ run_t load8(entry_t e, int&) const
+    {
+        return load_run(xd, __builtin_elementwise_min(__builtin_elementwise_add_sat(e, ln2), PAST_END));
     }
 
     template <bool STREAM, int CNT, typename OutT>
@@ -271,18 +289,15 @@ struct GeomQuads : GeomLinearBuf {
     __device__ __forceinline__ void init(long n)
     {
         xd = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16*>(X), 0, (int)xbytes, GATHER_BUFFER_FLAGS);
+        ldx2 = 8;
         ln2 = n < N ? (unsigned)((unsigned long)n >> 2) * x_image : PAST_END;
         ln2b = n + 4 < N ? (unsigned)((unsigned long)n >> 2) * x_image + x_image : PAST_END;
     }
-    __device__ __forceinline__ half8 load8(int col, bool zero, int&) const
+    __device__ __forceinline__ run_t load8(entry_t e, int&) const
     {
-        typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-        typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-        const unsigned o = (unsigned)col * 8u;
-        const bool none = col < 0 || zero;
-        const uint2v lo = __builtin_amdgcn_raw_buffer_load_b64(xd, (int)(none || ln2 == PAST_END ? PAST_END : ln2 + o), 0, 0);
-        const uint2v hi = __builtin_amdgcn_raw_buffer_load_b64(xd, (int)(none || ln2b == PAST_END ? PAST_END : ln2b + o), 0, 0);
-        return __builtin_bit_cast(half8, uint4v{lo[0], lo[1], hi[0], hi[1]});
+        const auto lo = __builtin_amdgcn_raw_buffer_load_b64(xd, (int)__builtin_elementwise_min(__builtin_elementwise_add_sat(e, ln2), PAST_END), 0, 0);
+        const auto hi = __builtin_amdgcn_raw_buffer_load_b64(xd, (int)__builtin_elementwise_min(__builtin_elementwise_add_sat(e, ln2b), PAST_END), 0, 0);
+        return run_t{lo[0], lo[1], hi[0], hi[1]};
     }
     template <bool STREAM, int CNT, typename OutT>
     __device__ __forceinline__ void store(int row, long n, const OutT* vals) const
@@ -297,32 +312,29 @@ struct GeomQuads : GeomLinearBuf {
 // Rows of fewer than 8 columns (one token, a few tokens).  The one lane of eight that has columns
 // loads 16 bytes from the row's start, whatever follows the row (columns beyond N are neither stored
 // nor mixed with others); where that would reach past the end of X it loads the last 16 bytes and
-// moves the values down (finish8).  X must hold 8 values or more.  4096 x 4096 by 4096 x 1 (V = 32,
-// 75 %): 38.3 us with element-wise loads, 6.3 us.
+// moves the values down (finish8).  X must hold 8 values or more.  4096 x 4096 by 4096 x 1 (V = 32, 75 %): 38.3 us with element-wise loads, 6.3 us.
 struct GeomNarrow : GeomLinearBuf {
     static constexpr bool FINISH = true, CHOICE = false;
-    __device__ __forceinline__ half8 load8(int col, bool zero, int& shift) const
+    __device__ __forceinline__ run_t load8(entry_t e, int& shift) const
     {
-        unsigned off = __umul24((unsigned)col, ldx2) + ln2;
-        const unsigned lim = xbytes - 16u;
+        const unsigned off = __builtin_elementwise_add_sat(e, ln2), lim = xbytes - 16u;
         const unsigned at = off < lim ? off : lim;
         shift = (int)(off - at) >> 1;
-        off = (col < 0 || ln2 == PAST_END || zero) ? PAST_END : at;
-        return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(xd, (int)off, 0, 0));
+        return load_run(xd, e == PAST_END || ln2 == PAST_END ? PAST_END : at);
     }
     // values shift .. 7 of v moved to 0 (shift 0 .. 7; only columns that exist are looked at afterwards)
-    static __device__ __forceinline__ half8 finish8(half8 v, int shift)
+    static __device__ __forceinline__ run_t finish8(run_t x, int shift)
     {
-        typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-        uint4v x = __builtin_bit_cast(uint4v, v);
         if (shift & 4) { x[0] = x[2]; x[1] = x[3]; }
-        if (shift & 2) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
+        if (shift & 2) {
+#pragma unroll
+            for (int i = 0; i + 1 < 4; ++i) x[i] = x[i + 1];
+        }
         const unsigned bits = (shift & 1) * 16;
-        x[0] = __builtin_amdgcn_alignbit(x[1], x[0], bits);
-        x[1] = __builtin_amdgcn_alignbit(x[2], x[1], bits);
-        x[2] = __builtin_amdgcn_alignbit(x[3], x[2], bits);
+#pragma unroll
+        for (int i = 0; i + 1 < 4; ++i) x[i] = __builtin_amdgcn_alignbit(x[i + 1], x[i], bits);
         x[3] >>= bits;
-        return __builtin_bit_cast(half8, x);
+        return x;
     }
     template <bool STREAM, int CNT, typename OutT>
     __device__ __forceinline__ void store(int row, long n, const OutT* vals) const
@@ -358,7 +370,7 @@ struct GeomConvRuns : GeomLinearBuf {
     unsigned ist;             // input bytes between images (NCHW)
     long osM, osB;            // output elements between channels, and between images (NCHW)
     int iy0, ix0;             // this lane's window origin
-    static constexpr bool FINISH = !CHWN, LIST = true;
+    static constexpr bool FINISH = !CHWN, CONV = true;
     static constexpr unsigned NO_ROW = 0x7fff0000u;   // padded images have fewer than 32768 rows
 
     // slot of virtual column n: image (the first of 8 for CHWN), output row and column (the first of 8 for NCHW)
@@ -406,7 +418,7 @@ struct GeomConvRuns : GeomLinearBuf {
         return entry_t{off, exists && col >= 0 ? (r << 16) | s : NO_ROW};
     }
     // shift: by how many columns the run lies right of the one asked for (-1, 0 or 1; NCHW only)
-    __device__ __forceinline__ half8 load8(entry_t e, int& shift) const
+    __device__ __forceinline__ run_t load8(entry_t e, int& shift) const
     {
         const int iy = iy0 + (int)(e[1] >> 16);
         const int ix = ix0 + (int)(e[1] & 0xffffu);
@@ -420,21 +432,18 @@ struct GeomConvRuns : GeomLinearBuf {
             shift = ic - ix;
             off += (unsigned)ic * 2u;
         }
-        off = ok ? off : PAST_END;
-        return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(xd, (int)off, 0, 0));
+        return load_run(xd, ok ? off : PAST_END);
     }
     // the run that was asked for, from the one loaded `shift` columns over
-    static __device__ __forceinline__ half8 finish8(half8 v, int shift)
+    static __device__ __forceinline__ run_t finish8(run_t x, int shift)
     {
-        typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-        const uint4v x = __builtin_bit_cast(uint4v, v);
         const unsigned up = shift > 0 ? 0x05040302u : 0x07060504u, down = shift < 0 ? 0x05040302u : 0x03020100u;
-        uint4v y, z;
+        run_t y, z;
 #pragma unroll
         for (int i = 0; i < 4; ++i) y[i] = __builtin_amdgcn_perm(x[i], i ? x[i - 1] : 0u, up);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[i] = __builtin_amdgcn_perm(i < 3 ? y[i + 1] : 0u, y[i], down);
-        return __builtin_bit_cast(half8, z);
+        for (int i = 0; i < 4; ++i) z[i] = __builtin_amdgcn_perm(i + 1 < 4 ? y[i + 1] : 0u, y[i], down);
+        return z;
     }
     template <bool STREAM, int CNT, typename OutT>
     __device__ __forceinline__ void store(int row, long n, const OutT* vals) const
@@ -463,6 +472,9 @@ struct GeomConv {
     int base[8];
     int yx[8];
     int live;
+    static constexpr bool FINISH = false, CONV = false, CHOICE = false;
+    typedef int entry_t;
+    __device__ __forceinline__ entry_t entry(int col, bool exists) const { return exists ? col : -1; }
 
     __device__ __forceinline__ void split_n(long n, int& b, int& y, int& x) const
     {
@@ -495,10 +507,10 @@ struct GeomConv {
         }
     }
 
-    __device__ __forceinline__ half8 load8(int col, long) const
+    __device__ __forceinline__ run_t load8(entry_t col, int&) const
     {
-        half8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (col < 0) return v;
+        half8 v = {};
+        if (col < 0) return __builtin_bit_cast(run_t, v);
         const int c = col / (R * S);
         const int rs = col - c * (R * S);
         const int r = rs / S, s = rs - r * S;
@@ -509,7 +521,7 @@ struct GeomConv {
             const bool ok = ((live >> e) & 1) && iy >= 0 && iy < H && ix >= 0 && ix < W;
             if (ok) v[e] = in[(long)base[e] + koff];
         }
-        return v;
+        return __builtin_bit_cast(run_t, v);
     }
 
     template <bool STREAM, int CNT, typename OutT>
@@ -536,14 +548,10 @@ struct GatherShape {
     static constexpr int RB = SMALL ? 1 : V / 32;     // row blocks per group
     static constexpr int TILE_N = SMALL ? 16 : 32;    // output columns per instruction
     static constexpr int NT = WN / TILE_N;
-    static constexpr int LPR = WN / 8;                // lanes per activation row (16 B each)
-    static constexpr int RPI = 64 / LPR;              // rows per load instruction
-    static constexpr int NLD = TK / RPI;              // loads per lane per k-step
-    static constexpr int PITCH = WN + 8;              // LDS row pitch in binary16
-    static constexpr int STAGE = TK * PITCH;          // binary16 per staged tile
+    static constexpr int LPR = WN / 8;                // lanes per activation row, 8 columns (16 B) each
+    static constexpr int NLD = TK * LPR / 64;         // activation rows, and loads, of a lane per k-step
     static constexpr int ROWS_E = SMALL ? 16 : 32;    // rows per epilogue pass
-    static constexpr int EPI = ROWS_E * PITCH;        // binary16 needed by one epilogue pass
-    static constexpr int REGION = (2 * STAGE > EPI) ? 2 * STAGE : EPI;
+    static constexpr int EPI = ROWS_E * (WN + 8);     // binary16 needed by one epilogue pass
 };
 
 // Which workgroup takes which block of column tiles and which group.  Workgroups are dealt to the eight
@@ -556,33 +564,36 @@ struct GatherOrder {
     int uniform_steps;           // k-steps of every group when they all have the same number, else -1
 };
 
-template <class Geom>
-constexpr bool uses_list()
-{
-    if constexpr (std::is_base_of<GeomLinearBuf, Geom>::value) return Geom::LIST;
-    else return false;
-}
-
 // f with std::true_type or std::false_type: streaming stores or not.  One choice for all the stores of a
 // pass: taken at every store, it keeps the reads of the finished tile from running ahead of the stores (1x1 on
 // 28x28 images, 64 -> 256 channels, V = 64 7.05 -> 6.78 us; 1024 x 1024 by 5632 at 90 %, V = 64 5.70 -> 5.47).
 template <class Geom, class F>
 __device__ __forceinline__ void with_stores(const Geom& geom, F&& f)
 {
-    if constexpr (std::is_base_of<GeomLinearBuf, Geom>::value) {
-        if constexpr (Geom::CHOICE) {
-            if (geom.stream) {
-                asm volatile("");   // kept apart: merged with the other branch, the stores lose their hint
-                f(std::true_type{});
-                asm volatile("");
-                return;
-            }
+    if constexpr (Geom::CHOICE) {
+        if (geom.stream) {
+            asm volatile("");   // kept apart: merged with the other branch, the stores lose their hint
+            f(std::true_type{});
+            asm volatile("");
+            return;
         }
     }
     f(std::false_type{});
 }
 
-// Wavefronts a SIMD must be able to hold.  Left alone, the compiler counts on one workgroup per CU: with four
+// k-steps whose weights the wavefronts of a workgroup bring into the LDS at a time
+template <int V, int WAVES>
+constexpr int gather_chunk() { return V == 128 || (V == 64 && WAVES == 4) ? 4 : 8; }
+
+// k-steps whose rows (and weights, unless shared) are on their way while a step multiplies
+template <int V, int WN>
+constexpr int gather_ahead() { return 2; }
+
+// k-steps of one pass through the loop where the weights are not shared
+template <int V, int WN>
+constexpr int gather_batch() { return V == 32 && WN == 128 ? 4 : 2; }
+
+// Wavefronts a SIMD must be able to hold (SPLIT: SHARES of the kernel).  Left alone, the compiler counts on one workgroup per CU: with four
 // wavefronts or fewer in it, a SIMD to each, it keeps the accumulators in registers of their own (V = 128: 328
 // registers, one wavefront per SIMD).  Two are asked for, and four (128 registers) for V = 64, which takes
 // up to 132 otherwise, two workgroups of eight becoming one (not for the split by 8, of which there is no more
@@ -592,32 +603,37 @@ __device__ __forceinline__ void with_stores(const Geom& geom, F&& f)
 template <int V, int WN, class Geom, int SPLIT>
 constexpr int gather_min_waves()
 {
-    return V == 64 && WN == 64 && SPLIT < 8 && !std::is_same<Geom, GeomConv>::value ? 4 : 2;
+    return V == 64 && WN == 64 && SPLIT > 0 && SPLIT < 8 && !std::is_same<Geom, GeomConv>::value ? 4 : 2;
 }
 
-// SPLIT = 1: the wavefronts of a workgroup own different column tiles of one group.
-// SPLIT > 1 (too few tiles to fill the chip): SPLIT neighbouring wavefronts share one tile, each
+// SHARES = 1: the wavefronts of a workgroup own different column tiles of one group.
+// SHARES = 0: the same, and they take the weights, which are the same for all, from the LDS, where each brings a part
+// of them a chunk of k-steps ahead, with a barrier per chunk.
+// SHARES > 1 (SPLIT; too few tiles to fill the chip): SHARES neighbouring wavefronts share one tile, each
 // takes a contiguous share of the group's k-steps; the partial accumulators of a row block meet in
 // the LDS, every wavefront of the tile adds up its share of them and stores its share of the rows.
-template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SPLIT>
-__global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, Geom, SPLIT>()))
+template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SHARES>
+__global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, Geom, SHARES>()))
 void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
 {
     using S = GatherShape<V, WN>;
     constexpr int TK = S::TK, RB = S::RB, NT = S::NT, LPR = S::LPR, NLD = S::NLD;
-    constexpr int PITCH = S::PITCH;
-    constexpr bool BUF = std::is_base_of<GeomLinearBuf, Geom>::value;
-    constexpr bool LIST = uses_list<Geom>();
+    constexpr bool SHARE = SHARES == 0;
+    constexpr int SPLIT = SHARE ? 1 : SHARES;
     constexpr int TILES = WAVES / SPLIT;                             // column tiles of a workgroup
     static_assert(TILES * SPLIT == WAVES, "whole tiles per workgroup");
     constexpr int QUADS = S::SMALL ? NT : NT * 4;                    // groups of 4 accumulators per lane and row block
     constexpr int EPS = WN + 16 / (int)sizeof(OutT);                 // row pitch of a finished tile (SPLIT > 1), in OutT units
-    constexpr int RED_BYTES = SPLIT > 1 ? WAVES * QUADS * 1024 : 0;
-    constexpr int FIN_BYTES = SPLIT > 1 ? TILES * S::ROWS_E * EPS * (int)sizeof(OutT) : 0;
-    constexpr int TILE_BYTES = WAVES * S::REGION * 2 > RED_BYTES ? (WAVES * S::REGION * 2 > FIN_BYTES ? WAVES * S::REGION * 2 : FIN_BYTES)
-                                                                  : (RED_BYTES > FIN_BYTES ? RED_BYTES : FIN_BYTES);
-    constexpr int LIST_BYTES = LIST ? WAVES * 2 * 64 * 8 : 0;        // two batches of 64 entries per wavefront
-    __shared__ __attribute__((aligned(16))) _Float16 smem[(TILE_BYTES + LIST_BYTES) / 2];
+    constexpr int RED_BYTES = WAVES * QUADS * 1024;
+    constexpr int FIN_BYTES = TILES * S::ROWS_E * EPS * (int)sizeof(OutT);
+    constexpr int TILE_BYTES = SPLIT == 1 ? WAVES * S::EPI * 2 : RED_BYTES + FIN_BYTES;
+    typedef typename Geom::entry_t entry_t;
+    constexpr int LIST_BYTES = (int)sizeof(entry_t) * WAVES * 2 * 64;   // two batches of 64 entries per wavefront
+    constexpr int CHUNK = gather_chunk<V, WAVES>();                         // SHARE: k-steps of a chunk of weights
+    constexpr int CHUNK_BYTES = CHUNK * RB * 1024;
+    constexpr int WPW = SHARE ? CHUNK * RB / WAVES : 1;              // kilobytes of it that a wavefront brings
+    static_assert(!SHARE || WPW * WAVES == CHUNK * RB, "whole kilobytes per wavefront");
+    __shared__ __attribute__((aligned(16))) char smem[TILE_BYTES + LIST_BYTES + (SHARE ? 2 * CHUNK_BYTES : 0)];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -630,16 +646,15 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         g = (int)w - tblock * A.G;
     }
     const int tile = tblock * TILES + ti;
-    // without SPLIT a whole wavefront leaves and no workgroup barrier is used; with SPLIT one whose
-    // tile does not exist stays for the barriers, with no steps and nothing to store
-    if (SPLIT == 1 && tile >= n_tiles) return;
+    // without SPLIT or SHARE a whole wavefront leaves and no workgroup barrier is used; with them one whose
+    // tile does not exist stays for the barriers, with nothing to store
+    if (SPLIT == 1 && !SHARE && tile >= n_tiles) return;
     const long n0 = (long)tile * WN;
-    _Float16* my = smem + wave * S::REGION;
 
     // without a memory access when every group has the same number of steps: the column indices can be
     // requested at once instead of after a dependent load (convolutions, which compute their list
     // first, lose 1 to 2 % by it: 3x3, 14x14x256 12.1 -> 12.3 us)
-    const int uniform = LIST ? -1 : order.uniform_steps;
+    const int uniform = Geom::CONV ? -1 : order.uniform_steps;
     int sbeg = uniform >= 0 ? g * uniform : A.step_ptr[g];
     int nsteps = uniform >= 0 ? uniform : A.step_ptr[g + 1] - sbeg;
     if (SPLIT > 1) {
@@ -649,11 +664,9 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         nsteps = tile < n_tiles ? end - first : 0;
     }
 
-    // this lane's share of a staged tile: rows lrow..lrow+NLD-1, 8 columns at lcol
-    const int lrow = (lane / LPR) * NLD;
-    const int lcol = (lane % LPR) * 8;
-    const long ln = n0 + lcol;
-    geom.init(ln);
+    // this lane's share of a step: rows lrow .. lrow+NLD-1, 8 columns
+    const int lrow = lane / LPR * NLD;
+    geom.init(n0 + lane % LPR * 8);
 
     floatx16 acc32[S::SMALL ? 1 : RB][S::SMALL ? 1 : NT];
     floatx4 acc16[S::SMALL ? NT : 1];
@@ -679,13 +692,18 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     // Two row blocks of 128 columns with 32-bit results take each row when it is stored: with the rows at hand the
     // streaming stores come faster than they drain (8192 x 8192 by 4096 at 95 % 58.3 us, 61.7 with the rows at hand,
     // 4096 x 4096 by 4096 at 90 % 29.1 and 30.9; but 8192 x 4096 by 8200, rows of no whole 64-byte blocks, 160 and 149).
+    // V = 64 in 64 columns has registers for them in the loop only where the weights are shared (1024 x 4096 by 8192 at
+    // 85 %, 32-bit results, 23.3 us without, 19.1 with them).  Wavefronts that share steps request theirs after the last
+    // step, before the partial sums meet, whatever the geometry: at the stores, a row block after the other waited for them
+    // (3968 x 7584 by 8, V = 128 13.4 -> 11.9 us, 576 x 632 by 64 and the like 4.5 -> 3.9).
     constexpr bool ROWS_AHEAD = RB <= 2 && std::is_same<Geom, GeomLinearBuf>::value && !(RB == 2 && WN == 128 && sizeof(OutT) == 4);
-    constexpr int EARLY = !ROWS_AHEAD ? 0 : RB == 2 && SPLIT == 1 && sizeof(OutT) == 2 ? 1 : RB;
+    constexpr int EARLY = !ROWS_AHEAD || (V == 64 && WN == 64 && !SHARE) ? 0 : RB == 2 && SPLIT == 1 && sizeof(OutT) == 2 ? 1 : RB;
     constexpr int OPV = 16 / (int)sizeof(OutT);                      // values per 16 bytes
     // a store instruction of 16 bytes per lane: lanes per row and rows, without and with SPLIT
     constexpr int LPR_S = SPLIT > 1 ? WN / OPV : WN / ((int)sizeof(OutT) / 2) / OPV, RPI_S = 64 / LPR_S;
     constexpr int STORES_S = SPLIT > 1 ? (S::ROWS_E / RPI_S + SPLIT - 1) / SPLIT : S::ROWS_E / RPI_S;
-    int out_row[ROWS_AHEAD ? RB : 1][STORES_S];
+    constexpr bool ROWS_HELD = ROWS_AHEAD || SPLIT > 1;   // few per wavefront then, and requested before the partial sums meet
+    int out_row[ROWS_HELD ? RB : 1][STORES_S];
     const int32_t* rows_g = A.row_indices + (long)g * V;
     auto row_of = [&](int i) __attribute__((always_inline)) {         // stored row of this lane in its i-th store of a row block
         return SPLIT > 1 ? (part + i * SPLIT) * RPI_S + lane / LPR_S : i * RPI_S + lane / LPR_S;
@@ -702,229 +720,307 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         for (int rb = 0; rb < EARLY; ++rb) request_rows(rb);
     }
 
-    // ---- pipeline registers
-    int cols[PD][NLD];
-    half8 xr[PD][NLD];
-    int xf[PD][NLD];   // what geom.finish8 needs to know of a load
-    half8 wr[PD][RB];
-
-    // Column indices and weights of the wavefront's steps through buffer descriptors: the
-    // step's offset is a scalar register, the lane's a constant vector register.
-    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-    typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+    // Column indices and weights of the wavefront's steps through buffer descriptors.  A buffer load checks
+    // lane offset + immediate against the descriptor's size (not the scalar offset): the step goes into the
+    // lane offset, so that a step beyond the wavefront's range reads zeros instead of memory past it.
     const __amdgpu_buffer_rsrc_t col_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t*>(A.col_idx + (long)sbeg * TK), 0, nsteps * TK * 4, GATHER_BUFFER_FLAGS);
     const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<half8*>(A.values + (long)sbeg * RB * 64), 0, nsteps * RB * 1024, GATHER_BUFFER_FLAGS);
-    // A buffer load checks lane offset + immediate against the descriptor's size, NOT the
-    // scalar offset.  CHECKED puts the step into the lane offset, so that a step beyond the
-    // wavefront's range reads zeros instead of memory past it; the steady-state batches,
-    // whose steps all exist, keep the step in the scalar offset (no vector arithmetic).
-    auto load_cols = [&](int step, int (&c)[NLD], auto checked_tag) {
-        constexpr bool CHECKED = decltype(checked_tag)::value;
-        const int vo = CHECKED ? lrow * 4 + step * TK * 4 : lrow * 4;
-        const int so = CHECKED ? 0 : step * TK * 4;
-        if constexpr (NLD == 4) {
-            uint4v v = __builtin_amdgcn_raw_buffer_load_b128(col_rsrc, vo, so, 0);
-            c[0] = (int)v[0]; c[1] = (int)v[1]; c[2] = (int)v[2]; c[3] = (int)v[3];
-        } else if constexpr (NLD == 2) {
-            uint2v v = __builtin_amdgcn_raw_buffer_load_b64(col_rsrc, vo, so, 0);
-            c[0] = (int)v[0]; c[1] = (int)v[1];
-        } else {
-#pragma unroll
-            for (int i = 0; i < NLD; ++i)
-                c[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, vo + i * 4, so, 0);
-        }
+
+    // The rows a wavefront gathers are worked out 64 at a time (one per lane, U k-steps) and kept
+    // in a private list in the LDS, two batches of it, so that the divisions by a convolution's kernel size are
+    // paid once per 64 rows and not by every lane for each of its loads (32 images of 14x14,
+    // 256 channels, 3x3, V = 32, 75 %: 12.6 -> 11.8 us), and an address is one addition.
+    constexpr int U = 64 / TK;
+    constexpr int AHEAD = (U + PD) / U;   // batches: the last step of a batch reads entries of the batch AHEAD further on
+    entry_t* list = reinterpret_cast<entry_t*>(smem + TILE_BYTES) + wave * 128;
+    auto fetch = [&](int q) __attribute__((always_inline)) {
+        return (int)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, lane * 4 + q * 256, 0, 0);
     };
-    // in_range false: the step lies beyond the wavefront's range and gets zeros, like a padded slot
-    auto load_x = [&](const int (&c)[NLD], half8 (&x)[NLD], int (&f)[NLD], bool in_range) {
+    auto work_out = [&](int q, int col) __attribute__((always_inline)) {
+        list[(q & 1) * 64 + lane] = geom.entry(col, q * 64 + lane < nsteps * TK);
+    };
+    entry_t ent[NLD];
+    auto look_up = [&](int step) __attribute__((always_inline)) {
+        const entry_t* e = list + (step * TK & 127) + lrow;
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) ent[i] = e[i];
+    };
+    run_t xr[PD][NLD];
+    int xf[PD];   // what geom.finish8 needs to know of the loads, -8 .. 7 each
+    auto request = [&](run_t (&x)[NLD], int& f) __attribute__((always_inline)) {
+        f = 0;
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
-            if constexpr (LIST) x[i] = half8{0, 0, 0, 0, 0, 0, 0, 0};   // not reached
-            else if constexpr (BUF) x[i] = geom.load8(c[i], !in_range, f[i]);
-            else x[i] = geom.load8(in_range ? c[i] : -1, ln);
+            int shift = 0;
+            x[i] = geom.load8(ent[i], shift);
+            if constexpr (Geom::FINISH) f |= (shift & 15) << (4 * i);
         }
     };
-    auto arrived = [&](half8 x, int f) __attribute__((always_inline)) {
-        if constexpr (BUF) {
-            if constexpr (Geom::FINISH) return Geom::finish8(x, f);
-        }
-        return x;
-    };
-    auto load_w = [&](int step, half8 (&w)[RB], auto checked_tag) {
-        constexpr bool CHECKED = decltype(checked_tag)::value;
+
+    // StitchTile in registers.  A lane has 8 columns of NLD neighbouring rows of the step; an operand wants 8 rows of one
+    // column.  Rows are paired column by column (halves of two registers), and lanes that hold the other rows of
+    // the operand trade columns with this one until each has all 8 rows of the columns it keeps: lanes 16 apart
+    // in one instruction per pair of registers, lanes 8 apart (64-column tiles) through the lane shifter.  Operand
+    // t of a lane is column
+    //   128 columns, V >= 32: 8*(l % 16) + 2t + l/16 % 2             64: 8*(l % 8) + 4t + 2*(l/8 % 2) + l/16 % 2
+    //   128 columns, V = 16:  8*(l % 16) + t                         64: 8*(l % 8) + 4*(l/8 % 2) + t
+    // 6 vector instructions per operand (128 columns; V = 16: 4; 12 and 10 in 64 columns).
+    constexpr int PAIRS = NLD / 2 * 8;
+    // rows 2i, 2i+1 of column c at 8*i + c.  The rows' registers are free for the next request then.
+    auto pairs = [&](const run_t (&x)[NLD], unsigned (&p)[PAIRS]) __attribute__((always_inline)) {
+        constexpr unsigned LOW = 0x05040100u, HIGH = 0x07060302u;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int off = (step * RB + rb) * 1024;
-            w[rb] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(
-                val_rsrc, CHECKED ? lane * 16 + off : lane * 16, CHECKED ? 0 : off, 0));
-        }
-    };
-
-    // The loop below is straight-line code over whole batches of PD steps, so that the
-    // register sets stay static and the compiler's wait counts exact (a conditional refill
-    // turns into a copy behind a full wait).  A step beyond the wavefront's range multiplies
-    // zero weights (range-checked loads) with gathered zeros.
-    const int nsteps_r = (nsteps + PD - 1) / PD * PD;
-    if constexpr (!LIST) {
+        for (int i = 0; i < NLD / 2; ++i)
 #pragma unroll
-    for (int u = 0; u < PD; ++u) {
-        int c0[NLD];
-        load_cols(u, c0, std::true_type{});
-        load_x(c0, xr[u], xf[u], u < nsteps);
-        load_cols(u + PD, cols[u], std::true_type{});
-        load_w(u, wr[u], std::true_type{});
-        // sets in the order the loop issues them: its wait counts assume set 0 is the oldest
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    }
-
-    // transposed-read addresses (in binary16 units inside a staged tile)
-    // 32-wide: block b = lane/16 covers n = 16*(b%2)+0..15, k = 8*(b/2)+4h+0..3
-    // 16-wide: block b covers n = 0..15,                k = 8*b+4h+0..3
-    const int bl = lane >> 4, il = lane & 15;
-    const int tr_row = S::SMALL ? (8 * bl + (il >> 2)) : (8 * (bl >> 1) + (il >> 2));
-    const int tr_col = S::SMALL ? (4 * (il & 3)) : (16 * (bl & 1) + 4 * (il & 3));
-    const int tr_off = tr_row * PITCH + tr_col;
-
-    // the products of one step from its staged tile
-    auto multiply = [&](const _Float16* buf, const half8 (&w)[RB]) __attribute__((always_inline)) {
+            for (int c = 0; c < 8; ++c) p[8 * i + c] = __builtin_amdgcn_perm(x[2 * i + 1][c / 2], x[2 * i][c / 2], c % 2 ? HIGH : LOW);
+    };
+    auto operands = [&](const unsigned (&p)[PAIRS], half8 (&o)[NT]) __attribute__((always_inline)) {
+        // a: the own column's rows from the lane with the bit clear, b: from the one with it set
+        auto trade16 = [&](unsigned& a, unsigned& b) __attribute__((always_inline)) {
+            const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+            a = r[0];
+            b = r[1];
+        };
+        auto trade8 = [&](unsigned& a, unsigned& b) __attribute__((always_inline)) {
+            constexpr int ROR8 = 0x128;                                          // lane ^ 8
+            const unsigned a0 = a;
+            a = (unsigned)__builtin_amdgcn_update_dpp((int)a0, (int)b, ROR8, 0xf, 0xc, false);
+            b = (unsigned)__builtin_amdgcn_update_dpp((int)b, (int)a0, ROR8, 0xf, 0x3, false);
+        };
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const _Float16* base = buf + tr_off + t * S::TILE_N;
-            short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(base));
-            short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(base + 4 * PITCH));
-            half4 l4 = __builtin_bit_cast(half4, lo), h4 = __builtin_bit_cast(half4, hi);
-            half8 a = {l4[0], l4[1], l4[2], l4[3], h4[0], h4[1], h4[2], h4[3]};
+            run_t v;
+            if constexpr (S::SMALL && WN == 128) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = p[8 * i + t];
+            } else if constexpr (S::SMALL) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    unsigned a = p[8 * i + t], b = p[8 * i + t + 4];
+                    trade8(a, b);
+                    v[i] = a;
+                    v[2 + i] = b;
+                }
+            } else if constexpr (WN == 128) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    unsigned a = p[8 * i + 2 * t], b = p[8 * i + 2 * t + 1];
+                    trade16(a, b);
+                    v[i] = a;
+                    v[2 + i] = b;
+                }
+            } else {
+                unsigned a = p[4 * t], b = p[4 * t + 1], c = p[4 * t + 2], d = p[4 * t + 3];
+                trade16(a, b);
+                trade16(c, d);
+                trade8(a, c);
+                trade8(b, d);
+                v = run_t{a, c, b, d};
+            }
+            o[t] = __builtin_bit_cast(half8, v);
+        }
+    };
+    auto products = [&](const half8 (&x)[NT], const half8 (&w)[RB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
             if (S::SMALL) {
-                acc16[t] = mma16<BF>(a, w[0], acc16[t]);
+                acc16[t] = mma16<BF>(x[t], w[0], acc16[t]);
             } else {
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-                    acc32[rb][t] = mma32<BF>(a, w[rb], acc32[rb][t]);
+                for (int rb = 0; rb < RB; ++rb) acc32[rb][t] = mma32<BF>(x[t], w[rb], acc32[rb][t]);
             }
         }
     };
 
-    if constexpr (LIST) {
-        // The rows a wavefront gathers are worked out 64 at a time (one per lane, U k-steps) and kept
-        // in a private list in the LDS, two batches of it, so that the divisions by the kernel's size are
-        // paid once per 64 rows and not by every lane for each of its loads (32 images of 14x14,
-        // 256 channels, 3x3, V = 32, 75 %: 12.6 -> 11.8 us).
-        constexpr int U = 64 / TK;
-        static_assert(PD == 2 && U % PD == 0, "loads of a step go out two steps ahead, from this batch's entries or the next one's");
-        typedef typename Geom::entry_t entry_t;
-        entry_t* list = reinterpret_cast<entry_t*>(reinterpret_cast<char*>(smem) + TILE_BYTES) + wave * 128;
-        auto fetch = [&](int q) __attribute__((always_inline)) {
-            return (int)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, lane * 4 + q * 256, 0, 0);
-        };
-        auto work_out = [&](int q, int col) __attribute__((always_inline)) {
-            list[(q & 1) * 64 + lane] = geom.entry(col, q * 64 + lane < nsteps * TK);
-        };
-        // s: k-step; q: its batch
-        auto request = [&](int s, int q, half8 (&x)[NLD], int (&f)[NLD]) __attribute__((always_inline)) {
-            const entry_t* e = list + (q & 1) * 64 + (s - q * U) * TK + lrow;
+    // weights: SHARE by way of the LDS, otherwise a wavefront loads them for itself PD steps ahead (one where
+    // the registers of four wavefronts per SIMD leave no room for more)
+    constexpr int WA = V == 64 && WN == 64 && Geom::FINISH ? 1 : PD;
+    char* ring = smem + TILE_BYTES + LIST_BYTES;
+    half8 ws[WPW], wr[SHARE ? 2 : WA][RB];
+    auto bring = [&](int k) __attribute__((always_inline)) {          // a chunk from memory
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) x[i] = geom.load8(e[i], f[i]);
-        };
-        int c = fetch(0);
+        for (int j = 0; j < WPW; ++j)
+            ws[j] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(
+                val_rsrc, lane * 16 + (wave * WPW + j) * 1024 + k * CHUNK_BYTES, 0, 0));
+    };
+    auto deposit = [&](int k) __attribute__((always_inline)) {        // to the LDS
 #pragma unroll
-        for (int u = 0; u < PD; ++u) load_w(u, wr[u], std::true_type{});
-        work_out(0, c);
-        c = fetch(1);
-        SHFLBW_WAVE_LDS_SYNC();
+        for (int j = 0; j < WPW; ++j)
+            *reinterpret_cast<half8*>(ring + (k & 1) * CHUNK_BYTES + (wave * WPW + j) * 1024 + lane * 16) = ws[j];
+    };
+    auto weights = [&](int k, int v, half8 (&w)[RB]) __attribute__((always_inline)) {   // of the v-th step of chunk k
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            w[rb] = *reinterpret_cast<const half8*>(ring + (k & 1) * CHUNK_BYTES + (v * RB + rb) * 1024 + lane * 16);
+    };
+    auto load_w = [&](int step, half8 (&w)[RB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            w[rb] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16 + (step * RB + rb) * 1024, 0, 0));
+    };
+
+    // The rows of the first PD steps do not wait for the list where an entry is one multiplication.
+    int first[PD][NLD];
+    if constexpr (!Geom::CONV) {
 #pragma unroll
         for (int u = 0; u < PD; ++u) {
-            request(u, u / U, xr[u], xf[u]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        for (int q = 0; q * U < nsteps; ++q) {
-            work_out(q + 1, c);
-            c = fetch(q + 2);
-            SHFLBW_WAVE_LDS_SYNC();
+            const int at = (u * TK + lrow) * 4;
+            if constexpr (NLD == 2) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(col_rsrc, at, 0, 0);
+                first[u][0] = (int)v[0]; first[u][1] = (int)v[1];
+            } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int s = q * U + u;
-                if (u && u % PD == 0 && s >= nsteps) break;   // uniform
-                _Float16* buf = my + (u & 1) * S::STAGE;
+                for (int i = 0; i < NLD; i += 4) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(col_rsrc, at + 4 * i, 0, 0);
 #pragma unroll
-                for (int i = 0; i < NLD; ++i)
-                    *reinterpret_cast<half8*>(buf + (lrow + i) * PITCH + lcol) = arrived(xr[u % PD][i], xf[u % PD][i]);
-                SHFLBW_WAVE_LDS_SYNC();
-                request(s + PD, u + PD < U ? q : q + 1, xr[u % PD], xf[u % PD]);
-                multiply(buf, wr[u % PD]);
-                load_w(s + PD, wr[u % PD], std::true_type{});
-                __builtin_amdgcn_sched_barrier(0);   // steps stay in program order, see below
+                    for (int e = 0; e < 4; ++e) first[u][i + e] = (int)v[e];
+                }
             }
         }
-    } else {
-    // One batch.  NEXT: the batch after this one exists, its X rows and weights are
-    // requested; AFTER: so does the one after that, whose column indices are requested.
-    // The last two batches therefore issue no loads that nobody waits for.
-    auto batch = [&](int s0, auto next_tag, auto after_tag) __attribute__((always_inline)) {
-        constexpr bool NEXT = decltype(next_tag)::value, AFTER = decltype(after_tag)::value;
+    }
+    int c[AHEAD];
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q) c[q] = fetch(q);
+    if constexpr (SHARE) bring(0);
+    else {
+#pragma unroll
+        for (int u = 0; u < WA; ++u) load_w(u, wr[u]);
+    }
+    int cn = fetch(AHEAD);
+    __builtin_amdgcn_sched_barrier(0);   // what the loop waits for first is requested first: its wait counts assume so
+    if constexpr (!Geom::CONV) {
 #pragma unroll
         for (int u = 0; u < PD; ++u) {
-            const int s = s0 + u;
-            _Float16* buf = my + (s & 1) * S::STAGE;
 #pragma unroll
-            for (int i = 0; i < NLD; ++i)
-                *reinterpret_cast<half8*>(buf + (lrow + i) * PITCH + lcol) = arrived(xr[u][i], xf[u][i]);
-            SHFLBW_WAVE_LDS_SYNC();
-
-            if (NEXT) load_x(cols[u], xr[u], xf[u], AFTER || s + PD < nsteps);
-            // may name up to PD - 1 steps past the range: those indices (whatever follows in the
-            // packed matrix) are never turned into addresses
-            if (AFTER) load_cols(s + 2 * PD, cols[u], std::false_type{});
-
-            multiply(buf, wr[u]);
-            // refilled after its last use, so the load lands in the set's own registers
-            // the last loading batch may reach past the range: checked there
-            if (NEXT) load_w(s + PD, wr[u], std::integral_constant<bool, !AFTER>{});
-            // steps stay in program order: hoisting the next step's LDS writes above this
-            // step's products would make them wait for the loads issued just above
+            for (int i = 0; i < NLD; ++i) ent[i] = geom.entry(first[u][i], u < nsteps);
+            request(xr[u], xf[u]);
             __builtin_amdgcn_sched_barrier(0);
-            // no second sync: the next step writes the other buffer, and its own
-            // sync separates these reads from the writes of the step after it
         }
+    }
+#pragma unroll
+    for (int q = 0; q < AHEAD && q < 2; ++q) work_out(q, c[q]);
+    SHFLBW_WAVE_LDS_SYNC();
+    if constexpr (Geom::CONV) {
+#pragma unroll
+        for (int u = 0; u < PD; ++u) {
+            look_up(u);
+            request(xr[u], xf[u]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    SHFLBW_WAVE_LDS_SYNC();
+#pragma unroll
+    for (int q = 2; q < AHEAD; ++q) work_out(q, c[q]);
+    SHFLBW_WAVE_LDS_SYNC();
+    look_up(PD);
+    if constexpr (SHARE) {
+        deposit(0);
+        bring(1);
+        __syncthreads();
+        weights(0, 0, wr[0]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // Steps come in batches of ST that run without a test between their steps, which keeps the register sets static
+    // and the wait counts exact.
+    constexpr int ST = SHARE ? CHUNK : gather_batch<V, WN>();
+    static_assert(ST % PD == 0 && (!SHARE || (ST % U == 0 && ST % 2 == 0)), "register sets are static");
+    // step s, the v-th of its batch
+    auto one = [&](int s, int v) __attribute__((always_inline)) {
+        if (U <= ST ? v % U == 0 : v == 0 && s % U == 0) {   // uniform
+            work_out(s / U + AHEAD, cn);
+            cn = fetch(s / U + AHEAD + 1);
+            SHFLBW_WAVE_LDS_SYNC();
+        }
+        if constexpr (SHARE) {
+            if (v == CHUNK - 2) { deposit(s / CHUNK + 1); bring(s / CHUNK + 2); }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // steps stay in program order
+        unsigned p[PAIRS];
+        half8 o[NT];
+        if constexpr (Geom::FINISH) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) xr[v % PD][i] = Geom::finish8(xr[v % PD][i], xf[v % PD] << (28 - 4 * i) >> 28);
+        }
+        pairs(xr[v % PD], p);
+        if constexpr (!SHARE && WA < PD) {
+            operands(p, o);
+            products(o, wr[0]);
+            load_w(s + 1, wr[0]);   // before the rows that are waited for later
+            request(xr[v % PD], xf[v % PD]);
+            look_up(s + PD + 1);
+        } else {
+            request(xr[v % PD], xf[v % PD]);
+            look_up(s + PD + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            operands(p, o);
+        }
+        if constexpr (SHARE) {
+            if (v != CHUNK - 1) weights(s / CHUNK, v + 1, wr[(v + 1) % 2]);
+            products(o, wr[v % 2]);
+            if (v == CHUNK - 1) {
+                __syncthreads();
+                weights(s / CHUNK + 1, 0, wr[0]);
+            }
+        } else if constexpr (WA == PD) {
+            products(o, wr[v % PD]);
+            load_w(s + PD, wr[v % PD]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    int s0 = 0;
-    for (; s0 + 2 * PD < nsteps_r; s0 += PD) batch(s0, std::true_type{}, std::true_type{});
-    if (s0 + PD < nsteps_r) {
-        batch(s0, std::true_type{}, std::false_type{});
-        s0 += PD;
+    int s = 0;
+    for (; s + ST <= nsteps; s += ST) {
+#pragma unroll
+        for (int v = 0; v < ST; ++v) one(s + v, v);
     }
-    if (s0 < nsteps_r) batch(s0, std::false_type{}, std::false_type{});
+#pragma unroll
+    for (int v = 0; v < ST - 1; ++v) {
+        if (s + v >= nsteps) break;   // uniform
+        one(s + v, v);
     }
-    if constexpr (ROWS_AHEAD) {
+    if constexpr (ROWS_HELD) {
 #pragma unroll
         for (int rb = EARLY; rb < RB; ++rb) request_rows(rb);
     }
     SHFLBW_WAVE_LDS_SYNC();
 
+    // accumulators in groups of four neighbouring columns: group q of row block rb, and its first column
+    auto quad = [&](int rb, int q) __attribute__((always_inline)) {
+        if constexpr (S::SMALL) {
+            const int r = q / (NT / 4), t = q % (NT / 4) * 4;
+            return floatx4{acc16[t][r], acc16[t + 1][r], acc16[t + 2][r], acc16[t + 3][r]};
+        } else if constexpr (WN == 128) {
+            const int r = q / 2, t = q % 2 * 2;
+            return floatx4{acc32[rb][t][r], acc32[rb][t][r + 8], acc32[rb][t + 1][r], acc32[rb][t + 1][r + 8]};
+        } else {
+            const int r = q / 2, t = q % 2;
+            return floatx4{acc32[rb][t][r], acc32[rb][t][r + 8], acc32[rb][t][r + 4], acc32[rb][t][r + 12]};
+        }
+    };
+    auto quad_col = [&](int q) __attribute__((always_inline)) {
+        if constexpr (S::SMALL) return WN == 128 ? 8 * (4 * (lane >> 4) + q / 2) + 4 * (q % 2) : 8 * (4 * (lane >> 4 & 1) + q) + 4 * (lane >> 5);
+        else return WN == 128 ? 8 * (8 * (q / 8) + 4 * (lane >> 5) + q / 2 % 4) + 4 * (q % 2) : 8 * (4 * (lane >> 5) + q / 2) + 4 * (q % 2);
+    };
+    const int lane_row = lane & (S::ROWS_E - 1);   // this lane's row of a row block
+
     if constexpr (SPLIT > 1) {
         // quad q of wavefront w sits at float4 index (w*QUADS + q)*64 + lane, free of bank conflicts
-        constexpr int SHARE = (QUADS + SPLIT - 1) / SPLIT;           // quads a wavefront adds up
+        constexpr int OWN = (QUADS + SPLIT - 1) / SPLIT;           // quads a wavefront adds up
         floatx4* red = reinterpret_cast<floatx4*>(smem);
-        OutT* fin = reinterpret_cast<OutT*>(smem) + ti * S::ROWS_E * EPS;
+        OutT* fin = reinterpret_cast<OutT*>(smem + RED_BYTES) + ti * S::ROWS_E * EPS;
         typedef OutT vec4 __attribute__((ext_vector_type(4)));
         typedef OutT vecw __attribute__((ext_vector_type(OPV)));
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            __syncthreads();   // the staged tiles, or the finished tile of the row block before, are read
+            // the sums of the row block before are taken: its finished tile is
 #pragma unroll
-            for (int q = 0; q < QUADS; ++q) {
-                floatx4 v;
-                if (S::SMALL) v = acc16[q];
-                else
-                    v = floatx4{acc32[rb][q / 4][4 * (q % 4)], acc32[rb][q / 4][4 * (q % 4) + 1],
-                                acc32[rb][q / 4][4 * (q % 4) + 2], acc32[rb][q / 4][4 * (q % 4) + 3]};
-                red[(wave * QUADS + q) * 64 + lane] = v;
-            }
+            for (int q = 0; q < QUADS; ++q) red[(wave * QUADS + q) * 64 + lane] = quad(rb, q);
             __syncthreads();
-            floatx4 sum[SHARE];
+            floatx4 sum[OWN];
 #pragma unroll
-            for (int i = 0; i < SHARE; ++i) {
+            for (int i = 0; i < OWN; ++i) {
                 const int q = part + i * SPLIT;
                 if (QUADS % SPLIT == 0 || q < QUADS) {
                     sum[i] = red[(ti * SPLIT * QUADS + q) * 64 + lane];
@@ -932,14 +1028,12 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
                     for (int p = 1; p < SPLIT; ++p) sum[i] += red[((ti * SPLIT + p) * QUADS + q) * 64 + lane];
                 }
             }
-            __syncthreads();
 #pragma unroll
-            for (int i = 0; i < SHARE; ++i) {
+            for (int i = 0; i < OWN; ++i) {
                 const int q = part + i * SPLIT;
                 if (QUADS % SPLIT == 0 || q < QUADS) {
-                    OutT* d = S::SMALL ? fin + (lane & 15) * EPS + 16 * q + 4 * (lane >> 4)
-                                       : fin + (lane & 31) * EPS + 32 * (q / 4) + 8 * (q % 4) + 4 * (lane >> 5);
-                    *reinterpret_cast<vec4*>(d) = vec4{(OutT)sum[i][0], (OutT)sum[i][1], (OutT)sum[i][2], (OutT)sum[i][3]};
+                    // (the tile before was read before the barrier above)
+                    *reinterpret_cast<vec4*>(fin + lane_row * EPS + quad_col(q)) = vec4{(OutT)sum[i][0], (OutT)sum[i][1], (OutT)sum[i][2], (OutT)sum[i][3]};
                 }
             }
             __syncthreads();
@@ -958,7 +1052,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
                         OutT tmp[OPV];
 #pragma unroll
                         for (int e = 0; e < OPV; ++e) tmp[e] = v[i][e];
-                        const int orig = ROWS_AHEAD ? out_row[ROWS_AHEAD ? rb : 0][i] : rows_g[rb * 32 + row];
+                        const int orig = ROWS_HELD ? out_row[ROWS_HELD ? rb : 0][i] : rows_g[rb * 32 + row];
                         geom.template store<decltype(stream_tag)::value, OPV>(orig, n0 + lane % LPR_S * OPV, tmp);
                     }
                 }
@@ -973,8 +1067,8 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     constexpr int PASSES = (int)sizeof(OutT) / 2;                   // column halves per row block
     constexpr int CW = WN / PASSES;                                  // columns per pass
     constexpr int EP = CW + 16 / (int)sizeof(OutT);                 // pitch in OutT units
-    static_assert(S::ROWS_E * EP * (int)sizeof(OutT) <= S::REGION * 2, "epilogue tile must fit");
-    OutT* ep = reinterpret_cast<OutT*>(my);
+    static_assert(S::ROWS_E * EP * (int)sizeof(OutT) <= S::EPI * 2, "epilogue tile must fit");
+    OutT* ep = reinterpret_cast<OutT*>(smem + wave * S::EPI * 2);
     static_assert(SPLIT > 1 || CW / OPV == LPR_S, "lanes per row at readback");
     const int echunk = lane % LPR_S;
 
@@ -982,25 +1076,15 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
         for (int pass = 0; pass < PASSES; ++pass) {
-            constexpr int TPP = NT / PASSES;  // instruction tiles per pass
+            // the columns of a pass are half of every lane's groups, or all groups of half of the lanes
+            constexpr bool BY_GROUP = PASSES > 1 && !S::SMALL && WN == 128;
+            if (PASSES == 1 || BY_GROUP || (WN == 128 || !S::SMALL ? lane >> 5 : lane >> 4 & 1) == pass) {
 #pragma unroll
-            for (int tt = 0; tt < TPP; ++tt) {
-                const int t = pass * TPP + tt;
-                if (S::SMALL) {
-                    // lane: row l%16, n = 16*tt + 4*(l/16) + 0..3
-                    OutT* d = ep + (lane & 15) * EP + 16 * tt + 4 * (lane >> 4);
+                for (int i = 0; i < (BY_GROUP ? QUADS / PASSES : QUADS); ++i) {
+                    const int q = BY_GROUP ? pass * (QUADS / PASSES) + i : i;
+                    const floatx4 a = quad(rb, q);
                     typedef OutT vec4 __attribute__((ext_vector_type(4)));
-                    vec4 v = {(OutT)acc16[t][0], (OutT)acc16[t][1], (OutT)acc16[t][2], (OutT)acc16[t][3]};
-                    *reinterpret_cast<vec4*>(d) = v;
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        OutT* d = ep + (lane & 31) * EP + 32 * tt + 8 * q + 4 * (lane >> 5);
-                        typedef OutT vec4 __attribute__((ext_vector_type(4)));
-                        vec4 v = {(OutT)acc32[rb][t][4 * q + 0], (OutT)acc32[rb][t][4 * q + 1],
-                                  (OutT)acc32[rb][t][4 * q + 2], (OutT)acc32[rb][t][4 * q + 3]};
-                        *reinterpret_cast<vec4*>(d) = v;
-                    }
+                    *reinterpret_cast<vec4*>(ep + lane_row * EP + quad_col(q) - pass * CW) = vec4{(OutT)a[0], (OutT)a[1], (OutT)a[2], (OutT)a[3]};
                 }
             }
             SHFLBW_WAVE_LDS_SYNC();
@@ -1014,7 +1098,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
                     OutT tmp[OPV];
 #pragma unroll
                     for (int e = 0; e < OPV; ++e) tmp[e] = v[i][e];
-                    const int orig = ROWS_AHEAD ? out_row[ROWS_AHEAD ? rb : 0][i] : rows_g[rb * 32 + row_of(i)];
+                    const int orig = ROWS_HELD ? out_row[ROWS_HELD ? rb : 0][i] : rows_g[rb * 32 + row_of(i)];
                     geom.template store<decltype(stream_tag)::value, OPV>(orig, n0 + pass * CW + echunk * OPV, tmp);
                 }
             });
