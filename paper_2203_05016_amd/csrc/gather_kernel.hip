@@ -626,9 +626,14 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     constexpr int EPS = WN + 16 / (int)sizeof(OutT);                 // row pitch of a finished tile (SPLIT > 1), in OutT units
     constexpr int RED_BYTES = WAVES * QUADS * 1024;
     constexpr int FIN_BYTES = TILES * S::ROWS_E * EPS * (int)sizeof(OutT);
-    constexpr int TILE_BYTES = SPLIT == 1 ? WAVES * S::EPI * 2 : RED_BYTES + FIN_BYTES;
+    // the finished tile lies apart from the partial sums (over the lists, which are read by then), which saves two
+    // barriers per row block, but where that would cost residency
+    constexpr bool APART = sizeof(OutT) == 2 || SPLIT == 8;
+    static_assert(SPLIT == 1 || APART || FIN_BYTES <= RED_BYTES, "the finished tile lies where the partial sums were");
+    constexpr int TILE_BYTES = SPLIT == 1 ? WAVES * S::EPI * 2 : RED_BYTES;
     typedef typename Geom::entry_t entry_t;
-    constexpr int LIST_BYTES = (int)sizeof(entry_t) * WAVES * 2 * 64;   // two batches of 64 entries per wavefront
+    constexpr int LISTS = (int)sizeof(entry_t) * WAVES * 2 * 64;        // two batches of 64 entries per wavefront
+    constexpr int LIST_BYTES = SPLIT > 1 && APART && FIN_BYTES > LISTS ? FIN_BYTES : LISTS;
     constexpr int CHUNK = gather_chunk<V, WAVES>();                         // SHARE: k-steps of a chunk of weights
     constexpr int CHUNK_BYTES = CHUNK * RB * 1024;
     constexpr int WPW = SHARE ? CHUNK * RB / WAVES : 1;              // kilobytes of it that a wavefront brings
@@ -1009,12 +1014,13 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         // quad q of wavefront w sits at float4 index (w*QUADS + q)*64 + lane, free of bank conflicts
         constexpr int OWN = (QUADS + SPLIT - 1) / SPLIT;           // quads a wavefront adds up
         floatx4* red = reinterpret_cast<floatx4*>(smem);
-        OutT* fin = reinterpret_cast<OutT*>(smem + RED_BYTES) + ti * S::ROWS_E * EPS;
+        OutT* fin = reinterpret_cast<OutT*>(smem + (APART ? RED_BYTES : 0)) + ti * S::ROWS_E * EPS;
         typedef OutT vec4 __attribute__((ext_vector_type(4)));
         typedef OutT vecw __attribute__((ext_vector_type(OPV)));
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            // the sums of the row block before are taken: its finished tile is
+            // (APART: every wavefront has taken its sums of the row block before when its tile is finished)
+            if (!APART && rb) __syncthreads();
 #pragma unroll
             for (int q = 0; q < QUADS; ++q) red[(wave * QUADS + q) * 64 + lane] = quad(rb, q);
             __syncthreads();
@@ -1028,6 +1034,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
                     for (int p = 1; p < SPLIT; ++p) sum[i] += red[((ti * SPLIT + p) * QUADS + q) * 64 + lane];
                 }
             }
+            if (!APART) __syncthreads();
 #pragma unroll
             for (int i = 0; i < OWN; ++i) {
                 const int q = part + i * SPLIT;
