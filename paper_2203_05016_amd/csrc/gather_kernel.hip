@@ -589,9 +589,14 @@ constexpr int gather_chunk() { return V == 128 || (V == 64 && WAVES == 4) ? 4 : 
 template <int V, int WN>
 constexpr int gather_ahead() { return 2; }
 
-// k-steps of one pass through the loop where the weights are not shared
-template <int V, int WN>
-constexpr int gather_batch() { return V == 32 && WN == 128 ? 4 : 2; }
+// k-steps of one pass through the loop where the weights are not shared.  Whole tiles of 128 columns, V = 32: two, which
+// leaves three wavefronts per SIMD (136 to 159 registers; four steps took 202 to 223 of them, two wavefronts).  us by four /
+// two steps, 3x3, V = 32: 64 images of 56x56, 64 -> 256 channels at 50 %, NCHW 124 / 112, CHWN 75.0 / 65.7; 64 of 28x28,
+// 128 -> 512 at 50 %, CHWN 63.9 / 58.2; linear layers: 6272 x 65 by 2880 10.3 / 9.5, 2816 x 3200 by 12121 at 95 % 87.9 / 85.0.
+// Shared steps run on one or two workgroups per CU either way: 608 x 240 by 14241 unpruned 19.2 / 20.0, 704 x 1568 by 2021
+// at 85 % 8.1 / 7.7.
+template <int V, int WN, int SHARES>
+constexpr int gather_batch() { return V == 32 && WN == 128 && SHARES > 1 ? 4 : 2; }
 
 // Wavefronts a SIMD must be able to hold (SPLIT: SHARES of the kernel).  Left alone, the compiler counts on one workgroup per CU: with four
 // wavefronts or fewer in it, a SIMD to each, it keeps the accumulators in registers of their own (V = 128: 328
@@ -930,7 +935,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
 
     // Steps come in batches of ST that run without a test between their steps, which keeps the register sets static
     // and the wait counts exact.
-    constexpr int ST = SHARE ? CHUNK : gather_batch<V, WN>();
+    constexpr int ST = SHARE ? CHUNK : gather_batch<V, WN, SHARES>();
     static_assert(ST % PD == 0 && (!SHARE || (ST % U == 0 && ST % 2 == 0)), "register sets are static");
     // step s, the v-th of its batch
     auto one = [&](int s, int v) __attribute__((always_inline)) {
