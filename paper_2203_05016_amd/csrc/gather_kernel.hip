@@ -845,8 +845,9 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     };
 
     // weights: SHARE by way of the LDS, otherwise a wavefront loads them for itself PD steps ahead (one where
-    // the registers of four wavefronts per SIMD leave no room for more)
-    constexpr int WA = V == 64 && WN == 64 && Geom::FINISH ? 1 : PD;
+    // the registers of its share of a SIMD leave no room for more: with 64-bit addresses, V = 64, two steps spilled 2
+    // registers of 128 in 64 columns and 11 of 256 in a convolution's 128)
+    constexpr int WA = V == 64 && ((WN == 64 && Geom::FINISH) || !std::is_base_of<GeomLinearBuf, Geom>::value) ? 1 : PD;
     char* ring = smem + TILE_BYTES + LIST_BYTES;
     half8 ws[WPW], wr[SHARE ? 2 : WA][RB];
     auto bring = [&](int k) __attribute__((always_inline)) {          // a chunk from memory
