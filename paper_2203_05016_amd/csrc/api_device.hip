@@ -490,24 +490,9 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
         return fail(SHFLBW_ERR_BAD_OPTION, "slab kernel needs the windowed layout and aligned operands");
     bool use_slab = A->tune_kernel == 2;
     if (A->tune_kernel == 0 && slab_possible) {
-        // Automatic choice, from timings of both kernels: the slab kernel streams all of X whatever the sparsity, and
-        // a workgroup's 12 groups share it, so it pays where a gathered byte serves few rows (V = 16, 32) and enough of each
-        // chunk is used, provided its workgroups, one per CU, fill their last round.  us slab / gather: V = 32, 4096 x 4096
-        // by 8192 (704 workgroups) at 75 % 108 / 109, 50 % 182 / 193, 0 % 306 / 376; 4096 x 1024 by 8192 at 75 % 36.3 / 33.0,
-        // 50 % 55 / 57, 0 % 85 / 99; 2048 x 2048 by 16384 at 75 % 60.7 / 58.0; 5760 x 5480 by 2264 (270 workgroups: two rounds) at
-        // 75 % 92 / 78; 1024 x 4096 by 8192 (192) 35.5 / 28.2, at 50 % 53 / 53; V = 16, 4096 x 4096 by 8192 at 75 % 178 / 189,
-        // 4096 x 1024 62 / 57, 6096 x 302 by 6688 37 / 43, 1024 x 4096 (384: 75 % full) 62 / 53.  V = 64 and 128 are gathered at every
-        // density: 8192 x 8192 by 16384 at 75 % 671 / 593, 4096 x 4096 by 8192, V = 64 at 75 % 87 / 76, 0 % 266 / 262,
-        // V = 128 87 / 77, 0 % 264 / 252.
-        const long tiles = ((N + SLAB_TN - 1) / SLAB_TN) * ((A->G + 11) / 12);
-        const double density = (double)A->nnz / ((double)A->M * A->K);
-        const double full = tiles > 0 ? (double)tiles / (double)((tiles + 255) / 256 * 256) : 0;
-        bool pays;
-        if (A->V == 16) pays = density >= (tiles < 128 ? 0.6 : full >= 0.85 ? 0.17 : full >= 0.65 ? 0.35 : 0.6);
-        else pays = tiles >= 128 && density >= (tiles >= 256 && full >= 0.85 ? 0.17 : tiles >= 256 && full >= 0.65 ? 0.3 : 0.5);
-        // very few column tiles: the gather kernel with split k-steps fills the chip better
-        const bool skinny = ((N + 63) / 64) * A->G <= 512;
-        use_slab = A->V <= 32 && A->G >= 12 && pays && !skinny;
+        // the slab kernel streams all of X whatever the sparsity and its workgroup's groups share it: it pays where
+        // enough of each chunk is used, sooner where a gathered byte serves few rows (V = 16, 32)
+        use_slab = choose_cut(cut_sizes(A, (long)N, Rows::ALIGNED, ydtype == SHFLBW_F32)) == SLAB;
     }
     if (use_slab) {
         if (A->dtype == SHFLBW_BF16) {

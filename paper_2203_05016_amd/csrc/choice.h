@@ -1,0 +1,173 @@
+// Which kernel a linear layer takes and how its work is cut, from sizes alone.  Host code without HIP.
+#pragma once
+
+namespace shflbw {
+
+// A workgroup's tiles: four of 64 or of 128 columns, one wavefront each; one of 128 columns whose k-steps 2 or 4 wavefronts
+// share; one of 64 whose steps 2, 4 or 8 share; and the shared-slab kernel.
+enum Cut { WHOLE_64, WHOLE_128, WIDE_BY_2, WIDE_BY_4, BY_2, BY_4, BY_8, SLAB };
+constexpr int GATHER_CUTS = 7;
+
+// The rows of X: whole 16-byte units, no particular alignment, or those of images (1x1 convolutions; short rows).
+enum class Rows { ALIGNED, ANY, IMAGES };
+
+struct CutSizes {
+    int V;
+    long G, N, steps;       // groups, output columns (whole slots of 8 where rows are not aligned), k-steps of all groups
+    int K;
+    Rows rows;
+    bool uneven;            // groups of different numbers of steps
+    bool f32;               // 32-bit results
+    bool slab;              // the layout and the operands admit the slab kernel
+    double kept;            // share of the weights that is kept
+
+    long per() const { return steps / (G > 0 ? G : 1); }
+    long tiles() const { return (N + 63) / 64 * G; }
+    int v() const { return V == 16 ? 0 : V == 32 ? 1 : V == 64 ? 2 : 3; }
+};
+
+// Whole tiles take their weights by way of the LDS from 5 k-steps (V = 16 in 128 columns: from 13): four fetches of them
+// become one, at the price of a barrier every 4 or 8 steps.  Time shared / own, geometric mean over the products of
+// profiles/cut_sweep.csv with 200 workgroups or more, by steps:
+//                     up to 4   5-8    9-12   13-16   17-32   33-64   more
+//   64 columns, V 16     .98    .96    .95    .91     .90     .90     .85
+//               V 32     .99    .96    .94    .92     .90     .87     .81
+//               V 64     .98    .96    .94    .93     .89     .86     .78
+//               V 128    .99    .97    .96    .92     .94     .88     .82
+//   128 columns, V 16   1.05   1.01   1.04    .96     .99    1.03    1.00
+//               V 32    1.01    .99    .97    .97     .94     .91     .88
+//               V 64    1.00    .98    .97    .97     .95     .92     .87
+// (up to 4 steps 64 columns gain nothing that a repetition would show: the plain kernel, which holds more wavefronts)
+inline bool shares_weights(int V, bool wide, long per) { return per > (V == 16 && wide ? 12 : 4); }
+
+// Workgroups of the fullest of 256 CUs; beyond four rounds they even out.
+inline double rounds_of(long workgroups) { return workgroups > 1024 ? (double)workgroups / 256 : (double)((workgroups + 255) / 256); }
+
+// The slab kernel deals column tiles of 128 to the eight XCDs in turn, one workgroup of 12 (V = 64: 8, V = 128: 4) groups
+// per CU: what counts is the XCD with most tiles.  (1152 columns are nine tiles, two of them on one XCD: 6624 x 4152 at
+// 75 %, V = 32, 162 workgroups, 68 us where 36 would be a full round's.)
+inline long slab_group_blocks(const CutSizes& s)
+{
+    const long per = s.V <= 32 ? 12 : s.V == 64 ? 8 : 4;
+    return (s.G + per - 1) / per;
+}
+inline double slab_rounds(const CutSizes& s)
+{
+    const long on_xcd = ((s.N + 127) / 128 + 7) / 8 * slab_group_blocks(s);
+    return on_xcd > 256 ? (double)on_xcd / 32 : (double)((on_xcd + 31) / 32);
+}
+// ... with enough groups to fill its compute wavefronts, a quarter of a round of workgroups, and more than very few tiles,
+// which the gather kernel's split steps spread better
+inline bool slab_considered(const CutSizes& s)
+{
+    return s.slab && s.G >= (s.V <= 32 ? 12 : s.V == 64 ? 8 : 4) && s.tiles() > 512 && (s.N + 127) / 128 * slab_group_blocks(s) >= 64;
+}
+
+// Estimated time of a cut, us.  A CU's first workgroup takes `start` plus `first` per k-step, each further one `step`
+// per k-step (the memory pipeline is full by then), each `store` for its epilogue and stores (16-bit results).  From the
+// times of 3740 products in every cut that they admit (profiles/cut_sweep.csv: V 16 to 128, 1 to 500 steps, 1 to
+// 512 groups, 1 to 16384 columns, aligned, unaligned, images): the parameters that make the choice below lose least.
+inline double cut_time(const CutSizes& s, Cut cut)
+{
+    struct Cost { double start, first, step, store; };
+    constexpr Cost NONE = {1e9, 0, 0, 0};   // four row blocks x four tiles of accumulators do not fit
+    constexpr Cost COSTS[4][GATHER_CUTS] = {
+        {{2.91, .17, .188, .272}, {3.59, .29, .336, .369}, {3, .113, .089, .269}, {3.4, .078, .103, .381},
+         {2.8, .097, .063, .111}, {2.81, .055, .066, .19}, {2.97, .054, .059, .597}},
+        {{2.31, .129, .094, .688}, {2.84, .165, .164, 1.09}, {2.49, .083, .045, .66}, {2.99, .052, .06, .854},
+         {2.18, .091, .038, .247}, {2.42, .054, .041, .315}, {2.38, .037, .042, .694}},
+        {{2.22, .167, .111, 1.32}, {.75, .236, .16, 3.5}, {3.38, .106, .06, 1.06}, {3.57, .064, .093, 1.24},
+         {2.8, .111, .056, .362}, {2.47, .066, .058, .541}, {2.75, .047, .064, 1.07}},
+        {{2.37, .221, .176, 3.27}, NONE, NONE, NONE,
+         {2.95, .14, .09, .906}, {2.94, .079, .109, 1.32}, {2.99, .06, .13, 2.98}}};
+    // us per round of workgroups: per k-step, per chunk of 64 rows of X (all are streamed, kept or not), and for the stores
+    struct SlabCost { double step, chunk, store, start; };
+    constexpr SlabCost SLAB_COSTS[4] = {{.298, .215, 2.83, 1.13}, {.198, .249, 4.47, .208}, {.262, .239, 5.49, 0}, {.271, .276, 4.88, 0}};
+    const double per = (double)s.per();
+    if (cut == SLAB) {
+        const SlabCost& c = SLAB_COSTS[s.v()];
+        return c.start + slab_rounds(s) * (per * c.step + s.K / 64. * c.chunk + c.store * (s.f32 ? 1.56 : 1));
+    }
+    const Cost& c = COSTS[s.v()][cut];
+    const bool whole = cut == WHOLE_64 || cut == WHOLE_128;
+    const long columns = cut == WHOLE_128 || cut == WIDE_BY_2 || cut == WIDE_BY_4 ? 128 : 64, tiles = (s.N + columns - 1) / columns;
+    const double rounds = rounds_of(s.G * (whole ? (tiles + 3) / 4 : tiles));
+    double steps = per, store = c.store;
+    if (s.uneven) steps *= whole ? 1.47 : 1.09;   // a CU's workgroups wait for the longest group
+    if (s.f32) {
+        store *= !whole ? 1.18 : s.V == 64 && cut == WHOLE_128 ? 2.09 : 2.18;
+        // two row blocks in wide tiles leave in bursts, which the next tile's loads wait for: whole tiles of 128 columns against 64, geometric
+        // means, 8 steps 1.18, 24 1.13, 48 1.06, 96 1.02, more .97
+        if (s.V == 64 && columns == 128) steps *= cut == WHOLE_128 && per < 96 ? 1.5 : 1.18;
+    }
+    // unaligned rows cost the address unit twice the accesses, and their stores two lines
+    if (s.rows == Rows::ANY) { steps *= whole ? 1.21 : 1.16; store *= 1.44; }
+    if (s.rows == Rows::IMAGES) { steps *= whole ? 1.23 : 1.03; store *= 1.45; }
+    return c.start + steps * c.first + store + (rounds - 1) * (steps * c.step + store);
+}
+
+// By tiles of 64 columns x one group and k-steps of a group: fewer tiles than four to seven per CU (by V and steps) leave
+// CUs idle or unevenly loaded, so the k-steps of a tile are shared by 2, 4 or 8 wavefronts.  WHOLE_64: they are not.
+// Measured, us by whole tiles / split by 2 / 4 / 8 (the host's part is 3.1):
+//   32 tiles of 2 k-steps (512 x 512 by 64 at 90 %, V = 16)         3.1 /  3.1 /  3.1 /  3.2
+//   32 tiles of 4 k-steps (512 x 512 by 64 at 75 %, V = 16)         3.6 /  3.2 /  3.1 /  3.2
+//   8 tiles of 2 k-steps (512 x 512 by 64 at 90 %, V = 64)          3.2 /  3.4 /  3.3 /  3.9
+//   512 tiles of 2 k-steps (512 x 512 by 1024 at 90 %, V = 16)      3.1 /  3.2 /  3.4 /  4.3
+//   1024 tiles of 2 k-steps (512 x 512 by 2048 at 90 %, V = 16)     3.0 /  3.5 /  4.2 /  6.2
+//   128 tiles of 64 k-steps (4096 x 4096 by 64, V = 32)            14.0 /  9.1 /  6.2 /  5.1
+//   128 tiles of 16 k-steps (1024 x 1024 by 512, V = 64)            5.6 /  4.5 /  4.0 /  4.4
+//   448 tiles of 72 k-steps (3x3, 14x14x256 -> 256, V = 64)        36.5 / 18.0 / 13.3 / 13.6
+//   512 tiles of 26 k-steps (2048 x 4096 by 1024, V = 64)          10.5 /  7.9 /  6.8 /  7.6
+//   784 tiles of  5 k-steps (3x3, 28x28x64 -> 64, V = 16)           9.4 /  9.3 / 10.1 / 12.7
+//   1200 tiles of  8 k-steps (1024 x 1024 by 9600 at 88 %, V = 128) 10.3 / 11.3 / 14.0 / 24.7
+//   1408 tiles of 16 k-steps (1024 x 1024 by 2816, V = 32)          7.0 /  6.6 /  7.6 / 10.1
+//   1536 tiles of  8 k-steps (1024 x 1024 by 1536, V = 16)          7.2 /  7.0 /  7.3 /  9.9
+//   1568 tiles of 18 k-steps (3x3 / 2, 56x56x128 -> 128, V = 32)   10.3 / 10.3 / 11.0 / 13.7
+//   1792 tiles of 32 k-steps (1x1, 7x7x512 -> 2048, V = 32)        20.8 / 18.9 / 19.3 / 21.0
+//   1792 tiles of 32 k-steps (1024 x 2048 by 7168, V = 64)         13.9 / 14.5 / 15.9 / 19.5
+// Convolutions take it as it is: over 132 of them, 3x3 and 5x5, it costs 1.025 of the best cut's time (geometric mean); what it misses is
+// one to two thousand tiles of whole groups, which would do better split (25x25, 128 -> 416 channels at 90 %, 61 images, V = 32, 56 us, split by 2 32).
+inline Cut cut_by_tiles(int V, long tiles, long per)
+{
+    if (tiles <= 256 && per >= 32) return BY_8;
+    if ((tiles <= 256 && per >= 4) || (tiles <= 512 && per >= 32)) return BY_4;
+    const bool by2 = tiles <= 1024 ? per >= (V == 16 && tiles > 512 ? 3 : 2) :
+                     V <= 64 && (tiles <= 1360 ? per >= 8 : tiles <= 1600 ? per >= (V == 16 ? 8 : 16) : V == 32 && tiles <= 1800 && per >= 32);
+    return by2 ? BY_2 : WHOLE_64;
+}
+
+// 128 columns fetch the weights half as often, which decides where there are thousands of tiles and many steps
+inline bool wide_by_tiles(const CutSizes& s) { return s.V <= 64 && s.steps >= 20 * s.G && (s.N + 127) / 128 * s.G >= 2048; }
+
+// The cut of a linear layer of four groups or more.  Numbers of tiles, steps and kept weights propose one, and the
+// estimates overrule it where another is 10 % below: they are within 15 to 20 % of the times, and better between cuts
+// of one product.  Over the sweep the choice takes 1.02 times the best cut's time (geometric mean; 95 % of the products within
+// 1.12).  The proposal alone takes 1.05 (1.23), the least estimate alone 1.03 (1.15); cuts by time per k-step without a workgroup's
+// own cost, and the slab kernel for V = 16 and 32 alone, took 1.05 (1.24).
+// Slab against gather, us, 16-bit results: V = 16, 4096 x 1024 by 8192 at 83 % 54.2 / 49.0, 80 % 53.8 / 49.5, 75 % 56.1 / 68.6;
+// V = 32, the same 83 % 34.0 / 27.5, 80 % 34.5 / 31.7, 75 % 34.9 / 33.7, 70 % 38.8 / 38.1, 60 % 43.6 / 48.4, 50 % 46.6 / 54.9;
+// 4096 x 4096 by 8192 at 80 % 105 / 92, 75 % 109 / 108, 70 % 121 / 131, 50 % 160 / 203; V = 64, 4096 x 1024 by 8192 at 75 % 31.4 / 26.7,
+// 50 % 42.9 / 42.7, 0 % 67.5 / 74.5; 8192 x 8192 by 16384 at 75 % 671 / 574, 50 % 1048 / 1083, 0 % 1937 / 2075; 2048 x 296 by
+// 14216 at 50 % 29.5 / 31.4, with 32-bit results 44.4 / 53.4; V = 128, 4096 x 4096 by 8192 at 75 % 97 / 79, 50 % 140 / 140, 0 % 247 / 267.
+// The proposal's limits are where the two cross; at 75 %, V = 32, they are within 8 % of each other.
+inline Cut choose_cut(const CutSizes& s)
+{
+    Cut proposed = cut_by_tiles(s.V, s.tiles(), s.per());
+    if (proposed == WHOLE_64 && wide_by_tiles(s)) proposed = WHOLE_128;
+    const bool slab = slab_considered(s);
+    if (slab) {
+        const long workgroups = (s.N + 127) / 128 * slab_group_blocks(s);
+        const double need = s.V == 16 ? (workgroups >= 128 ? .2 : .6) : workgroups < 128 ? 2 : workgroups < 256 ? .5 : s.V == 32 ? .25 : .4;
+        if (s.kept >= need) proposed = SLAB;
+    }
+    Cut best = proposed;
+    double least = .9 * cut_time(s, proposed);
+    for (int c = 0; c <= SLAB; ++c) {
+        if (c == SLAB && !slab) continue;
+        const double t = cut_time(s, (Cut)c);
+        if (t < least) { least = t; best = (Cut)c; }
+    }
+    return best;
+}
+
+}  // namespace shflbw

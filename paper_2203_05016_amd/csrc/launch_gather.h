@@ -4,10 +4,25 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "choice.h"
 #include "gather_kernel.hip"
 #include "shflbw_internal.h"
 
 namespace shflbw {
+
+// what the choice of a cut looks at
+inline CutSizes cut_sizes(const shflbw_matrix* A, long N, Rows rows, bool f32)
+{
+    CutSizes s;
+    s.V = A->V; s.G = A->G; s.N = N; s.K = A->K;
+    s.steps = A->step_ptr.empty() ? 0 : A->step_ptr.back();
+    s.rows = rows;
+    s.uneven = A->uniform_steps < 0;
+    s.f32 = f32;
+    s.slab = rows == Rows::ALIGNED && A->slab_ok;
+    s.kept = (double)A->nnz / ((double)A->M * A->K);
+    return s;
+}
 
 int run_gather_f16(const shflbw_matrix* A, const GeomLinear<true>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_f16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, shflbw_dtype ydtype, hipStream_t stream);
