@@ -174,9 +174,9 @@ __device__ __forceinline__ void store_run(OutT* p, const OutT* vals)
 }
 
 // The aligned linear layer again, with X behind a buffer descriptor: a load's
-// address is one 24-bit multiply-add in a vector register (byte offset of the
-// row plus the lane's column offset) instead of 64-bit arithmetic, and the
-// descriptor's range check stands in for the two conditions - a padded slot
+// address is a saturating addition and a minimum in a vector register (byte offset of the
+// row, one 24-bit multiplication per entry of the list, plus the lane's column offset) instead of 64-bit
+// arithmetic, and the descriptor's range check stands in for the two conditions - a padded slot
 // (column -1) and a lane beyond N get an offset past the end and read as zero.
 // The host uses it when K and 2*ldx are below 2^24 and X spans less than 4 GiB.
 constexpr int GATHER_BUFFER_FLAGS = 0x00020000;   // last word of a raw buffer descriptor: untyped 32-bit data
@@ -233,9 +233,10 @@ struct GeomLinearBuf {
 // the same terms in the same order, and stored twice with the same bits.  Measured on 4096 x
 // 1024 by 1024 x 2047 (V = 32, 75 %): 18.5 us against 65 us with element-wise loads and stores
 // (12.6 us at N = 2048: a row segment of 128 bytes spans two lines when it is not aligned).
-// Loading odd offsets one value early, with the missing last value from the next lane, takes the
-// address unit's accesses from 62 to 20 per load and gains nothing (18.6 us; convolutions lose 1 us
-// to the extra instructions).
+// What a load costs is set by whether it is aligned at all (58 to 72 GB/s per CU at any misalignment, 130 aligned), not by the
+// address unit's accesses that the counters show, 62 for a load at an odd element, 20 at an even one: loading odd offsets one
+// value early, with the missing last value from the next lane, gained nothing when rows went through the LDS (18.6 us; convolutions
+// lost 1 us to the extra instructions).  It was not repeated with the rows in registers.
 struct GeomRows : GeomLinearBuf {
     long x_image, y_image;   // element strides between images
     int P, slots;            // columns of an image, and ceil(P / 8)
@@ -347,7 +348,7 @@ struct GeomNarrow : GeomLinearBuf {
 };
 
 // Convolution whose gathered values come in runs of 8 along the tensor's innermost dimension
-// (Section 4.1's implicit GEMM, unfolded on the way into the LDS): images for CHWN (any stride,
+// (Section 4.1's implicit GEMM, unfolded on the way into the registers): images for CHWN (any stride,
 // 8 or more images), output columns of one row for NCHW (unit stride along x, 8 or more output
 // columns, padding of at most one column).  As in GeomRows the innermost dimension is cut into slots
 // of 8 of which the last may overlap the one before, so that every load is 16 bytes of one row of
@@ -585,9 +586,8 @@ __device__ __forceinline__ void with_stores(const Geom& geom, F&& f)
 template <int V, int WAVES>
 constexpr int gather_chunk() { return V == 128 || (V == 64 && WAVES == 4) ? 4 : 8; }
 
-// k-steps whose rows (and weights, unless shared) are on their way while a step multiplies
-template <int V, int WN>
-constexpr int gather_ahead() { return 2; }
+// k-steps whose rows (and weights, unless shared) are on their way while a step multiplies (four gained nothing)
+constexpr int GATHER_AHEAD = 2;
 
 // k-steps of one pass through the loop where the weights are not shared.  Whole tiles of 128 columns, V = 32: two, which
 // leaves three wavefronts per SIMD (136 to 159 registers; four steps took 202 to 223 of them, two wavefronts).  us by four /
@@ -617,12 +617,12 @@ constexpr int gather_min_waves()
 // SHARES > 1 (SPLIT; too few tiles to fill the chip): SHARES neighbouring wavefronts share one tile, each
 // takes a contiguous share of the group's k-steps; the partial accumulators of a row block meet in
 // the LDS, every wavefront of the tile adds up its share of them and stores its share of the rows.
-template <int V, int WN, int WAVES, int PD, typename OutT, class Geom, bool BF, int SHARES>
+template <int V, int WN, int WAVES, typename OutT, class Geom, bool BF, int SHARES>
 __global__ __launch_bounds__(64 * WAVES, (gather_min_waves<V, WN, Geom, SHARES>()))
 void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder order)
 {
     using S = GatherShape<V, WN>;
-    constexpr int TK = S::TK, RB = S::RB, NT = S::NT, LPR = S::LPR, NLD = S::NLD;
+    constexpr int TK = S::TK, RB = S::RB, NT = S::NT, LPR = S::LPR, NLD = S::NLD, PD = GATHER_AHEAD;
     constexpr bool SHARE = SHARES == 0;
     constexpr int SPLIT = SHARE ? 1 : SHARES;
     constexpr int TILES = WAVES / SPLIT;                             // column tiles of a workgroup
@@ -744,6 +744,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
     // 256 channels, 3x3, V = 32, 75 %: 12.6 -> 11.8 us), and an address is one addition.
     constexpr int U = 64 / TK;
     constexpr int AHEAD = (U + PD) / U;   // batches: the last step of a batch reads entries of the batch AHEAD further on
+    static_assert(AHEAD <= 2, "the list holds two batches");
     entry_t* list = reinterpret_cast<entry_t*>(smem + TILE_BYTES) + wave * 128;
     auto fetch = [&](int q) __attribute__((always_inline)) {
         return (int)__builtin_amdgcn_raw_buffer_load_b32(col_rsrc, lane * 4 + q * 256, 0, 0);
@@ -911,7 +912,7 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         }
     }
 #pragma unroll
-    for (int q = 0; q < AHEAD && q < 2; ++q) work_out(q, c[q]);
+    for (int q = 0; q < AHEAD; ++q) work_out(q, c[q]);
     SHFLBW_WAVE_LDS_SYNC();
     if constexpr (Geom::CONV) {
 #pragma unroll
@@ -921,9 +922,6 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    SHFLBW_WAVE_LDS_SYNC();
-#pragma unroll
-    for (int q = 2; q < AHEAD; ++q) work_out(q, c[q]);
     SHFLBW_WAVE_LDS_SYNC();
     look_up(PD);
     if constexpr (SHARE) {

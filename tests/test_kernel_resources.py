@@ -60,7 +60,7 @@ def _report():
         assert job.returncode == 0, text[-2000:]
         for part in text.split("Function Name: ")[1:]:
             name = part.split()[0]
-            m = re.search(r"gather_kernelILi(\d+)ELi(\d+)ELi\d+ELi\d+E(f|DF16_)NS_\d+([A-Za-z]+)(ILb([01])EE)?ELb\dELi(\d+)EEE", name)
+            m = re.search(r"gather_kernelILi(\d+)ELi(\d+)ELi\d+E(f|DF16_)NS_\d+([A-Za-z]+)(ILb([01])EE)?ELb\dELi(\d+)EEE", name)
             if m:
                 geom = m.group(4) + ("" if m.group(6) is None else "<%s>" % ("true" if m.group(6) == "1" else "false"))
                 key = (int(m.group(1)), int(m.group(2)), int(m.group(7)), "f32" if m.group(3) == "f" else "16", geom)
