@@ -492,7 +492,8 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
     if (A->tune_kernel == 0 && slab_possible) {
         // the slab kernel streams all of X whatever the sparsity and its workgroup's groups share it: it pays where
         // enough of each chunk is used, sooner where a gathered byte serves few rows (V = 16, 32)
-        use_slab = choose_cut(cut_sizes(A, (long)N, Rows::ALIGNED, ydtype == SHFLBW_F32)) == SLAB;
+        const CutSizes sizes = cut_sizes(A, (long)N, Rows::ALIGNED, ydtype == SHFLBW_F32);
+        use_slab = slab_considered(sizes) && choose_cut(sizes) == SLAB;
     }
     if (use_slab) {
         if (A->dtype == SHFLBW_BF16) {

@@ -21,12 +21,13 @@ struct CutSizes {
     bool slab;              // the layout and the operands admit the slab kernel
     double kept;            // share of the weights that is kept
 
-    long per() const { return steps / (G > 0 ? G : 1); }
+    long per;               // steps of a group, rounded down (a division: once)
+
     long tiles() const { return (N + 63) / 64 * G; }
     int v() const { return V == 16 ? 0 : V == 32 ? 1 : V == 64 ? 2 : 3; }
 };
 
-// Whole tiles take their weights by way of the LDS from 5 k-steps (V = 16 in 128 columns: from 13): four fetches of them
+// Whole tiles take their weights by way of the LDS from 4 k-steps (in 128 columns from 5, V = 16 there from 13): four fetches of them
 // become one, at the price of a barrier every 4 or 8 steps.  Time shared / own, geometric mean over the products of
 // profiles/cut_sweep.csv with 200 workgroups or more, by steps:
 //                     up to 4   5-8    9-12   13-16   17-32   33-64   more
@@ -37,8 +38,8 @@ struct CutSizes {
 //   128 columns, V 16   1.05   1.01   1.04    .96     .99    1.03    1.00
 //               V 32    1.01    .99    .97    .97     .94     .91     .88
 //               V 64    1.00    .98    .97    .97     .95     .92     .87
-// (up to 4 steps 64 columns gain nothing that a repetition would show: the plain kernel, which holds more wavefronts)
-inline bool shares_weights(int V, bool wide, long per) { return per > (V == 16 && wide ? 12 : 4); }
+// (2048 x 1024 by 2048 at 90 %, V = 16, 4 steps: 6.03 us shared, 6.21 own)
+inline bool shares_weights(int V, bool wide, long per) { return per > (!wide ? 3 : V == 16 ? 12 : 4); }
 
 // Workgroups of the fullest of 256 CUs; beyond four rounds they even out.
 inline double rounds_of(long workgroups) { return workgroups > 1024 ? (double)workgroups / 256 : (double)((workgroups + 255) / 256); }
@@ -70,8 +71,8 @@ inline bool slab_considered(const CutSizes& s)
 inline double cut_time(const CutSizes& s, Cut cut)
 {
     struct Cost { double start, first, step, store; };
-    constexpr Cost NONE = {1e9, 0, 0, 0};   // four row blocks x four tiles of accumulators do not fit
-    constexpr Cost COSTS[4][GATHER_CUTS] = {
+    static constexpr Cost NONE = {1e9, 0, 0, 0};   // four row blocks x four tiles of accumulators do not fit
+    static constexpr Cost COSTS[4][GATHER_CUTS] = {
         {{2.91, .17, .188, .272}, {3.59, .29, .336, .369}, {3, .113, .089, .269}, {3.4, .078, .103, .381},
          {2.8, .097, .063, .111}, {2.81, .055, .066, .19}, {2.97, .054, .059, .597}},
         {{2.31, .129, .094, .688}, {2.84, .165, .164, 1.09}, {2.49, .083, .045, .66}, {2.99, .052, .06, .854},
@@ -82,8 +83,8 @@ inline double cut_time(const CutSizes& s, Cut cut)
          {2.95, .14, .09, .906}, {2.94, .079, .109, 1.32}, {2.99, .06, .13, 2.98}}};
     // us per round of workgroups: per k-step, per chunk of 64 rows of X (all are streamed, kept or not), and for the stores
     struct SlabCost { double step, chunk, store, start; };
-    constexpr SlabCost SLAB_COSTS[4] = {{.298, .215, 2.83, 1.13}, {.198, .249, 4.47, .208}, {.262, .239, 5.49, 0}, {.271, .276, 4.88, 0}};
-    const double per = (double)s.per();
+    static constexpr SlabCost SLAB_COSTS[4] = {{.298, .215, 2.83, 1.13}, {.198, .249, 4.47, .208}, {.262, .239, 5.49, 0}, {.271, .276, 4.88, 0}};
+    const double per = (double)s.per;
     if (cut == SLAB) {
         const SlabCost& c = SLAB_COSTS[s.v()];
         return c.start + slab_rounds(s) * (per * c.step + s.K / 64. * c.chunk + c.store * (s.f32 ? 1.56 : 1));
@@ -152,7 +153,7 @@ inline bool wide_by_tiles(const CutSizes& s) { return s.V <= 64 && s.steps >= 20
 // The proposal's limits are where the two cross; at 75 %, V = 32, they are within 8 % of each other.
 inline Cut choose_cut(const CutSizes& s)
 {
-    Cut proposed = cut_by_tiles(s.V, s.tiles(), s.per());
+    Cut proposed = cut_by_tiles(s.V, s.tiles(), s.per);
     if (proposed == WHOLE_64 && wide_by_tiles(s)) proposed = WHOLE_128;
     const bool slab = slab_considered(s);
     if (slab) {

@@ -16,6 +16,7 @@ inline CutSizes cut_sizes(const shflbw_matrix* A, long N, Rows rows, bool f32)
     CutSizes s;
     s.V = A->V; s.G = A->G; s.N = N; s.K = A->K;
     s.steps = A->step_ptr.empty() ? 0 : A->step_ptr.back();
+    s.per = s.steps / (s.G > 0 ? s.G : 1);
     s.rows = rows;
     s.uneven = A->uniform_steps < 0;
     s.f32 = f32;

@@ -41,7 +41,7 @@ def test_whole_tiles_exact(V, tile_n, K, N, ragged):
         _check(p, out, "<%d,%d,whole tiles" % (V, tile_n if V < 128 else 64), kernel=1, tile_n=tile_n)
         if K >= 600 and not (V == 16 and tile_n == 128 and ragged):   # V = 16: fewer than 13 steps of 32 columns of K
             assert "shared weights" in binding.last_kernel()
-        elif K < 100:
+        elif K < 100 and tile_n == 128 and V < 128:
             assert "shared weights" not in binding.last_kernel()
 
 
