@@ -27,7 +27,7 @@ struct CutSizes {
     int v() const { return V == 16 ? 0 : V == 32 ? 1 : V == 64 ? 2 : 3; }
 };
 
-// Whole tiles take their weights by way of the LDS from 4 k-steps (in 128 columns from 5, V = 16 there from 13): four fetches of them
+// Whole tiles take their weights by way of the LDS from 5 k-steps (V = 16 from 4, in 128 columns from 13): four fetches of them
 // become one, at the price of a barrier every 4 or 8 steps.  Time shared / own, geometric mean over the products of
 // profiles/cut_sweep.csv with 200 workgroups or more, by steps:
 //                     up to 4   5-8    9-12   13-16   17-32   33-64   more
@@ -38,8 +38,8 @@ struct CutSizes {
 //   128 columns, V 16   1.05   1.01   1.04    .96     .99    1.03    1.00
 //               V 32    1.01    .99    .97    .97     .94     .91     .88
 //               V 64    1.00    .98    .97    .97     .95     .92     .87
-// (2048 x 1024 by 2048 at 90 %, V = 16, 4 steps: 6.03 us shared, 6.21 own)
-inline bool shares_weights(int V, bool wide, long per) { return per > (!wide ? 3 : V == 16 ? 12 : 4); }
+// (4 steps, the most frequent number below 5: V = 16 .975, 95 % of them below 1.0; V = 64 .97, but on unaligned rows and images 1.0, up to 1.17)
+inline bool shares_weights(int V, bool wide, long per) { return per > (V != 16 ? 4 : wide ? 12 : 3); }
 
 // Workgroups of the fullest of 256 CUs; beyond four rounds they even out.
 inline double rounds_of(long workgroups) { return workgroups > 1024 ? (double)workgroups / 256 : (double)((workgroups + 255) / 256); }
