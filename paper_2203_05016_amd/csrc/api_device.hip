@@ -121,6 +121,30 @@ int dispatch_out(const shflbw_matrix* A, const Geom& geom, long N, shflbw_dtype 
 // what stream_stores calls reads
 double reads_of(const shflbw_matrix* A) { return (double)A->nnz / ((double)A->M * A->V); }
 
+// The slab kernel with a resident slab, where it applies and pays: rc is the launch's status.  yelems: from Y's start to
+// its end, in elements.
+template <class Geom>
+bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, int64_t yelems, shflbw_dtype ydtype, hipStream_t stream, int* rc)
+{
+    if (A->tune_kernel != 0 || A->tune_tile_n != 0 || A->K > RESIDENT_K) return false;
+    const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
+    const int64_t pitch = geom.ldy * ob, ybytes = yelems * ob;
+    // results' offsets: 24-bit products in 32 bits
+    if (pitch >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
+    // Streaming stores where results are rows of whole 64-byte blocks.  Else two column tiles write a block's parts, which meet
+    // in the L2 only if the stores stay there: 4096 x 1024 by 2047 16.6 us streaming, 13.8 plain, by 8191 51 and 29; with 32-bit
+    // results by 2047 30 and 17; 1x1, 512 -> 1024 channels of 14x14 10.6 and 9.5.
+    const bool whole = (pitch | (int64_t)reinterpret_cast<uintptr_t>(geom.Y)) % 64 == 0;
+    const CutSizes sizes = cut_sizes(A, N, rows, ydtype == SHFLBW_F32);
+    const ResidentPlan plan = plan_resident(sizes, whole);
+    if (!resident_pays(sizes, whole, plan)) return false;
+    Geom g = geom;
+    g.stream = whole;
+    *rc = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, N, plan, (unsigned)ybytes, ydtype, stream)
+                                  : run_resident_f16(A, g, N, plan, (unsigned)ybytes, ydtype, stream);
+    return true;
+}
+
 // `images` products over rows of P columns each (GeomRows)
 int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image, void* Y, int64_t ldy,
              int64_t y_image, int P, int images, int64_t xbytes, shflbw_dtype ydtype, hipStream_t stream)
@@ -136,6 +160,9 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
     g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob, reads_of(A), images > 1);
     g.N = (long)images * g.slots * 8;
+    int rc = SHFLBW_OK;
+    if (try_resident(A, g, g.N, images > 1 ? Rows::IMAGES : Rows::ANY, (images - 1) * y_image + (A->M - 1) * ldy + P, ydtype, stream, &rc))
+        return rc;
     return dispatch_out(A, g, g.N, ydtype, stream);
 }
 
@@ -488,6 +515,17 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
     const bool slab_possible = aligned && A->slab_ok;
     if (A->tune_kernel == 2 && !slab_possible)
         return fail(SHFLBW_ERR_BAD_OPTION, "slab kernel needs the windowed layout and aligned operands");
+    // X behind a buffer descriptor where 24-bit offset arithmetic and a 32-bit range cover it
+    const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
+    const bool described = A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64;
+    GeomLinearBuf g;
+    if (aligned && described) {
+        g.X = static_cast<const _Float16*>(X);
+        g.Y = Y;
+        g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
+        g.xbytes = (unsigned)xbytes;
+        if (try_resident(A, g, (long)N, Rows::ALIGNED, (A->M - 1) * ldy + N, ydtype, st, &rc)) return rc;
+    }
     bool use_slab = A->tune_kernel == 2;
     if (A->tune_kernel == 0 && slab_possible) {
         // the slab kernel streams all of X whatever the sparsity and its workgroup's groups share it: it pays where
@@ -506,38 +544,30 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
         return dispatch_slab<float, false>(A, X, (long)ldx, Y, (long)ldy, (long)N, st);
     }
     if (aligned) {
-        // X behind a buffer descriptor where 24-bit offset arithmetic and a 32-bit range cover it
-        const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
-        if (A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64) {
-            GeomLinearBuf g;
-            g.X = static_cast<const _Float16*>(X);
-            g.Y = Y;
-            g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
-            g.xbytes = (unsigned)xbytes;
+        if (described) {
             const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
             g.stream = stream_stores(Y, ldy * ob, ob, 2.0 * A->K * N, (double)ob * A->M * N, reads_of(A));
             return dispatch_out(A, g, (long)N, ydtype, st);
         }
-        GeomLinear<true> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
-        return dispatch_out(A, g, (long)N, ydtype, st);
+        GeomLinear<true> wide{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
+        return dispatch_out(A, wide, (long)N, ydtype, st);
     }
     // rows of no particular alignment: whole 16-byte accesses where 24-bit offset arithmetic and a
     // 32-bit range cover X
-    const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
-    if (A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64) {
+    if (described) {
         if (N >= 8) return run_rows(A, X, ldx, 0, Y, ldy, 0, (int)N, 1, xbytes, ydtype, st);
         if (xbytes >= 16) {
-            GeomNarrow g;
-            g.X = static_cast<const _Float16*>(X);
-            g.Y = Y;
-            g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
-            g.xbytes = (unsigned)xbytes;
-            g.stream = 0;
-            return dispatch_out(A, g, (long)N, ydtype, st);
+            GeomNarrow narrow;
+            narrow.X = static_cast<const _Float16*>(X);
+            narrow.Y = Y;
+            narrow.ldx = (long)ldx; narrow.ldy = (long)ldy; narrow.N = (long)N;
+            narrow.xbytes = (unsigned)xbytes;
+            narrow.stream = 0;
+            return dispatch_out(A, narrow, (long)N, ydtype, st);
         }
     }
-    GeomLinear<false> g{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
-    return dispatch_out(A, g, (long)N, ydtype, st);
+    GeomLinear<false> any{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
+    return dispatch_out(A, any, (long)N, ydtype, st);
 }
 
 int shflbw_spmm_unbound(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int64_t ldy,

@@ -1,6 +1,8 @@
 // Which kernel a linear layer takes and how its work is cut, from sizes alone.  Host code without HIP.
 #pragma once
 
+#include <cmath>
+
 namespace shflbw {
 
 // A workgroup's tiles: four of 64 or of 128 columns, one wavefront each; one of 128 columns whose k-steps 2 or 4 wavefronts
@@ -169,6 +171,74 @@ inline Cut choose_cut(const CutSizes& s)
         if (t < least) { least = t; best = (Cut)c; }
     }
     return best;
+}
+
+// The slab kernel with a resident slab (resident_kernel.hip): 64 columns of X with all their rows stay in a workgroup's LDS,
+// `parts` workgroups of `waves` wavefronts share a column tile, each with a share of the row groups.
+struct ResidentPlan { int parts = 0, waves = 0; double time = 1e9; };
+
+// K rows of 128 bytes, a row of zeros and a counter fill the LDS of a CU; half of it, and 8 wavefronts, leave room for a
+// second workgroup, whose products hide the copy of this one's slab (K = 512, 4096 rows by 8192, V = 32: 18.1 us with 16
+// wavefronts, 17.4 with 8; K = 256 16.8 and 15.1).  Two row blocks (V >= 64) need the registers of 16 wavefronts for 8.
+constexpr int RESIDENT_K = 1278, RESIDENT_K_HALF = 638;
+inline int resident_waves(int V, int K) { return V >= 64 || K <= RESIDENT_K_HALF ? 8 : 16; }
+
+// Estimated time, us, in `parts` shares: a round of workgroups takes `copy` per row of the slab (more where rows are not
+// aligned), then per item (a group; V = 128: half of one) `step` per k-step and `store` for its results, or the time of one
+// wavefront's items, `chain` per step, where there are few of them; `start` once, `round` per round.  k-steps come in fours.
+// whole: results are rows of whole 64-byte blocks (else these are written in parts by two column tiles).
+// Fitted to 11 000 times of 3200 random layers (V 16 to 128, K 64 to 1278, 256 to 16384 columns, unpruned to 95 %), which it meets within 12 %.
+inline double resident_time(const CutSizes& s, bool whole, int parts, int waves)
+{
+    struct Cost { double start, copy, step, store, chain, round, parted; };
+    static constexpr Cost COSTS[4] = {{2.32, .00182, .019, .0328, .108, .904, 1.99}, {2.26, .00156, .0159, .0796, .0828, 1.21, 1.53},
+                                      {2.74, .00207, .0265, .228, .0961, 1.03, 1.32}, {3.02, .00225, .0277, .213, .103, .923, 1.32}};
+    const Cost& c = COSTS[s.v()];
+    const long items = s.G * (s.V == 128 ? 2 : 1), per = (items + parts - 1) / parts;
+    const long workgroups = (s.N + 63) / 64 * ((items + per - 1) / per);
+    const int at_once = waves == 8 && s.V < 64 ? 2 : 1;               // workgroups of a CU
+    const long cus = 256 * at_once;
+    const double rounds = workgroups > 4 * cus ? (double)workgroups / cus : (double)((workgroups + cus - 1) / cus);
+    const double live = at_once == 2 && workgroups > 256 ? 2 : 1;
+    const double steps = (double)((s.per + 3) / 4 * 4) * (s.uneven ? 1.09 : 1);
+    const double work = per * (steps * c.step + c.store * (s.f32 ? 2.4 : 1) * (whole ? 1 : c.parted)) * live;
+    const double chain = (double)((per + waves - 1) / waves) * steps * c.chain;
+    const double longer = work > chain ? work : chain, ratio = (work + chain - longer) / longer, r2 = ratio * ratio;
+    return c.start + rounds * (s.K * c.copy * (s.rows == Rows::ALIGNED ? 1 : 1.4) * live + longer * std::sqrt(std::sqrt(1 + r2 * r2)) + c.round);
+}
+
+// The number of shares with the least estimate: whole rounds of 256 workgroups.  (Twice 128 shares of half a round each
+// copy every slab twice; 4096 x 1024 by 8192, V = 32 at 75 %: 128 / 256 / 512 workgroups 35.7 / 26.8 / 30.2 us.)
+inline ResidentPlan plan_resident(const CutSizes& s, bool whole)
+{
+    ResidentPlan best;
+    const long tiles = (s.N + 63) / 64, items = s.G * (s.V == 128 ? 2 : 1);
+    if (s.K > RESIDENT_K || s.G < 4 || tiles * (items < 1024 ? items : 1024) >= (1L << 19)) return best;
+    const int waves = resident_waves(s.V, s.K);
+    long last = 0;
+    for (long rounds = 1; rounds <= 4; ++rounds) {
+        long parts = 256 * rounds / tiles;
+        parts = parts < 1 ? 1 : parts > items ? items : parts;
+        if (parts == last) continue;
+        last = parts;
+        const double t = resident_time(s, whole, (int)parts, waves);
+        if (t < best.time) { best.time = t; best.parts = (int)parts; best.waves = waves; }
+    }
+    return best;
+}
+
+// Taken where its estimate is below the best cut's.  That one is on average 14 % low where results are no whole 64-byte blocks
+// (4 to 10 % else; 4 % high for images of whole blocks), and least sure where steps or columns are few: hence the margins.  Over those 3200
+// layers the choice takes 0.951 of the time of the other kernels (geometric mean over all, 615 take this one; the best of both
+// 0.919), 22 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other kernels / resident: by 8192
+// 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047 16.3 / 12.2 to 13.8, by 2048
+// 10.1 / 9.6 to 10.7; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.8; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
+// 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
+inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
+{
+    if (plan.parts <= 0) return false;
+    const double margin = s.per <= 4 || s.N < 1024 ? .85 : !whole ? 1 : s.rows == Rows::IMAGES ? .88 : .95;
+    return plan.time < margin * cut_time(s, choose_cut(s));
 }
 
 }  // namespace shflbw

@@ -218,6 +218,8 @@ struct GeomLinearBuf {
     {
         if (n < N) store_run<STREAM, CNT>(static_cast<OutT*>(Y) + (long)row * ldy + n, vals);
     }
+    // where column n of a result row lies, elements from the row's start (n < N)
+    __device__ __forceinline__ unsigned out_col(long n) const { return (unsigned)n; }
 };
 
 // Rows of P contiguous columns with no particular alignment, in `images` matrices (1 for a
@@ -275,6 +277,12 @@ struct GeomRows : GeomLinearBuf {
             OutT* p = static_cast<OutT*>(Y) + (long)img * y_image + (long)row * ldy + c + ((unsigned)n & 7u);
             store_run<STREAM, CNT>(p, vals);
         }
+    }
+    __device__ __forceinline__ unsigned out_col(long n) const
+    {
+        unsigned img, c;
+        place(n, img, c);
+        return img * (unsigned)y_image + c + ((unsigned)n & 7u);
     }
 };
 

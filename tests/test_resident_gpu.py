@@ -1,0 +1,117 @@
+"""The slab kernel with a resident slab, as the automatic choice launches it: row groups that end at any step of four and at any
+of a load's sixteen, more of them than wavefronts and fewer, unequal ones, groups without columns; columns at and beside the edges of
+a tile, rows of no alignment and rows of images; the longest reduction.  Small integers: every sum is exact in 32 bits, and the
+comparison with the oracle is bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import c_oracle
+from paper_2203_05016_amd import binding, synth
+from gpu_util import announce, run_spmm, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _rounded(want, dtype):
+    import torch
+    return want if dtype == "float32" else torch.from_numpy(want).to(getattr(torch, dtype)).double().numpy()
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("V,G,K,N,sparsity,ragged", [
+    (16, 256, 1024, 4096, 0.75, False),
+    (16, 128, 1278, 3001, 0.70, True),     # the longest reduction; rows of no alignment, the last tile of 57 columns
+    (16, 200, 300, 8160, 0.40, True),      # 8 wavefronts; the last tile of 32 columns
+    (32, 128, 1024, 8192, 0.75, False),
+    (32, 128, 1000, 8104, 0.75, True),     # rows of no whole blocks, the last tile of 40 columns
+    (32, 96, 1278, 4097, 0.50, False),     # the last slot one column on from the one before
+    (32, 100, 638, 6007, 0.50, True),      # the longest for 8 wavefronts
+    (32, 100, 639, 6007, 0.50, True),      # the shortest for 16
+    (64, 64, 1024, 8191, 0.50, True),
+    (64, 64, 1278, 8189, 0.50, False),
+    (128, 33, 1024, 8191, 0.30, True),     # two items of a group, an odd number of groups
+])
+def test_resident_slab_exact(V, G, K, N, sparsity, ragged, fmt):
+    announce("resident slab", V, G, K, N, ragged, fmt)
+    p = synth.make_spmm(G * V, K, N, V, sparsity, seed=1701 + N + V, integer=True, ragged=ragged, fmt=fmt)
+    want, _ = c_oracle.spmm(p.W, p.mask, p.X)
+    for out in ("float32", "bfloat16" if fmt == "bf16" else "float16"):
+        got = run_spmm(p, out_dtype=out).astype(np.float64)
+        assert "resident in %d wavefronts" % (8 if V >= 64 or K <= 638 else 16) in binding.last_kernel(), binding.last_kernel()
+        assert np.array_equal(got, _rounded(want, out)), np.argwhere(got != _rounded(want, out))[:4]
+
+
+def test_resident_slab_writes_its_window_only():
+    """Padded leading dimensions and a base of no alignment: nothing outside the results is written (run_spmm looks)."""
+    announce("resident slab, window")
+    p = synth.make_spmm(128 * 32, 1024, 4090, 32, 0.75, seed=1711, integer=True)
+    want, _ = c_oracle.spmm(p.W, p.mask, p.X)
+    got = run_spmm(p, out_dtype="float32", pad_ld=13, offset=3)
+    assert "resident" in binding.last_kernel(), binding.last_kernel()
+    assert np.array_equal(got.astype(np.float64), want)
+
+
+@pytest.mark.parametrize("V,batch,C,H,W,M", [(16, 32, 512, 7, 7, 2048), (32, 33, 640, 13, 13, 1024), (16, 32, 256, 14, 14, 2048)])
+def test_resident_slab_images_exact(V, batch, C, H, W, M):
+    """1x1 convolutions: slots that overlap at the end of every image."""
+    import torch
+    announce("resident slab, images", V, batch, C, H, W)
+    p = synth.make_conv(batch, C, H, W, M, 1, 1, V, 0.5, seed=1721 + V, integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (1, 1), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    for dt in (torch.float16, torch.float32):
+        out = torch.full((batch, M, H, W), float("nan"), dtype=dt, device="cuda:0")
+        A.conv2d(to_device(p.conv["input"]), 1, 1, out=out)
+        torch.cuda.synchronize()
+        assert "resident" in binding.last_kernel(), binding.last_kernel()
+        assert np.array_equal(to_host(out).astype(np.float64), _rounded(want, "float16" if dt == torch.float16 else "float32"))
+
+
+def test_resident_slab_keeps_infinities_apart():
+    """A group of infinite weights and a row of X that no group keeps full of NaN: padded slots and steps beyond a group's end
+    multiply zeros by zeros."""
+    import torch
+    announce("resident slab, infinities")
+    V, G, K, N = 32, 128, 1024, 4096
+    p = synth.make_spmm(G * V, K, N, V, 0.72, seed=1731, integer=True, ragged=True)
+    W, X, mask = p.W.copy(), p.X.copy(), p.mask.copy()
+    rows = p.perm[V:2 * V]
+    W[np.ix_(rows, np.flatnonzero(mask[rows[0]]))] = np.float16(np.inf)
+    X[0] = np.float16(np.nan)
+    mask[:, 0] = 0
+    want, _ = c_oracle.spmm(np.where(np.isinf(W), 0, W).astype(np.float16), mask, np.nan_to_num(X))
+    A = binding.compress(W, mask, p.perm, V).bind_device("cuda:0")
+    Y = torch.empty((G * V, N), dtype=torch.float32, device="cuda:0")
+    A.spmm(torch.from_numpy(X).to("cuda:0"), Y)
+    torch.cuda.synchronize()
+    assert "resident" in binding.last_kernel(), binding.last_kernel()
+    others = np.setdiff1d(np.arange(G * V), rows)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64)[others], want[others])
+
+
+def test_resident_slab_without_kept_columns_and_under_capture():
+    import torch
+    announce("resident slab, empty groups and a graph")
+    V, G, K, N = 32, 128, 1024, 4096
+    p = synth.make_spmm(G * V, K, N, V, 0.6, seed=1741, integer=True)
+    mask = p.mask.copy()
+    for g in (0, 5, 17, 127):
+        mask[p.perm[g * V:(g + 1) * V]] = 0
+    want, _ = c_oracle.spmm(p.W, mask, p.X)
+    A = binding.compress(p.W, mask, p.perm, V).bind_device("cuda:0")
+    X = to_device(p.X)
+    Y = torch.full((G * V, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    A.spmm(X, Y)
+    torch.cuda.synchronize()
+    assert "resident" in binding.last_kernel(), binding.last_kernel()
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), want)
+    eager = Y.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        A.spmm(X, Y)
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager)
+        A.spmm(X, Y)
