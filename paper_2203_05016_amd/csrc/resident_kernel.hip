@@ -94,13 +94,12 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
     constexpr bool F32 = sizeof(OutT) == 4;
     constexpr int ROWS_E = SMALL ? 16 : 32;                  // rows of a row block
     // (rows one step ahead instead of two: by 2047 15.0 us instead of 12.2, by 4096 16.6 instead of 14.8; three gained nothing)
-    constexpr int QUAD = 4, BATCH = 16, AHEAD = 2;                      // steps of a pass through the loop; whose indices are loaded at a time; that rows are read ahead
+    constexpr int QUAD = 4, BATCH = 16, AHEAD = 2;       // steps of a pass through the loop; whose indices are loaded at a time; that rows are read ahead
     extern __shared__ __attribute__((aligned(128))) char slab[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned w = (blockIdx.x & 7) * (unsigned)a.per_xcd + (blockIdx.x >> 3);
-    if (w >= (unsigned)a.total) return;                      // uniform for the workgroup
     const int tile = (int)(((unsigned long long)w * a.m_parts) >> 40), part = (int)w - tile * a.parts;
     const int g_lo = part * a.per_part, g_hi = g_lo + a.per_part < a.A.G * IPG ? g_lo + a.per_part : a.A.G * IPG;
     const long n0 = (long)tile * RESIDENT_TN;
@@ -116,8 +115,10 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
     for (int i = 0; i < STAGES; ++i) {
         int unused = 0;
         const int r = srow + i * STAGE_ROWS;
-        if (i * STAGE_ROWS <= K) staged[i] = geom.load8(geom.entry(r, r < K), unused);
+        if (i * STAGE_ROWS + wave * 8 < K) staged[i] = geom.load8(geom.entry(r, r < K), unused);   // uniform for the wavefront
     }
+    // (after the loads: before them it would be a wait for the arguments of its own; tiles beyond the last read nothing)
+    if (w >= (unsigned)a.total) return;                      // uniform for the workgroup
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- the stream of k-steps, four at a time, of this wavefront's groups
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
 #pragma unroll
     for (int i = 0; i < STAGES; ++i) {
         const int r = srow + i * STAGE_ROWS;
-        if (i * STAGE_ROWS <= K && r <= K) {                  // row K: zeros
+        if (i * STAGE_ROWS + wave * 8 < K && r < K) {
             run_t v = staged[i];
             const int t = turn(r);
             if constexpr (SMALL) {
@@ -217,6 +218,7 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
             *reinterpret_cast<run_t*>(slab + r * RESIDENT_ROW + ((sunit * 16) ^ (t & ~15))) = v;
         }
     }
+    if (tid < 8) *reinterpret_cast<run_t*>(slab + K * RESIDENT_ROW + tid * 16) = run_t{0, 0, 0, 0};
     if (tid == 0) *claimed = g_lo + 2 * WAVES;
     // byte of the row that this lane addresses for instruction tile 0.  The operand's columns are any that
     // suit the write-back, in fours: an accumulator quad of a lane then continues the one before it.
