@@ -24,7 +24,8 @@
 // tokens each),
 // and the transposed rows are gathered from LDS columns, two neighbouring
 // features per lane (row pitch chosen so that the 64 four-byte reads of a
-// wavefront fall into 64 different banks).
+// wavefront fall into 64 different banks).  Rows too wide for that go through registers, 1024 features
+// at a time; few tokens have their features shared by several workgroups (layernorm_transpose_few_kernel).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -56,6 +57,12 @@ struct LnArgs {
     int stream;             // streaming stores, see ln_store
     int blocks_per_wg;      // 64-feature blocks one workgroup transposes (grid.y covers K)
     int slices_per_wg;      // register-resident variant: 1024-feature slices one workgroup stores (grid.y covers K)
+};
+
+// the kernel for few tokens
+struct LnFew {
+    int blocks, slice, pitch;   // token blocks; features of a slice; LDS pitch of a token's slice, 16-bit units
+    int per_xcd, total;         // workgroups of an XCD, and with work
 };
 
 // Streaming where the row segments of 64 (128) bytes are whole 64-byte blocks of memory; plain where
@@ -663,6 +670,131 @@ __global__ __launch_bounds__(1024) void layernorm_transpose_register_kernel(LnAr
     }
 }
 
+// Few tokens.  What bounds it is one chain of latencies, launch -> rows -> statistics -> rows of the output, and how long a CU
+// takes over its part of each: with 32 tokens and all their features to a workgroup, most CUs had none and the others 2.4 us
+// per 1024 features.  Here a workgroup reads the rows of TOK tokens (16 or 8: 64 KB at 2048 or 4096 features) once, into the
+// registers of its sixteen wavefronts, takes the statistics, and passes on only a slice of the features (few.slice of them, a multiple
+// of 16): every slice of a token block is another workgroup's, which reads the rows for itself, mostly from the L2.  Output rows get 32 or 16
+// bytes per workgroup, half the write rate or less, which is why many tokens do not come here (the rule is where it is launched).
+template <bool BF, int TOK>
+__global__ __launch_bounds__(1024) void layernorm_transpose_few_kernel(LnArgs a, LnFew few)
+{
+    static_assert(TOK == 16 || TOK == 8, "whole tokens per wavefront, or two wavefronts per token");
+    constexpr int WPT = 16 / TOK;                            // wavefronts of a token, which take its runs of 512 features in turn
+    constexpr int RUNS = TOK == 16 ? 4 : 16;                 // of a wavefront, at most: 2048 features of 16 tokens, 16 384 of 8
+    constexpr int CH = TOK / 8, FP = 64 / CH;
+    extern __shared__ __attribute__((aligned(16))) char ln_smem[];
+    const int P = few.pitch, Q = P / 2;
+    uint16_t* xs = reinterpret_cast<uint16_t*>(ln_smem);     // [TOK][P]
+    float* st_mean = reinterpret_cast<float*>(ln_smem + (size_t)TOK * P * 2);   // [TOK]
+    float* st_rstd = st_mean + TOK;                          // [TOK]
+    float* st_part = st_rstd + TOK;                          // [2][16]: sums of a wavefront, where a token has two
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // an XCD takes neighbouring token blocks of a slice: the parts of a 64-byte block that they write meet in its L2
+    const unsigned w = (blockIdx.x & 7) * (unsigned)few.per_xcd + (blockIdx.x >> 3);
+    if (w >= (unsigned)few.total) return;                    // uniform for the workgroup
+    const int sl = (int)(w / (unsigned)few.blocks);
+    const long n0 = (long)((int)w - sl * few.blocks) * TOK;
+    const int K = a.K, k0 = sl * few.slice, k1 = k0 + few.slice < K ? k0 + few.slice : K;
+    const int token = wave / WPT, run0 = wave % WPT;
+
+    // what does not exist loads the last token or feature (neither summed nor stored)
+    const long nt = n0 + token;
+    const uint16_t* row = a.x + (nt < a.N ? nt : a.N - 1) * a.ldx;
+    const uint16_t first = row[0];
+    ln_ushort8 v[RUNS];
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) {
+        const int kc = (j * WPT + run0) * 512 + lane * 8;
+        if ((j * WPT + run0) * 512 < K)                      // uniform for the wavefront
+            v[j] = *reinterpret_cast<const ln_ushort8*>(row + (kc < K ? kc : K - 8));
+    }
+    // the outputs' place, and gamma and beta of this lane's first features
+    const int kk2 = lane / CH, tchunk = lane % CH;
+    const long n = n0 + tchunk * 8;
+    const unsigned one2 = BF ? 0x3f803f80u : 0x3c003c00u;    // 1.0 twice, for an absent gamma
+    auto feature = [&](int pass) __attribute__((always_inline)) { return (pass * 16 + wave) * 2 * FP + 2 * kk2; };
+    auto gamma_of = [&](int k) __attribute__((always_inline)) { return a.gamma ? *reinterpret_cast<const unsigned*>(a.gamma + (k < K ? k : K - 8)) : one2; };
+    auto beta_of = [&](int k) __attribute__((always_inline)) { return a.beta ? *reinterpret_cast<const unsigned*>(a.beta + (k < K ? k : K - 8)) : 0u; };
+    unsigned gw = gamma_of(k0 + feature(0)), bw = beta_of(k0 + feature(0));
+
+    float s1 = 0.f, s2 = 0.f;
+    const float pivot = ln_widen<BF>(first);
+#pragma unroll
+    for (int j = 0; j < RUNS; ++j) {
+        const int kc = (j * WPT + run0) * 512 + lane * 8;
+        if (kc < K) {
+            const ln_ushort8& c = v[j];
+            const unsigned p[4] = {(unsigned)c[0] | ((unsigned)c[1] << 16), (unsigned)c[2] | ((unsigned)c[3] << 16),
+                                   (unsigned)c[4] | ((unsigned)c[5] << 16), (unsigned)c[6] | ((unsigned)c[7] << 16)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float d0, d1;
+                ln_add_pair<BF>(p[e], -pivot, d0, d1);
+                s1 += d0;
+                s2 += d0 * d0;
+                s1 += d1;
+                s2 += d1 * d1;
+            }
+            if (kc >= k0 && kc < k1) {
+                uint2* dst = reinterpret_cast<uint2*>(xs + token * P + kc - k0);
+                dst[0] = uint2{p[0], p[1]};
+                dst[1] = uint2{p[2], p[3]};
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        s1 += __shfl_xor(s1, off, 64);
+        s2 += __shfl_xor(s2, off, 64);
+    }
+    if constexpr (WPT == 2) {
+        if (lane == 0) { st_part[wave] = s1; st_part[16 + wave] = s2; }
+        __syncthreads();
+        s1 += st_part[wave ^ 1];
+        s2 += st_part[16 + (wave ^ 1)];
+    }
+    if (lane == 0 && run0 == 0) {
+        const float m = s1 / (float)K;
+        float var = s2 / (float)K - m * m;
+        var = var > 0.f ? var : 0.f;
+        st_mean[token] = pivot + m;
+        st_rstd[token] = 1.0f / __builtin_sqrtf(var + a.eps);
+    }
+    __syncthreads();
+    if (n >= a.N) return;
+    float mean[8], rstd[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { mean[e] = st_mean[tchunk * 8 + e]; rstd[e] = st_rstd[tchunk * 8 + e]; }
+    const unsigned* xw = reinterpret_cast<const unsigned*>(xs) + tchunk * 8 * Q;
+    for (int pass = 0;; ++pass) {
+        const int kl = feature(pass);
+        if (k0 + kl >= k1) break;
+        unsigned x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = xw[e * Q + (kl >> 1)];
+        const unsigned gn = gamma_of(k0 + feature(pass + 1)), bn = beta_of(k0 + feature(pass + 1));
+        float g0, g1, b0, b1;
+        ln_add_pair<BF>(gw, 0.f, g0, g1);
+        ln_add_pair<BF>(bw, 0.f, b0, b1);
+        ln_ushort8 o0, o1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float lo, hi;
+            ln_add_pair<BF>(x[e], -mean[e], lo, hi);
+            o0[e] = ln_narrow<BF>(lo * rstd[e] * g0 + b0);
+            o1[e] = ln_narrow<BF>(hi * rstd[e] * g1 + b1);
+        }
+        uint16_t* dst = a.out + (long)(k0 + kl) * a.ldo + n;
+        ln_store<false>(dst, o0);
+        ln_store<false>(dst + a.ldo, o1);
+        gw = gn;
+        bw = bn;
+    }
+}
+
 }  // namespace
 }  // namespace shflbw
 
@@ -695,6 +827,43 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
     a.normalize = normalize ? 1 : 0;
     a.stream = ((uintptr_t)(ldo * 2) | reinterpret_cast<uintptr_t>(out)) % 64 == 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // Few tokens: 16 at a time (up to 2048 features) or 8, the features shared by about 128 workgroups (up to 256 for more
+    // than 64 blocks of 8; twice as many cost what their reads of the same rows take).  us by the other kernels / this one: 64 tokens of
+    // 256 features 4.1 / 3.7, 1024 5.5 / 3.9, 2048 7.8 / 4.5, 4096 8.3 / 5.1, 16 384 16.5 / 9.4; 552 tokens of 1024
+    // 5.9 / 4.3, 2048 8.3 / 5.3, 3584 10.2 / 6.8, 8192 14.5 / 12.3, 16 384 25.0 / 19.5; 2048 of 1024 5.9 / 5.2, of 2048
+    // 8.3 / 7.3; 4096 of 1024 6.6 / 6.2; but 4096 of 1600 8.3 / 9.2, 1024 of 4096 8.7 / 9.3, of 8192 13.3 / 15.5, of 16 384 23.3 / 27.3.
+    if (a.normalize && K <= 16384 && N <= (K <= 1024 ? 4096 : K <= 2048 ? 2048 : 768)) {
+        const int few_tok = K <= 2048 ? 16 : 8;
+        LnFew f;
+        f.blocks = (int)((N + few_tok - 1) / few_tok);
+        int shares = (few_tok == 8 && f.blocks > 64 ? 256 : 128) / f.blocks;
+        if (shares > K / 64) shares = K / 64;
+        if (shares < 1) shares = 1;
+        f.slice = ((K + shares - 1) / shares + 15) / 16 * 16;
+        // (pitch / 2) mod 8, as in the LDS-resident kernel: 64 words of a read in 64 banks
+        f.pitch = f.slice + (few_tok == 16 ? 8 : 0);
+        f.total = f.blocks * ((K + f.slice - 1) / f.slice);
+        f.per_xcd = (f.total + 7) / 8;
+        const size_t bytes = (size_t)few_tok * f.pitch * 2 + 2 * few_tok * 4 + 2 * 16 * 4;
+        typedef void (*few_fn)(LnArgs, LnFew);
+        static const few_fn ftable[4] = {&layernorm_transpose_few_kernel<false, 16>, &layernorm_transpose_few_kernel<false, 8>,
+                                         &layernorm_transpose_few_kernel<true, 16>, &layernorm_transpose_few_kernel<true, 8>};
+        const int which = (dtype == SHFLBW_BF16 ? 2 : 0) + (few_tok == 8 ? 1 : 0);
+        const few_fn fn = ftable[which];
+        static thread_local int raised_few[4] = {-1, -1, -1, -1};
+        int dev = 0;
+        hipError_t ea = hipGetDevice(&dev);
+        if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(ea));
+        if (raised_few[which] != dev) {
+            ea = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (ea != hipSuccess) return fail(SHFLBW_ERR_HIP, "hipFuncSetAttribute: %s", hipGetErrorString(ea));
+            raised_few[which] = dev;
+        }
+        hipLaunchKernelGGL(fn, dim3(8u * (unsigned)f.per_xcd), dim3(1024), bytes, st, a, f);
+        hipError_t el = hipGetLastError();
+        if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(el));
+        return SHFLBW_OK;
+    }
     // LDS-resident variant when a block of tokens with all its features fits
     auto resident_bytes = [&](int tok, int& pitch) {
         const int want = tok == 32 ? 2 : 1;             // (pitch / 2) mod 8, see the kernel
@@ -758,7 +927,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         // statistics for itself (its reads of the other slices come from the L2), as long as there is at
         // most one workgroup per CU.  One workgroup per 32 tokens leaves most CUs idle: 848 tokens of 5800
         // features 22.5 -> 16.1 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
-        // 15.0 -> 10.1, 64 of 16 384 51 -> 17.
+        // 15.0 -> 10.1.  (Up to 768 tokens do not come here with a LayerNorm, above.)
         const int slices = (K + 1023) / 1024;
         int shares = rwgs > 0 && rwgs < 256 ? (int)(256 / rwgs) : 1;
         if (shares > slices) shares = slices;
