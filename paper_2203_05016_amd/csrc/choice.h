@@ -227,17 +227,19 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole)
     return best;
 }
 
-// Taken where its estimate is below the best cut's.  That one is on average 14 % low where results are no whole 64-byte blocks
-// (4 to 10 % else; 4 % high for images of whole blocks), and least sure where steps or columns are few: hence the margins.  Over those 3200
-// layers the choice takes 0.951 of the time of the other kernels (geometric mean over all, 615 take this one; the best of both
-// 0.919), 22 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other kernels / resident: by 8192
-// 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047 16.3 / 12.2 to 13.8, by 2048
-// 10.1 / 9.6 to 10.7; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.8; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
+// Taken where its estimate is below the best cut's, which is 5 to 20 % low by V and by how results lie in memory, and least
+// sure where steps or columns are few: hence the margins.  Over those 3200 layers the choice takes 0.943 of the time of the other kernels
+// (geometric mean over all, 800 take this one; the best of both 0.924), 30 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other
+// kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
+// 16.3 / 12.1 to 15.2; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
 inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
-    const double margin = s.per <= 4 || s.N < 1024 ? .85 : !whole ? 1 : s.rows == Rows::IMAGES ? .88 : .95;
+    // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few, images
+    static constexpr double MARGINS[4][5] = {{1.04, 1.04, .96, .9, 1.02}, {1.05, .92, .9, .88, .94}, {1.08, .92, 1.02, .86, .88}, {.94, .85, 1.15, .85, .85}};
+    const int few = s.per <= 4 || s.N < 1024 ? 1 : 0;
+    const double margin = MARGINS[s.v()][s.rows == Rows::IMAGES ? 4 : (whole ? 2 : 0) + few];
     return plan.time < margin * cut_time(s, choose_cut(s));
 }
 
