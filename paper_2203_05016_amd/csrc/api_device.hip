@@ -128,7 +128,7 @@ bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, i
 {
     if (A->tune_kernel != 0 || A->tune_tile_n != 0 || A->K > RESIDENT_K) return false;
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
-    const int64_t pitch = geom.ldy * ob, ybytes = yelems * ob;
+    const int64_t pitch = geom.out_pitch() * ob, ybytes = yelems * ob;
     // results' offsets: 24-bit products in 32 bits
     if (pitch >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
     // Streaming stores where results are rows of whole 64-byte blocks.  Else two column tiles write a block's parts, which meet
@@ -136,7 +136,7 @@ bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, i
     // results by 2047 30 and 17; 1x1, 512 -> 1024 channels of 14x14 10.6 and 9.5.
     const bool whole = (pitch | (int64_t)reinterpret_cast<uintptr_t>(geom.Y)) % 64 == 0;
     const CutSizes sizes = cut_sizes(A, N, rows, ydtype == SHFLBW_F32);
-    const ResidentPlan plan = plan_resident(sizes, whole);
+    const ResidentPlan plan = plan_resident(sizes, whole, rows == Rows::ALIGNED ? 1 : RESIDENT_COPY_UNALIGNED);
     if (!resident_pays(sizes, whole, plan)) return false;
     Geom g = geom;
     g.stream = whole;
@@ -704,6 +704,28 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         return layout == SHFLBW_CHWN ? gather_runs(chwn, status) : gather_runs(nchw, status);
     };
     int status = SHFLBW_OK;
+    // the unfolded matrix resident in the LDS, 64 columns of it per workgroup
+    const auto try_resident_runs = [&](auto& g) {
+        constexpr bool CHWN = std::is_same<std::decay_t<decltype(g)>, GeomConvRuns<true>>::value;
+        if (!fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, 2 * (int64_t)batch * C_in * H * W, 2))
+            return false;
+        const int64_t ybytes = 2 * (int64_t)A->M * N;
+        if (g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
+        // (stores: 4 to 7 % either way, as for linear layers)
+        const bool whole = ((CHWN ? batch : Wo) * 2 | (int64_t)reinterpret_cast<uintptr_t>(out)) % 64 == 0;
+        const CutSizes sizes = cut_sizes(A, g.N, Rows::ANY, false);
+        const ResidentPlan plan = plan_resident(sizes, whole, CHWN ? RESIDENT_COPY_CHWN : RESIDENT_COPY_NCHW);
+        if (!resident_conv_pays(sizes, CHWN, runs_pay, plan)) return false;
+        g.stream = whole;
+        status = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, g.N, plan, (unsigned)ybytes, ydtype, st)
+                                         : run_resident_f16(A, g, g.N, plan, (unsigned)ybytes, ydtype, st);
+        return true;
+    };
+    if (A->tune_kernel == 0 && A->tune_tile_n == 0 && A->V <= 32 && A->K <= RESIDENT_K && ydtype != SHFLBW_F32) {
+        GeomConvRuns<true> chwn;
+        GeomConvRuns<false> nchw;
+        if (layout == SHFLBW_CHWN ? try_resident_runs(chwn) : try_resident_runs(nchw)) return status;
+    }
     if ((A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) && try_runs(&status))
         return status;
     if (A->tune_kernel != 1 && A->tune_kernel != 3) {

@@ -183,12 +183,12 @@ struct ResidentPlan { int parts = 0, waves = 0; double time = 1e9; };
 constexpr int RESIDENT_K = 1278, RESIDENT_K_HALF = 638;
 inline int resident_waves(int V, int K) { return V >= 64 || K <= RESIDENT_K_HALF ? 8 : 16; }
 
-// Estimated time, us, in `parts` shares: a round of workgroups takes `copy` per row of the slab (more where rows are not
-// aligned), then per item (a group; V = 128: half of one) `step` per k-step and `store` for its results, or the time of one
+// Estimated time, us, in `parts` shares: a round of workgroups takes Cost::copy per row of the slab (`copy` times it for other
+// than aligned rows), then per item (a group; V = 128: half of one) `step` per k-step and `store` for its results, or the time of one
 // wavefront's items, `chain` per step, where there are few of them; `start` once, `round` per round.  k-steps come in fours.
 // whole: results are rows of whole 64-byte blocks (else these are written in parts by two column tiles).
 // Fitted to 11 000 times of 3200 random layers (V 16 to 128, K 64 to 1278, 256 to 16384 columns, unpruned to 95 %), which it meets within 12 %.
-inline double resident_time(const CutSizes& s, bool whole, int parts, int waves)
+inline double resident_time(const CutSizes& s, bool whole, int parts, int waves, double copy)
 {
     struct Cost { double start, copy, step, store, chain, round, parted; };
     static constexpr Cost COSTS[4] = {{2.32, .00182, .019, .0328, .108, .904, 1.99}, {2.26, .00156, .0159, .0796, .0828, 1.21, 1.53},
@@ -204,12 +204,12 @@ inline double resident_time(const CutSizes& s, bool whole, int parts, int waves)
     const double work = per * (steps * c.step + c.store * (s.f32 ? 2.4 : 1) * (whole ? 1 : c.parted)) * live;
     const double chain = (double)((per + waves - 1) / waves) * steps * c.chain;
     const double longer = work > chain ? work : chain, ratio = (work + chain - longer) / longer, r2 = ratio * ratio;
-    return c.start + rounds * (s.K * c.copy * (s.rows == Rows::ALIGNED ? 1 : 1.4) * live + longer * std::sqrt(std::sqrt(1 + r2 * r2)) + c.round);
+    return c.start + rounds * (s.K * c.copy * copy * live + longer * std::sqrt(std::sqrt(1 + r2 * r2)) + c.round);
 }
 
 // The number of shares with the least estimate: whole rounds of 256 workgroups.  (Twice 128 shares of half a round each
 // copy every slab twice; 4096 x 1024 by 8192, V = 32 at 75 %: 128 / 256 / 512 workgroups 35.7 / 26.8 / 30.2 us.)
-inline ResidentPlan plan_resident(const CutSizes& s, bool whole)
+inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
 {
     ResidentPlan best;
     const long tiles = (s.N + 63) / 64, items = s.G * (s.V == 128 ? 2 : 1);
@@ -221,7 +221,7 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole)
         parts = parts < 1 ? 1 : parts > items ? items : parts;
         if (parts == last) continue;
         last = parts;
-        const double t = resident_time(s, whole, (int)parts, waves);
+        const double t = resident_time(s, whole, (int)parts, waves, copy);
         if (t < best.time) { best.time = t; best.parts = (int)parts; best.waves = waves; }
     }
     return best;
@@ -233,6 +233,7 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole)
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
 // 16.3 / 12.1 to 15.2; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
+constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
 inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
@@ -241,6 +242,28 @@ inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& pla
     const int few = s.per <= 4 || s.N < 1024 ? 1 : 0;
     const double margin = MARGINS[s.v()][s.rows == Rows::IMAGES ? 4 : (whole ? 2 : 0) + few];
     return plan.time < margin * cut_time(s, choose_cut(s));
+}
+
+// Convolutions in runs of 8 (GeomConvRuns): the rows of the unfolded matrix are gathered once per workgroup instead of once per
+// group, or staged and read in single values.  What decides is how often a row is fetched, groups x kept share.  Estimates
+// from 1900 convolutions (3x3, 32 to 128 channels, 7x7 to 56x56, stride 1 and 2, both layouts): 10 to 17 % off, the resident slab's
+// with the copy at 2.1 (NCHW: at any alignment, moved in registers) and 1.6 times that of aligned rows 9 and 13 %.  Over them
+// taking it where its estimate is 10 % lower takes 0.92 of the time of the other kernels (geometric mean, the best of both 0.91);
+// a third of those of V = 16 and 32 take it, us before / now: 55 images of 18x18, 128 -> 1024
+// channels at 50 %, V = 16 147.5 / 55.5, 46 of 41x41, 112 -> 240 143.8 / 63.9, 32 of 28x28, 128 -> 512 at 75 %, V = 32 40.1 / 23.0.
+// V >= 64 gains nothing, and 32-bit results were not measured: neither comes here.
+constexpr double RESIDENT_COPY_NCHW = 2.12, RESIDENT_COPY_CHWN = 1.61;
+inline bool resident_conv_pays(const CutSizes& s, bool chwn, bool gathered, const ResidentPlan& plan)
+{
+    if (plan.parts <= 0) return false;
+    struct Cost { double start, step, item; };
+    static constexpr Cost GATHERED[2][2] = {{{4.09, .127, .0913}, {4.06, .0728, .176}}, {{3.84, .114, .0264}, {3.55, .061, .206}}};
+    static constexpr Cost STAGED[2] = {{6.08, .141, 0}, {6.88, .0736, .00289}};   // item: per row of the unfolded matrix and tile
+    const int v = s.V == 16 ? 0 : 1;
+    const double tiles = (double)((s.N + 63) / 64) / 256;
+    const double other = gathered ? GATHERED[chwn][v].start + tiles * s.G * (s.per * GATHERED[chwn][v].step + GATHERED[chwn][v].item)
+                                  : STAGED[v].start + tiles * (s.G * s.per * STAGED[v].step + s.K * STAGED[v].item);
+    return plan.time < .9 * other;
 }
 
 }  // namespace shflbw

@@ -218,8 +218,9 @@ struct GeomLinearBuf {
     {
         if (n < N) store_run<STREAM, CNT>(static_cast<OutT*>(Y) + (long)row * ldy + n, vals);
     }
-    // where column n of a result row lies, elements from the row's start (n < N)
+    // where column n of a result row lies, elements from the row's start (n < N); elements between rows
     __device__ __forceinline__ unsigned out_col(long n) const { return (unsigned)n; }
+    long out_pitch() const { return ldy; }
 };
 
 // Rows of P contiguous columns with no particular alignment, in `images` matrices (1 for a
@@ -464,6 +465,13 @@ struct GeomConvRuns : GeomLinearBuf {
             store_run<STREAM, CNT>(static_cast<OutT*>(Y) + (long)row * osM + pos + (n & 7), vals);
         }
     }
+    __device__ __forceinline__ unsigned out_col(long n) const
+    {
+        int b, y, x;
+        place(n, b, y, x);
+        return (unsigned)(CHWN ? ((long)y * Wo + x) * B + b : (long)b * osB + (long)y * Wo + x) + ((unsigned)n & 7u);
+    }
+    long out_pitch() const { return osM; }
 };
 
 // Convolution as implicit GEMM (Section 4.1): k = (c*R + r)*S + s, and

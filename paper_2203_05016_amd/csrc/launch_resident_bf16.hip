@@ -1,4 +1,5 @@
-// Launchers of the slab kernel with a resident slab, bfloat16 operands.
+// Launchers of the slab kernel with a resident slab, bfloat16 operands, linear layers.
+#define SHFLBW_LAUNCH_CONV 0
 #define SHFLBW_LAUNCH_BF true
 #define SHFLBW_LAUNCH_NAME run_resident_bf16
 #define SHFLBW_LAUNCH_OUT16 __bf16

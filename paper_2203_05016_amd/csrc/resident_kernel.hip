@@ -111,11 +111,13 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
     const int srow = tid >> 3, sunit = tid & 7;
     geom.init(n0 + sunit * 8);
     run_t staged[STAGES];
+    int moved[Geom::FINISH ? STAGES : 1];                    // what geom.finish8 needs to know of them
 #pragma unroll
     for (int i = 0; i < STAGES; ++i) {
-        int unused = 0;
+        int shift = 0;
         const int r = srow + i * STAGE_ROWS;
-        if (i * STAGE_ROWS + wave * 8 < K) staged[i] = geom.load8(geom.entry(r, r < K), unused);   // uniform for the wavefront
+        if (i * STAGE_ROWS + wave * 8 < K) staged[i] = geom.load8(geom.entry(r, r < K), shift);   // uniform for the wavefront
+        if constexpr (Geom::FINISH) moved[i] = shift;
     }
     // (after the loads: before them it would be a wait for the arguments of its own; tiles beyond the last read nothing)
     if (w >= (unsigned)a.total) return;                      // uniform for the workgroup
@@ -211,6 +213,7 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
         const int r = srow + i * STAGE_ROWS;
         if (i * STAGE_ROWS + wave * 8 < K && r < K) {
             run_t v = staged[i];
+            if constexpr (Geom::FINISH) v = Geom::finish8(v, moved[i]);
             const int t = turn(r);
             if constexpr (SMALL) {
                 if (t & 8) v = run_t{v[2], v[3], v[0], v[1]};

@@ -115,3 +115,34 @@ def test_resident_slab_without_kept_columns_and_under_capture():
         torch.cuda.synchronize()
         assert torch.equal(Y, eager)
         A.spmm(X, Y)
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("layout,V,batch,C,H,W,M,R,stride,pad,sparsity", [
+    ("NCHW", 16, 16, 128, 18, 18, 512, 3, 1, 1, 0.50),    # runs of 8, 8 and 2 columns; runs that begin before the image and end after it
+    ("NCHW", 32, 16, 142, 21, 17, 1024, 3, 1, 1, 0.50),   # the longest reduction, one column in the last run
+    ("NCHW", 32, 24, 70, 30, 32, 1024, 3, 1, 0, 0.50),    # no padding, 8 wavefronts
+    ("NCHW", 16, 16, 48, 20, 64, 512, 5, 1, 1, 0.60),     # padding smaller than the kernel's half
+    ("CHWN", 16, 20, 128, 16, 14, 512, 3, 1, 1, 0.50),    # images 12 .. 19 overlap 8 .. 15
+    ("CHWN", 32, 33, 64, 30, 30, 1024, 3, 2, 1, 0.40),
+    ("CHWN", 16, 32, 96, 14, 14, 768, 3, 2, 0, 0.50),
+])
+def test_resident_slab_convolution_exact(layout, V, batch, C, H, W, M, R, stride, pad, sparsity, fmt):
+    """The unfolded matrix in the LDS; NaN right before and after the input."""
+    import torch
+    announce("resident slab, convolution", layout, V, batch, C, H, W, M, R, stride, pad, fmt)
+    p = synth.make_conv(batch, C, H, W, M, R, R, V, sparsity, seed=1751 + V + H, pad=(pad, pad), stride=(stride, stride), integer=True, fmt=fmt)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], R, R, (stride, stride), (pad, pad))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    x = to_device(p.conv["input"])
+    if layout == "CHWN":
+        x = x.permute(1, 2, 3, 0).contiguous()
+    flat = torch.full((x.numel() + 16,), float("nan"), dtype=x.dtype, device="cuda:0")
+    flat[7:-9] = x.flatten()                              # no particular alignment
+    out = A.conv2d(flat[7:-9].view(x.shape), R, R, (stride, stride), (pad, pad), layout=layout)
+    torch.cuda.synchronize()
+    assert "resident" in binding.last_kernel(), binding.last_kernel()
+    if layout == "CHWN":
+        out = out.permute(3, 0, 1, 2)
+    want = _rounded(want, "bfloat16" if fmt == "bf16" else "float16")
+    assert np.array_equal(to_host(out.contiguous()).astype(np.float64), want)
