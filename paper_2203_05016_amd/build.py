@@ -18,7 +18,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libshflbw.so")
 SOURCES = ["compress.cpp", "pattern_search.cpp", "api_device.hip", "launch_gather_f16.hip", "launch_gather_bf16.hip",
-           "launch_gather_conv_f16.hip", "launch_gather_conv_bf16.hip", "launch_resident_f16.hip", "launch_resident_bf16.hip",
+           "launch_gather_conv_f16.hip", "launch_gather_conv_bf16.hip", "launch_gather_stride2_f16.hip", "launch_gather_stride2_bf16.hip",
+           "launch_resident_f16.hip", "launch_resident_bf16.hip",
            "launch_resident_conv_f16.hip", "launch_resident_conv_bf16.hip", "layernorm_transpose.hip"]
 # packed fp32 instructions are switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -210,12 +210,12 @@ double runs_limit(int V, int groups, bool chwn, int innermost)
 }
 
 // The convolution as gathers of runs of 8 (GeomConvRuns).  False when the tensor has no such
-// runs or is beyond the kernel's 24-bit and 32-bit offset arithmetic.
+// runs or is beyond the kernel's 24-bit and 32-bit offset arithmetic.  step: the stride along x that the NCHW geometry takes.
 template <bool CHWN>
 bool fill_conv_runs(const shflbw_matrix* A, GeomConvRuns<CHWN>& g, const void* in, void* out, int B, int C, int H, int W,
-                    int R, int S, int sh, int sw, int ph, int pw, int Ho, int Wo, int64_t in_total, int out_bytes)
+                    int R, int S, int sh, int sw, int ph, int pw, int Ho, int Wo, int64_t in_total, int out_bytes, int step = 1)
 {
-    if (CHWN ? B < 8 : (sw != 1 || Wo < 8 || W < 8 || pw > 1)) return false;
+    if (CHWN ? B < 8 : (sw != step || Wo < 8 || W < 8 * step || pw > 1)) return false;
     const int64_t RS = (int64_t)R * S;
     const int64_t sst = CHWN ? 2 * (int64_t)B : 2, rst = W * sst, cst = H * rst;
     // k / (R*S) by the high half of a product, the remainder / S by 16 bits of one: exact in these ranges
@@ -705,26 +705,39 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     };
     int status = SHFLBW_OK;
     // the unfolded matrix resident in the LDS, 64 columns of it per workgroup
-    const auto try_resident_runs = [&](auto& g) {
-        constexpr bool CHWN = std::is_same<std::decay_t<decltype(g)>, GeomConvRuns<true>>::value;
-        if (!fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, 2 * (int64_t)batch * C_in * H * W, 2))
-            return false;
+    const auto try_resident_runs = [&](auto& g, Runs runs) {
         const int64_t ybytes = 2 * (int64_t)A->M * N;
-        if (g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
+        if (A->V > 32 || A->K > RESIDENT_K || g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
         // (stores: 4 to 7 % either way, as for linear layers)
-        const bool whole = ((CHWN ? batch : Wo) * 2 | (int64_t)reinterpret_cast<uintptr_t>(out)) % 64 == 0;
+        const bool whole = ((runs == Runs::CHWN ? batch : Wo) * 2 | (int64_t)reinterpret_cast<uintptr_t>(out)) % 64 == 0;
         const CutSizes sizes = cut_sizes(A, g.N, Rows::ANY, false);
-        const ResidentPlan plan = plan_resident(sizes, whole, CHWN ? RESIDENT_COPY_CHWN : RESIDENT_COPY_NCHW);
-        if (!resident_conv_pays(sizes, CHWN, runs_pay, plan)) return false;
+        const ResidentPlan plan = plan_resident(sizes, whole, RESIDENT_COPY_RUNS[(int)runs]);
+        if (!resident_conv_pays(sizes, runs, runs_pay || runs == Runs::NCHW_BY_2, plan)) return false;
+        const int streams = g.stream;
         g.stream = whole;
         status = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, g.N, plan, (unsigned)ybytes, ydtype, st)
                                          : run_resident_f16(A, g, g.N, plan, (unsigned)ybytes, ydtype, st);
+        g.stream = streams;
         return true;
     };
-    if (A->tune_kernel == 0 && A->tune_tile_n == 0 && A->V <= 32 && A->K <= RESIDENT_K && ydtype != SHFLBW_F32) {
+    if (A->tune_kernel == 0 && A->tune_tile_n == 0 && ydtype != SHFLBW_F32) {
+        const auto fill = [&](auto& g, int step) {
+            return fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, 2 * (int64_t)batch * C_in * H * W, 2, step);
+        };
         GeomConvRuns<true> chwn;
         GeomConvRuns<false> nchw;
-        if (layout == SHFLBW_CHWN ? try_resident_runs(chwn) : try_resident_runs(nchw)) return status;
+        GeomConvRuns2 by2;
+        if (layout == SHFLBW_CHWN) {
+            if (fill(chwn, 1) && try_resident_runs(chwn, Runs::CHWN)) return status;
+        } else if (stride_w == 2) {
+            if (fill(static_cast<GeomConvRuns<false>&>(by2), 2)) {
+                if (try_resident_runs(by2, Runs::NCHW_BY_2)) return status;
+                if (strided_runs_pay(A->V, A->G, R * S, kept))
+                    return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st);
+            }
+        } else if (fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {
+            return status;
+        }
     }
     if ((A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) && try_runs(&status))
         return status;

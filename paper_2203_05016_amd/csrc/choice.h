@@ -247,23 +247,36 @@ inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& pla
 // Convolutions in runs of 8 (GeomConvRuns): the rows of the unfolded matrix are gathered once per workgroup instead of once per
 // group, or staged and read in single values.  What decides is how often a row is fetched, groups x kept share.  Estimates
 // from 1900 convolutions (3x3, 32 to 128 channels, 7x7 to 56x56, stride 1 and 2, both layouts): 10 to 17 % off, the resident slab's
-// with the copy at 2.1 (NCHW: at any alignment, moved in registers) and 1.6 times that of aligned rows 9 and 13 %.  Over them
+// with the copy at 2.1 (NCHW: at any alignment, moved in registers) and 1.6 times that of aligned rows 9 and 13 % (4.1 times with a stride along x).  Over them
 // taking it where its estimate is 10 % lower takes 0.92 of the time of the other kernels (geometric mean, the best of both 0.91);
 // a third of those of V = 16 and 32 take it, us before / now: 55 images of 18x18, 128 -> 1024
 // channels at 50 %, V = 16 147.5 / 55.5, 46 of 41x41, 112 -> 240 143.8 / 63.9, 32 of 28x28, 128 -> 512 at 75 %, V = 32 40.1 / 23.0.
 // V >= 64 gains nothing, and 32-bit results were not measured: neither comes here.
-constexpr double RESIDENT_COPY_NCHW = 2.12, RESIDENT_COPY_CHWN = 1.61;
-inline bool resident_conv_pays(const CutSizes& s, bool chwn, bool gathered, const ResidentPlan& plan)
+// NCHW with a stride of two along x (GeomConvRuns2): two loads per run.
+enum class Runs { NCHW, CHWN, NCHW_BY_2 };
+constexpr double RESIDENT_COPY_RUNS[3] = {2.12, 1.61, 4.09};
+inline bool resident_conv_pays(const CutSizes& s, Runs runs, bool gathered, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
     struct Cost { double start, step, item; };
-    static constexpr Cost GATHERED[2][2] = {{{4.09, .127, .0913}, {4.06, .0728, .176}}, {{3.84, .114, .0264}, {3.55, .061, .206}}};
+    static constexpr Cost GATHERED[3][2] = {{{4.09, .127, .0913}, {4.06, .0728, .176}}, {{3.84, .114, .0264}, {3.55, .061, .206}},
+                                            {{4.49, .25, .274}, {4.36, .153, .124}}};
     static constexpr Cost STAGED[2] = {{6.08, .141, 0}, {6.88, .0736, .00289}};   // item: per row of the unfolded matrix and tile
     const int v = s.V == 16 ? 0 : 1;
     const double tiles = (double)((s.N + 63) / 64) / 256;
-    const double other = gathered ? GATHERED[chwn][v].start + tiles * s.G * (s.per * GATHERED[chwn][v].step + GATHERED[chwn][v].item)
+    const Cost& g = GATHERED[(int)runs][v];
+    const double other = gathered ? g.start + tiles * s.G * (s.per * g.step + g.item)
                                   : STAGED[v].start + tiles * (s.G * s.per * STAGED[v].step + s.K * STAGED[v].item);
     return plan.time < .9 * other;
+}
+
+// NCHW convolutions with a stride of two along x are gathered but where a kernel larger than 1x1 has many groups that fetch many rows, which
+// staging reads once.  2650 random ones (1x1 and 3x3, 64 to 2048 channels, 15x15 to 58x58, 16-bit results): 0.57 of the time of the
+// staged kernel, geometric mean, 1 % of them more than 4 % slower; gathered always 0.57, 4 % slower, up to 4 times (V = 16, 37
+// images of 28x28, 256 -> 560 channels at 50 % 106 staged, 429 gathered).
+inline bool strided_runs_pay(int V, int G, int taps, double kept)
+{
+    return taps == 1 || V == 64 || G * kept < (V <= 32 ? 3 : 2.5);
 }
 
 }  // namespace shflbw

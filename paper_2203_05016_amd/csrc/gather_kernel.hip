@@ -120,6 +120,7 @@ struct GeomLinear {
     long n0;                                // the lane's first column
     static constexpr bool FINISH = false, CONV = false, CHOICE = false;
     typedef int entry_t;
+    typedef run_t loaded_t;
 
     __device__ __forceinline__ void init(long n) { n0 = n; }
     __device__ __forceinline__ entry_t entry(int col, bool exists) const { return exists ? col : -1; }
@@ -193,6 +194,7 @@ struct GeomLinearBuf {
     static constexpr bool FINISH = false;   // load returns the values as they are used
     static constexpr bool CONV = false;     // the list's entries take divisions
     static constexpr bool CHOICE = true;    // of streaming and plain stores
+    typedef run_t loaded_t;                 // what a load returns, in registers
 
     __device__ __forceinline__ void init(long n)
     {
@@ -474,6 +476,37 @@ struct GeomConvRuns : GeomLinearBuf {
     long out_pitch() const { return osM; }
 };
 
+// The same for NCHW with a stride of two along x (images of 16 columns or more): the 8 values lie in 16 neighbouring ones, two
+// loads, of which every other one is kept.  The 16 may begin one column before the image, or end up to two after it.
+struct runs2_t { run_t a, b; };
+struct GeomConvRuns2 : GeomConvRuns<false> {
+    typedef runs2_t loaded_t;
+    __device__ __forceinline__ runs2_t load8(entry_t e, int& shift) const
+    {
+        const int iy = iy0 + (int)(e[1] >> 16);
+        const int ix = ix0 + (int)(e[1] & 0xffffu);
+        int ic = ix < 0 ? 0 : ix;
+        ic = ic < W - 16 ? ic : W - 16;
+        shift = ic - ix;
+        const unsigned off = (unsigned)iy < (unsigned)H ? e[0] + ln2 + (unsigned)ic * 2u : PAST_END - 16u;
+        return runs2_t{load_run(xd, off), load_run(xd, off + 16u)};
+    }
+    // values 0, 2 .. 14 of those asked for, from the 16 loaded `shift` columns over (-2 .. 1)
+    static __device__ __forceinline__ run_t finish8(const runs2_t& x, int shift)
+    {
+        const unsigned d[10] = {0, x.a[0], x.a[1], x.a[2], x.a[3], x.b[0], x.b[1], x.b[2], x.b[3], 0};
+        const unsigned half = shift & 1 ? 0x07060302u : 0x05040100u;
+        unsigned u[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            u[j] = shift > 0 ? d[j] : d[j + 1];
+            u[j] = shift < -1 ? d[j + 2] : u[j];
+        }
+        return run_t{__builtin_amdgcn_perm(u[1], u[0], half), __builtin_amdgcn_perm(u[3], u[2], half),
+                     __builtin_amdgcn_perm(u[5], u[4], half), __builtin_amdgcn_perm(u[7], u[6], half)};
+    }
+};
+
 // Convolution as implicit GEMM (Section 4.1): k = (c*R + r)*S + s, and
 // n = (b*Ho + y)*Wo + x for NCHW or n = (y*Wo + x)*B + b for CHWN.  This is
 // the general element-wise form; the unfolded matrix never exists in memory.
@@ -491,6 +524,7 @@ struct GeomConv {
     int live;
     static constexpr bool FINISH = false, CONV = false, CHOICE = false;
     typedef int entry_t;
+    typedef run_t loaded_t;
     __device__ __forceinline__ entry_t entry(int col, bool exists) const { return exists ? col : -1; }
 
     __device__ __forceinline__ void split_n(long n, int& b, int& y, int& x) const
@@ -624,7 +658,7 @@ constexpr int gather_batch() { return V == 32 && WN == 128 && SHARES > 1 ? 4 : 2
 template <int V, int WN, class Geom, int SPLIT>
 constexpr int gather_min_waves()
 {
-    return V == 64 && WN == 64 && SPLIT > 0 && SPLIT < 8 && !std::is_same<Geom, GeomConv>::value ? 4 : 2;
+    return V == 64 && WN == 64 && SPLIT > 0 && SPLIT < 8 && !std::is_same<Geom, GeomConv>::value && !std::is_same<Geom, GeomConvRuns2>::value ? 4 : 2;
 }
 
 // SHARES = 1: the wavefronts of a workgroup own different column tiles of one group.
@@ -774,9 +808,9 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
 #pragma unroll
         for (int i = 0; i < NLD; ++i) ent[i] = e[i];
     };
-    run_t xr[PD][NLD];
+    typename Geom::loaded_t xr[PD][NLD];
     int xf[PD];   // what geom.finish8 needs to know of the loads, -8 .. 7 each
-    auto request = [&](run_t (&x)[NLD], int& f) __attribute__((always_inline)) {
+    auto request = [&](typename Geom::loaded_t (&x)[NLD], int& f) __attribute__((always_inline)) {
         f = 0;
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
@@ -966,10 +1000,13 @@ void shflbw_gather_kernel(PackedView A, Geom geom, int n_tiles, GatherOrder orde
         unsigned p[PAIRS];
         half8 o[NT];
         if constexpr (Geom::FINISH) {
+            run_t x[NLD];
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) xr[v % PD][i] = Geom::finish8(xr[v % PD][i], xf[v % PD] << (28 - 4 * i) >> 28);
+            for (int i = 0; i < NLD; ++i) x[i] = Geom::finish8(xr[v % PD][i], xf[v % PD] << (28 - 4 * i) >> 28);
+            pairs(x, p);
+        } else {
+            pairs(xr[v % PD], p);
         }
-        pairs(xr[v % PD], p);
         if constexpr (!SHARE && WA < PD) {
             operands(p, o);
             products(o, wr[0]);

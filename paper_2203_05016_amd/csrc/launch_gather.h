@@ -44,14 +44,19 @@ int run_gather_bf16(const shflbw_matrix* A, const GeomQuads& g, long N, shflbw_d
 int run_gather_bf16(const shflbw_matrix* A, const GeomConvRuns<false>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_bf16(const shflbw_matrix* A, const GeomConvRuns<true>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 
+// 16-bit results only
+int run_gather_f16(const shflbw_matrix* A, const GeomConvRuns2& g, long N, hipStream_t stream);
+int run_gather_bf16(const shflbw_matrix* A, const GeomConvRuns2& g, long N, hipStream_t stream);
 // the slab kernel with a resident slab (resident_kernel.hip).  ybytes: from g.Y to the end of the results
 int run_resident_f16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_f16(const shflbw_matrix* A, const GeomRows& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_f16(const shflbw_matrix* A, const GeomConvRuns<false>& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_f16(const shflbw_matrix* A, const GeomConvRuns<true>& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
+int run_resident_f16(const shflbw_matrix* A, const GeomConvRuns2& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_bf16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_bf16(const shflbw_matrix* A, const GeomRows& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_bf16(const shflbw_matrix* A, const GeomConvRuns<false>& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 int run_resident_bf16(const shflbw_matrix* A, const GeomConvRuns<true>& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
+int run_resident_bf16(const shflbw_matrix* A, const GeomConvRuns2& g, long N, const ResidentPlan& plan, unsigned ybytes, shflbw_dtype ydtype, hipStream_t stream);
 
 }  // namespace shflbw

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
     constexpr int STAGE_ROWS = 8 * WAVES, STAGES = V >= 64 ? 20 : 10;
     const int srow = tid >> 3, sunit = tid & 7;
     geom.init(n0 + sunit * 8);
-    run_t staged[STAGES];
+    typename Geom::loaded_t staged[STAGES];
     int moved[Geom::FINISH ? STAGES : 1];                    // what geom.finish8 needs to know of them
 #pragma unroll
     for (int i = 0; i < STAGES; ++i) {
@@ -212,8 +212,9 @@ __global__ __launch_bounds__(64 * WAVES, V >= 64 ? 2 : 4) void shflbw_slab_kerne
     for (int i = 0; i < STAGES; ++i) {
         const int r = srow + i * STAGE_ROWS;
         if (i * STAGE_ROWS + wave * 8 < K && r < K) {
-            run_t v = staged[i];
-            if constexpr (Geom::FINISH) v = Geom::finish8(v, moved[i]);
+            run_t v;
+            if constexpr (Geom::FINISH) v = Geom::finish8(staged[i], moved[i]);
+            else v = staged[i];
             const int t = turn(r);
             if constexpr (SMALL) {
                 if (t & 8) v = run_t{v[2], v[3], v[0], v[1]};
