@@ -136,6 +136,7 @@ bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, i
     // results by 2047 30 and 17; 1x1, 512 -> 1024 channels of 14x14 10.6 and 9.5.
     const bool whole = (pitch | (int64_t)reinterpret_cast<uintptr_t>(geom.Y)) % 64 == 0;
     const CutSizes sizes = cut_sizes(A, N, rows, ydtype == SHFLBW_F32);
+    if (!resident_worth_a_look(sizes)) return false;
     const ResidentPlan plan = plan_resident(sizes, whole, rows == Rows::ALIGNED ? 1 : RESIDENT_COPY_UNALIGNED);
     if (!resident_pays(sizes, whole, plan)) return false;
     Geom g = geom;
@@ -707,7 +708,7 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     // the unfolded matrix resident in the LDS, 64 columns of it per workgroup
     const auto try_resident_runs = [&](auto& g, Runs runs) {
         const int64_t ybytes = 2 * (int64_t)A->M * N;
-        if (A->V > 32 || A->K > RESIDENT_K || g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
+        if (!resident_conv_worth_a_look(A->V, A->K, (g.N + 63) / 64 * A->G) || g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
         // (stores: 4 to 7 % either way, as for linear layers)
         const bool whole = ((runs == Runs::CHWN ? batch : Wo) * 2 | (int64_t)reinterpret_cast<uintptr_t>(out)) % 64 == 0;
         const CutSizes sizes = cut_sizes(A, g.N, Rows::ANY, false);
@@ -727,15 +728,17 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         GeomConvRuns<true> chwn;
         GeomConvRuns<false> nchw;
         GeomConvRuns2 by2;
+        // (before the geometry is worked out: runs fill at most twice the columns)
+        const bool look = resident_conv_worth_a_look(A->V, A->K, (N / 32 + 1) * A->G);
         if (layout == SHFLBW_CHWN) {
-            if (fill(chwn, 1) && try_resident_runs(chwn, Runs::CHWN)) return status;
+            if (look && fill(chwn, 1) && try_resident_runs(chwn, Runs::CHWN)) return status;
         } else if (stride_w == 2) {
             if (fill(static_cast<GeomConvRuns<false>&>(by2), 2)) {
                 if (try_resident_runs(by2, Runs::NCHW_BY_2)) return status;
                 if (strided_runs_pay(A->V, A->G, R * S, kept))
                     return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st);
             }
-        } else if (fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {
+        } else if (look && fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {
             return status;
         }
     }

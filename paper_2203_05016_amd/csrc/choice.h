@@ -228,12 +228,16 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
 }
 
 // Taken where its estimate is below the best cut's, which is 5 to 20 % low by V and by how results lie in memory, and least
-// sure where steps or columns are few: hence the margins.  Over those 3200 layers the choice takes 0.943 of the time of the other kernels
-// (geometric mean over all, 800 take this one; the best of both 0.924), 30 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other
+// sure where steps or columns are few: hence the margins.  Over those 3200 layers the choice takes 0.945 of the time of the other kernels
+// (geometric mean over all, 730 take this one; the best of both 0.924), 24 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
 // 16.3 / 12.1 to 15.2; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
 constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
+// Fewer tiles than this gain little (of the layers below it a sixth would take it, and win 1 %), half of those that lose are among them,
+// and the estimates cost a call of 3 us 0.1.
+inline bool resident_worth_a_look(const CutSizes& s) { return s.K <= RESIDENT_K && s.tiles() >= 1024; }
+inline bool resident_conv_worth_a_look(int V, int K, long tiles) { return V <= 32 && K <= RESIDENT_K && tiles >= 512; }
 inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
