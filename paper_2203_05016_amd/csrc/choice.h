@@ -228,10 +228,12 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
 }
 
 // Taken where its estimate is below the best cut's, which is 5 to 20 % low by V and by how results lie in memory, and least
-// sure where steps or columns are few: hence the margins.  Over those 3200 layers the choice takes 0.945 of the time of the other kernels
-// (geometric mean over all, 730 take this one; the best of both 0.924), 24 lose more than 4 %.  4096 x 1024, V = 32 at 75 %, us other
+// sure where steps or columns are few: hence the margins.  Over those 3200 layers, which they were fitted to, the choice takes 0.951 of the
+// time of the other kernels (geometric mean over all, 580 take this one; the best of both 0.924), 11 lose more than 4 %.  Of 220 other
+// ones of 1024 tiles or more 84 take it, at 0.825 of the time, and 4 of them lose more than 4 % (1152 x 160 by 9210, V = 64 at 50 %
+// 10.2 / 12.2, 7760 x 184 by 216, V = 16 at 50 % 4.4 / 5.0).  Margins 6 % wider on linear layers: 105 at 0.852, 9 lose more than 4 %, 5 more than 10.  4096 x 1024, V = 32 at 75 %, us other
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
-// 16.3 / 12.1 to 15.2; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
+// 16.3 / 12.0 to 14.4; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
 constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
 // Fewer tiles than this gain little (of the layers below it a sixth would take it, and win 1 %), half of those that lose are among them,
@@ -242,7 +244,7 @@ inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& pla
 {
     if (plan.parts <= 0) return false;
     // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few, images
-    static constexpr double MARGINS[4][5] = {{1.04, 1.04, .96, .9, 1.02}, {1.05, .92, .9, .88, .94}, {1.08, .92, 1.02, .86, .88}, {.94, .85, 1.15, .85, .85}};
+    static constexpr double MARGINS[4][5] = {{.98, .98, .9, .85, 1.02}, {.99, .86, .85, .83, .94}, {1.02, .86, .96, .81, .88}, {.94, .8, 1.08, .8, .85}};
     const int few = s.per <= 4 || s.N < 1024 ? 1 : 0;
     const double margin = MARGINS[s.v()][s.rows == Rows::IMAGES ? 4 : (whole ? 2 : 0) + few];
     return plan.time < margin * cut_time(s, choose_cut(s));
