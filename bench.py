@@ -31,10 +31,10 @@ HBM_PEAK = 8.0e12
 # COUNTER_SOURCE (they are not measured by this run: counters are collected in runs of their
 # own).  They are reported only when the run launches what that summary profiled: automatic
 # kernel choice, no tile override, and the kernel named in COUNTER_KERNEL.
-COUNTER_SOURCE = "profiles/slab_kernel_ffn_config2_pmc.md"
-COUNTER_KERNEL = "shflbw_slab_kernel<32,12,f16,f16 out>"
-L2_TO_CU_BYTES = 330.0e6        # TCP_TCC_READ_REQ x 128 B per launch
-MEASURED_TRAFFIC_BYTES = 107.2e6  # FETCH_SIZE + WRITE_SIZE per launch, scaled by the same counters on a 64 MiB copy
+COUNTER_SOURCE = "profiles/resident_slab_ffn_pmc.md"
+COUNTER_KERNEL = "shflbw_slab_kernel<32,resident in 16 wavefronts,f16,f16 out>"
+L2_TO_CU_BYTES = 321.0e6        # TCP_TCC_READ_REQ x 128 B per launch
+MEASURED_TRAFFIC_BYTES = 101.9e6  # FETCH_SIZE + WRITE_SIZE per launch, scaled by the same counters on a 64 MiB copy
 PAPER_CONTEXT = "paper: up to 1.81x/4.18x/1.90x over cuBLAS dense at 75% on V100/T4/A100 (context only)"
 
 
@@ -492,7 +492,7 @@ def main():
     ln_r["fraction_of_headline_time"] = ln_r["ms"] / main_r["ms"]
     l2_r = measure_l2_stream(p)
     # bytes the headline kernel pulls from the L2s into its CUs per launch (TCP_TCC_READ_REQ x 128 B,
-    # profiles/slab_kernel_ffn_config2_pmc.md) over its launch time, against the probe's rates
+    # COUNTER_SOURCE) over its launch time, against the probe's rates
     counters_apply = args.kernel == 0 and args.tile_n == 0 and main_r["kernel"] == COUNTER_KERNEL
     if counters_apply:
         l2_r["kernel_l2_bytes_per_launch"] = L2_TO_CU_BYTES

@@ -1,5 +1,6 @@
-// Slab kernel with the whole slab resident, for the Shfl-BW product on gfx950 (CDNA4): linear layers and 1x1
-// convolutions whose reduction is short enough (K <= 1278) that 64 columns of X fit the 160 KB LDS of a CU.
+// Slab kernel with the whole slab resident, for the Shfl-BW product on gfx950 (CDNA4): linear layers, 1x1
+// convolutions and convolutions in runs whose reduction is short enough (K <= 1278) that 64 columns of X (of the unfolded matrix)
+// fit the 160 KB LDS of a CU.
 //
 // A workgroup copies its 64 columns of X to the LDS once, every row, and its wavefronts then take row groups of the
 // workgroup's share one after the other, each at its own pace: no ring, no hand-over, no barrier after the first.
@@ -18,7 +19,8 @@
 // CU, and a step of 64 columns brings 1 KB of weights through it (16 clocks, all that a step can do about it with 64 columns resident), beside 16 clocks
 // of the matrix cores; clocks are 1.5 to 1.7 GHz in it.  What else used that path was taken out: an index load of 4 bytes per lane costs what one of 16 does, so
 // indices come 16 steps at a time (2 loads per 4 steps -> 1 per 16: 28.3 -> 26.9).  HBM sees 102 MB, 86 of them what it cannot do without.
-// Tried without a gain: weights eight steps ahead instead of four (+-1 %, V = 16 +10 %: registers), groups in another order on every CU.
+// Tried without a gain: weights eight steps ahead instead of four (+-1 %, V = 16 +10 %: registers), rows three ahead instead of two (+1 %, V = 16 +7 %),
+// groups in another order on every CU (+1 %, by 2047 +8 %).
 #pragma once
 #include <hip/hip_runtime.h>
 
