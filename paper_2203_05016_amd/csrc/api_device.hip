@@ -735,7 +735,8 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         } else if (stride_w == 2) {
             if (fill(static_cast<GeomConvRuns<false>&>(by2), 2)) {
                 if (try_resident_runs(by2, Runs::NCHW_BY_2)) return status;
-                if (strided_runs_pay(A->V, A->G, R * S, kept))
+                // (the gather kernel's grid has a row per group; the staged kernel takes more of them)
+                if (A->G <= GATHER_MAX_GROUPS && strided_runs_pay(A->V, A->G, R * S, kept))
                     return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st);
             }
         } else if (look && fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {

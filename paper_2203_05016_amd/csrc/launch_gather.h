@@ -10,6 +10,8 @@
 
 namespace shflbw {
 
+constexpr int GATHER_MAX_GROUPS = 65535;   // rows of a launch's grid
+
 // what the choice of a cut looks at
 inline CutSizes cut_sizes(const shflbw_matrix* A, long N, Rows rows, bool f32)
 {

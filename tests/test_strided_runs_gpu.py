@@ -45,3 +45,16 @@ def test_stride_two_exact(V, batch, C, H, W, M, R, S, stride_h, pad, sparsity, k
     rounded = torch.from_numpy(want).to(x.dtype).double().numpy()
     assert np.array_equal(to_host(out).astype(np.float64), rounded)
     assert bool(torch.isnan(guard[:3]).all()) and bool(torch.isnan(guard[-13:]).all())
+
+
+def test_stride_two_of_more_groups_than_a_grid_has_rows():
+    """65 536 groups, one more than the gather kernel takes, of a size that is never resident: staged."""
+    import torch
+    announce("strided runs, 65536 groups")
+    p = synth.make_conv(1, 8, 1, 16, 65536 * 64, 1, 1, 64, 0.5, seed=1861, stride=(2, 2), integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], 1, 1, (2, 2), (0, 0))
+    A = binding.compress(p.W, p.mask, p.perm, 64).bind_device("cuda:0")
+    got = A.conv2d(to_device(p.conv["input"]), 1, 1, (2, 2), (0, 0))
+    torch.cuda.synchronize()
+    assert "conv" in binding.last_kernel(), binding.last_kernel()
+    assert np.array_equal(to_host(got).astype(np.float64), want)
