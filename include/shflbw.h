@@ -150,7 +150,11 @@ int shflbw_bind_device(shflbw_matrix* A, void* dev_buf, void* stream);
  * shflbw_conv2d (the call then fails with SHFLBW_ERR_BAD_OPTION when the
  * matrix, the operands or the shape do not allow it), 3 = gather kernel with
  * the k-steps of a tile split over the wavefronts of a workgroup (the variant
- * for very few output columns; shflbw_conv2d treats 3 like 1).
+ * for very few output columns; shflbw_conv2d treats 3 like 1), 4 = slab kernel
+ * with a resident slab, for both calls (SHFLBW_ERR_BAD_OPTION where it cannot
+ * run: K above 1278, fewer than four groups, fewer than 8 columns that are not
+ * aligned; convolutions, 1x1 of unit stride apart, also with V above 32, 32-bit
+ * results or no runs of 8).
  * tile_n: 0 = automatic, else the number of output columns one wavefront of
  * the gather kernel owns (64 or 128). */
 int shflbw_set_tuning(shflbw_matrix* A, int kernel, int tile_n);

@@ -121,12 +121,20 @@ int dispatch_out(const shflbw_matrix* A, const Geom& geom, long N, shflbw_dtype 
 // what stream_stores calls reads
 double reads_of(const shflbw_matrix* A) { return (double)A->nnz / ((double)A->M * A->V); }
 
-// The slab kernel with a resident slab, where it applies and pays: rc is the launch's status.  yelems: from Y's start to
+// Why set_tuning(4, ..) cannot be followed
+int no_resident()
+{
+    return fail(SHFLBW_ERR_BAD_OPTION, "the resident slab needs K <= %d and four groups or more, few enough column tiles, results within 4 GiB; convolutions other "
+                "than 1x1 also V = 16 or 32, runs of 8 and 16-bit results", RESIDENT_K);
+}
+
+// The slab kernel with a resident slab, where it applies, and pays or is forced: rc is the launch's status.  yelems: from Y's start to
 // its end, in elements.
 template <class Geom>
 bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, int64_t yelems, shflbw_dtype ydtype, hipStream_t stream, int* rc)
 {
-    if (A->tune_kernel != 0 || A->tune_tile_n != 0 || A->K > RESIDENT_K) return false;
+    const bool forced = A->tune_kernel == 4;
+    if (!forced && (A->tune_kernel != 0 || A->tune_tile_n != 0 || A->K > RESIDENT_K)) return false;
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
     const int64_t pitch = geom.out_pitch() * ob, ybytes = yelems * ob;
     // results' offsets: 24-bit products in 32 bits
@@ -136,9 +144,9 @@ bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, i
     // results by 2047 30 and 17; 1x1, 512 -> 1024 channels of 14x14 10.6 and 9.5.
     const bool whole = (pitch | (int64_t)reinterpret_cast<uintptr_t>(geom.Y)) % 64 == 0;
     const CutSizes sizes = cut_sizes(A, N, rows, ydtype == SHFLBW_F32);
-    if (!resident_worth_a_look(sizes)) return false;
+    if (!forced && !resident_worth_a_look(sizes)) return false;
     const ResidentPlan plan = plan_resident(sizes, whole, rows == Rows::ALIGNED ? 1 : RESIDENT_COPY_UNALIGNED);
-    if (!resident_pays(sizes, whole, plan)) return false;
+    if (plan.parts <= 0 || (!forced && !resident_pays(sizes, whole, plan))) return false;
     Geom g = geom;
     g.stream = whole;
     *rc = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, N, plan, (unsigned)ybytes, ydtype, stream)
@@ -164,6 +172,7 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     int rc = SHFLBW_OK;
     if (try_resident(A, g, g.N, images > 1 ? Rows::IMAGES : Rows::ANY, (images - 1) * y_image + (A->M - 1) * ldy + P, ydtype, stream, &rc))
         return rc;
+    if (A->tune_kernel == 4) return no_resident();
     return dispatch_out(A, g, g.N, ydtype, stream);
 }
 
@@ -527,6 +536,7 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
         g.xbytes = (unsigned)xbytes;
         if (try_resident(A, g, (long)N, Rows::ALIGNED, (A->M - 1) * ldy + N, ydtype, st, &rc)) return rc;
     }
+    if (A->tune_kernel == 4 && (aligned || !described || N < 8)) return no_resident();   // (the others: run_rows)
     bool use_slab = A->tune_kernel == 2;
     if (A->tune_kernel == 0 && slab_possible) {
         // the slab kernel streams all of X whatever the sparsity and its workgroup's groups share it: it pays where
@@ -655,7 +665,8 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     // A 1x1 convolution with unit stride and no padding on a batch-innermost tensor IS the
     // linear-layer product: [C_in][H*W*batch] in, [C_out][H*W*batch] out, both row-major.
-    if (A->tune_kernel == 0 && layout == SHFLBW_CHWN && R == 1 && S == 1 && stride_h == 1 &&
+    const bool resident_only = A->tune_kernel == 4;
+    if ((A->tune_kernel == 0 || resident_only) && layout == SHFLBW_CHWN && R == 1 && S == 1 && stride_h == 1 &&
         stride_w == 1 && pad_h == 0 && pad_w == 0)
         return shflbw_spmm(A, in, N, out, N, N, ydtype, stream);
     // The same on NCHW tensors is one such product per image; the gather kernel takes all images
@@ -671,8 +682,8 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         // 50 %, V = 16 23.8 / 19.0 at 50 %.
         const bool dense_quads = A->V <= 64 && (N + 63) / 64 * A->G >= 1024 && 2.5 * A->nnz > (double)A->M * A->K &&
                                  A->nnz >= (int64_t)160 * A->M;
-        if (A->tune_kernel == 0 && layout == SHFLBW_NCHW && R == 1 && S == 1 && stride_h == 1 &&
-            stride_w == 1 && pad_h == 0 && pad_w == 0 && (HW >= 8 || (HW == 4 && !dense_quads)) && HW * 2 < (1 << 24) &&
+        if ((A->tune_kernel == 0 || resident_only) && layout == SHFLBW_NCHW && R == 1 && S == 1 && stride_h == 1 &&
+            stride_w == 1 && pad_h == 0 && pad_w == 0 && (HW >= 8 || (HW == 4 && !dense_quads && !resident_only)) && HW * 2 < (1 << 24) &&
             C_in < (1 << 24) && in_total < ((int64_t)1 << 32) - 64) {
             if (HW >= 8)
                 return run_rows(A, in, HW, (long)C_in * HW, out, HW, (long)A->M * HW, (int)HW, batch, in_total, ydtype, st);
@@ -708,12 +719,13 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
     // the unfolded matrix resident in the LDS, 64 columns of it per workgroup
     const auto try_resident_runs = [&](auto& g, Runs runs) {
         const int64_t ybytes = 2 * (int64_t)A->M * N;
-        if (!resident_conv_worth_a_look(A->V, A->K, (g.N + 63) / 64 * A->G) || g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
+        if (!resident_only && !resident_conv_worth_a_look(A->V, A->K, (g.N + 63) / 64 * A->G)) return false;
+        if (A->V > 32 || g.out_pitch() * 2 >= (1 << 24) || A->M >= (1 << 24) || ybytes >= ((int64_t)1 << 32) - 64) return false;
         // (stores: 4 to 7 % either way, as for linear layers)
         const bool whole = ((runs == Runs::CHWN ? batch : Wo) * 2 | (int64_t)reinterpret_cast<uintptr_t>(out)) % 64 == 0;
         const CutSizes sizes = cut_sizes(A, g.N, Rows::ANY, false);
         const ResidentPlan plan = plan_resident(sizes, whole, RESIDENT_COPY_RUNS[(int)runs]);
-        if (!resident_conv_pays(sizes, runs, runs_pay || runs == Runs::NCHW_BY_2, plan)) return false;
+        if (plan.parts <= 0 || (!resident_only && !resident_conv_pays(sizes, runs, runs_pay || runs == Runs::NCHW_BY_2, plan))) return false;
         const int streams = g.stream;
         g.stream = whole;
         status = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, g.N, plan, (unsigned)ybytes, ydtype, st)
@@ -721,7 +733,7 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         g.stream = streams;
         return true;
     };
-    if (A->tune_kernel == 0 && A->tune_tile_n == 0 && ydtype != SHFLBW_F32) {
+    if (((A->tune_kernel == 0 && A->tune_tile_n == 0) || resident_only) && ydtype != SHFLBW_F32) {
         const auto fill = [&](auto& g, int step) {
             return fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, 2 * (int64_t)batch * C_in * H * W, 2, step);
         };
@@ -729,20 +741,21 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         GeomConvRuns<false> nchw;
         GeomConvRuns2 by2;
         // (before the geometry is worked out: runs fill at most twice the columns)
-        const bool look = resident_conv_worth_a_look(A->V, A->K, (N / 32 + 1) * A->G);
+        const bool look = resident_only || resident_conv_worth_a_look(A->V, A->K, (N / 32 + 1) * A->G);
         if (layout == SHFLBW_CHWN) {
             if (look && fill(chwn, 1) && try_resident_runs(chwn, Runs::CHWN)) return status;
         } else if (stride_w == 2) {
             if (fill(static_cast<GeomConvRuns<false>&>(by2), 2)) {
                 if (try_resident_runs(by2, Runs::NCHW_BY_2)) return status;
                 // (the gather kernel's grid has a row per group; the staged kernel takes more of them)
-                if (A->G <= GATHER_MAX_GROUPS && strided_runs_pay(A->V, A->G, R * S, kept))
+                if (!resident_only && A->G <= GATHER_MAX_GROUPS && strided_runs_pay(A->V, A->G, R * S, kept))
                     return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st);
             }
         } else if (look && fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {
             return status;
         }
     }
+    if (resident_only) return no_resident();
     if ((A->tune_kernel == 1 || A->tune_kernel == 3 || (A->tune_kernel == 0 && runs_pay)) && try_runs(&status))
         return status;
     if (A->tune_kernel != 1 && A->tune_kernel != 3) {

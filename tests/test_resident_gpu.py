@@ -146,3 +146,77 @@ def test_resident_slab_convolution_exact(layout, V, batch, C, H, W, M, R, stride
         out = out.permute(3, 0, 1, 2)
     want = _rounded(want, "bfloat16" if fmt == "bf16" else "float16")
     assert np.array_equal(to_host(out.contiguous()).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("V,G,K,N,sparsity,ragged", [
+    (16, 4, 1, 8, 0.0, False),             # one row of X, one slot of columns
+    (16, 5, 33, 64, 0.4, True),            # one column tile
+    (16, 7, 1278, 72, 0.5, False),
+    (32, 4, 9, 1, 0.0, False),             # (refused: fewer than 8 columns that are no whole units)
+    (32, 4, 640, 8, 0.9, True),
+    (32, 17, 638, 65, 0.5, True),          # one column in the second tile
+    (32, 35, 200, 130, 0.75, False),       # more groups than wavefronts of a workgroup
+    (64, 4, 1278, 63, 0.3, True),
+    (64, 19, 17, 128, 0.0, False),
+    (128, 4, 100, 9, 0.5, False),
+    (128, 9, 1278, 320, 0.8, True),
+])
+def test_resident_slab_as_asked_for(V, G, K, N, sparsity, ragged, fmt):
+    """set_tuning(4, 0): far fewer tiles than the automatic choice gives it."""
+    announce("resident slab, asked for", V, G, K, N, ragged, fmt)
+    p = synth.make_spmm(G * V, K, N, V, sparsity, seed=1761 + N + V + K, integer=True, ragged=ragged, fmt=fmt)
+    if N < 8:
+        with pytest.raises(binding.ShflbwError):
+            run_spmm(p, kernel=4)
+        return
+    want, _ = c_oracle.spmm(p.W, p.mask, p.X)
+    for out in ("float32", "bfloat16" if fmt == "bf16" else "float16"):
+        got = run_spmm(p, out_dtype=out, kernel=4, pad_ld=8 if N % 8 == 0 else 3).astype(np.float64)
+        assert "resident" in binding.last_kernel(), binding.last_kernel()
+        assert np.array_equal(got, _rounded(want, out)), np.argwhere(got != _rounded(want, out))[:4]
+
+
+@pytest.mark.parametrize("layout,V,batch,C,H,W,M,R,stride,pad,sparsity", [
+    ("NCHW", 16, 1, 3, 8, 8, 64, 3, 1, 1, 0.0),
+    ("NCHW", 32, 2, 142, 9, 11, 128, 3, 1, 1, 0.6),
+    ("NCHW", 16, 1, 51, 20, 19, 80, 5, 2, 1, 0.7),
+    ("NCHW", 32, 3, 70, 15, 17, 128, 3, 2, 1, 0.5),
+    ("NCHW", 128, 3, 65, 3, 3, 512, 1, 1, 0, 0.5),        # 1x1: a product per image
+    ("CHWN", 32, 8, 20, 5, 6, 128, 3, 1, 1, 0.5),
+    ("CHWN", 16, 13, 9, 7, 4, 64, 3, 2, 0, 0.2),
+    ("CHWN", 64, 5, 30, 3, 3, 256, 1, 1, 0, 0.5),
+])
+def test_resident_slab_convolution_as_asked_for(layout, V, batch, C, H, W, M, R, stride, pad, sparsity):
+    import torch
+    announce("resident slab, convolution asked for", layout, V, batch, C, H, W, M, R, stride, pad)
+    p = synth.make_conv(batch, C, H, W, M, R, R, V, sparsity, seed=1771 + V + H, pad=(pad, pad), stride=(stride, stride), integer=True)
+    want, _ = c_oracle.conv2d(p.W, p.mask, p.conv["input"], R, R, (stride, stride), (pad, pad))
+    A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+    A.set_tuning(4, 0)
+    x = to_device(p.conv["input"])
+    out = A.conv2d(x if layout == "NCHW" else x.permute(1, 2, 3, 0).contiguous(), R, R, (stride, stride), (pad, pad), layout=layout)
+    torch.cuda.synchronize()
+    assert "resident" in binding.last_kernel(), binding.last_kernel()
+    out = out if layout == "NCHW" else out.permute(3, 0, 1, 2).contiguous()
+    assert np.array_equal(to_host(out).astype(np.float64), _rounded(want, "float16"))
+
+
+def test_resident_slab_is_refused_where_it_cannot_run():
+    import torch
+    announce("resident slab, refused")
+    def matrix(V, G, K):
+        p = synth.make_spmm(G * V, K, 64, V, 0.5, seed=1781)
+        A = binding.compress(p.W, p.mask, p.perm, V).bind_device("cuda:0")
+        A.set_tuning(4, 0)
+        return A
+    X = torch.zeros((1279, 64), dtype=torch.float16, device="cuda:0")
+    for V, G, K in ((32, 8, 1279), (32, 3, 64), (128, 3, 64)):
+        with pytest.raises(binding.ShflbwError) as e:
+            matrix(V, G, K).spmm(X[:K])
+        assert e.value.status == -9
+    x = torch.zeros((2, 16, 12, 12), dtype=torch.float16, device="cuda:0")
+    for V, dt, w in ((64, torch.float16, 12), (32, torch.float32, 12), (32, torch.float16, 7)):   # too large groups, 32-bit results, no runs
+        with pytest.raises(binding.ShflbwError) as e:
+            matrix(V, 8, 144).conv2d(x[..., :w].contiguous(), 3, 3, (1, 1), (1, 1), out_dtype=dt)
+        assert e.value.status == -9

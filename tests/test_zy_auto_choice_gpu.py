@@ -1,7 +1,7 @@
 """The automatic kernel choice of shflbw_spmm on shapes that are none of the
 benchmark's: on each, the time of the automatic choice must stay within 1.2x
-of the fastest forced kernel (per-wave gather, shared slab, split k-steps;
-a kernel that refuses the shape does not compete).  Times are the best of
+of the fastest forced kernel (per-wave gather, shared slab, split k-steps,
+resident slab; a kernel that refuses the shape does not compete).  Times are the best of
 three batches after a settling phase, so the comparison is between kernels,
 not between clock states."""
 import numpy as np
@@ -66,7 +66,7 @@ def test_automatic_choice_is_within_a_fifth_of_the_best_forced_kernel(shape):
     Xs = [x0, x0.clone(), x0.clone()]
     Ys = [torch.empty((M, N), dtype=torch.float16, device="cuda:0") for _ in range(3)]
     forced = {}
-    for kernel in (1, 2, 3):
+    for kernel in (1, 2, 3, 4):
         t, name = _time(A, Xs, Ys, kernel)
         if t is not None:
             forced[name] = t
