@@ -227,13 +227,15 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
     return best;
 }
 
-// Taken where its estimate is below the best cut's, which is 5 to 20 % low by V and by how results lie in memory, and least
-// sure where steps or columns are few: hence the margins.  Over those 3200 layers, which they were fitted to, the choice takes 0.951 of the
-// time of the other kernels (geometric mean over all, 580 take this one; the best of both 0.924), 11 lose more than 4 %.  Of 220 other
-// ones of 1024 tiles or more 84 take it, at 0.825 of the time, and 4 of them lose more than 4 % (1152 x 160 by 9210, V = 64 at 50 %
-// 10.2 / 12.2, 7760 x 184 by 216, V = 16 at 50 % 4.4 / 5.0).  Margins 6 % wider on linear layers: 105 at 0.852, 9 lose more than 4 %, 5 more than 10.  4096 x 1024, V = 32 at 75 %, us other
+// Taken where its estimate is below the best cut's by a margin.  Both estimates are low, by 5 to 20 % by V and by how results lie, and neither
+// is better than 13 to 20 %, worst where a group has few steps, or where there are few columns or little work: hence the
+// margins, which are such that few layers get slower, at the price of some that would have gained.  Of 6992 random layers that nothing was fitted
+// to (half of them are profiles/resident_sweep.csv) 2778 take it, at .767 of the other kernels' time (geometric mean; over all .900, the best of both
+// .877): 45 of these lose more than 4 %, 11 more than 10 %, the worst 34 % (1x1, 26 images of 30x30, 1143 -> 1600 channels at 80 %, V = 32).  With one margin for all images and the same for little work
+// 6 % of those that took it lost more than 4 %, 3 % more than 10 %, and the gain over all was the same .900.
+// 4096 x 1024, V = 32 at 75 %, us other
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
-// 16.3 / 12.0 to 14.4; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
+// 16.3 / 12.0 to 15.2, by card; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
 constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
 // Fewer tiles than this gain little (of the layers below it a sixth would take it, and win 1 %), half of those that lose are among them,
@@ -243,10 +245,13 @@ inline bool resident_conv_worth_a_look(int V, int K, long tiles) { return V <= 3
 inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
-    // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few, images
-    static constexpr double MARGINS[4][5] = {{.98, .98, .9, .85, 1.02}, {.99, .86, .85, .83, .94}, {1.02, .86, .96, .81, .88}, {.94, .8, 1.08, .8, .85}};
+    // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few; then the same of images.  0: never.
+    static constexpr double MARGINS[4][8] = {{.98, .98, .9, .85, .99, 1.02, .87, .95}, {.98, .86, .85, .74, .94, .94, .87, 0},
+                                             {1.01, .86, .89, .81, .88, .88, .74, 0}, {.93, .8, 1.05, .8, 0, 0, 0, 0}};
     const int few = s.per <= 4 || s.N < 1024 ? 1 : 0;
-    const double margin = MARGINS[s.v()][s.rows == Rows::IMAGES ? 4 : (whole ? 2 : 0) + few];
+    double margin = MARGINS[s.v()][(s.rows == Rows::IMAGES ? 4 : 0) + (whole ? 2 : 0) + few];
+    const double work = (double)s.tiles() * s.per;
+    if (few && s.V < 128 && work < 12000) margin *= std::sqrt(std::sqrt(work / 12000));
     return plan.time < margin * cut_time(s, choose_cut(s));
 }
 

@@ -3,14 +3,32 @@
 
 using namespace shflbw;
 
-extern "C" int probe_choice(int V, long G, long N, long steps, int K, int rows, int uneven, int f32, int slab, double kept, int what)
+namespace {
+CutSizes sizes_of(int V, long G, long N, long steps, int K, int rows, int uneven, int f32, int slab, double kept)
 {
     CutSizes s;
     s.V = V; s.G = G; s.N = N; s.steps = steps; s.K = K;
     s.per = steps / (G > 0 ? G : 1);
     s.rows = rows == 0 ? Rows::ALIGNED : rows == 1 ? Rows::ANY : Rows::IMAGES;
     s.uneven = uneven; s.f32 = f32; s.slab = slab; s.kept = kept;
+    return s;
+}
+}  // namespace
+
+extern "C" int probe_choice(int V, long G, long N, long steps, int K, int rows, int uneven, int f32, int slab, double kept, int what)
+{
+    const CutSizes s = sizes_of(V, G, N, steps, K, rows, uneven, f32, slab, kept);
     if (what == 1) return shares_weights(V, false, s.per);
     if (what == 2) return shares_weights(V, true, s.per);
     return choose_cut(s);
+}
+
+// A linear layer (rows: as above) on the resident slab: whether it is taken; its plan and both estimates.
+extern "C" int probe_resident(int V, long G, long N, long steps, int K, int rows, int uneven, int f32, int slab, double kept, int whole,
+                              int* parts, int* waves, double* time, double* other)
+{
+    const CutSizes s = sizes_of(V, G, N, steps, K, rows, uneven, f32, slab, kept);
+    const ResidentPlan plan = plan_resident(s, whole, rows == 0 ? 1 : RESIDENT_COPY_UNALIGNED);
+    *parts = plan.parts; *waves = plan.waves; *time = plan.time; *other = cut_time(s, choose_cut(s));
+    return resident_worth_a_look(s) && resident_pays(s, whole, plan);
 }

@@ -1,5 +1,6 @@
 """The choice between the cuts of the gather kernel and the slab kernel against the timings it was made from
-(profiles/cut_sweep.csv: us of every product in every cut).  No GPU."""
+(profiles/cut_sweep.csv: us of every product in every cut); that of the resident slab against
+profiles/resident_sweep.csv, and the bounds that its kernel rests on.  No GPU."""
 import csv
 import ctypes
 import math
@@ -15,13 +16,20 @@ ROWS = {"aligned": 0, "any": 1, "images": 2}
 
 
 @pytest.fixture(scope="module")
-def probe(tmp_path_factory):
+def probes(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("choice") / "choice_probe.so")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
                            os.path.join(ROOT, "paper_2203_05016_amd", "csrc"), os.path.join(HERE, "choice_probe.cpp"), "-o", so])
-    f = ctypes.CDLL(so).probe_choice
-    f.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_long, ctypes.c_long] + [ctypes.c_int] * 5 + [ctypes.c_double, ctypes.c_int]
-    return f
+    L = ctypes.CDLL(so)
+    i, l, d, p = ctypes.c_int, ctypes.c_long, ctypes.c_double, ctypes.c_void_p
+    L.probe_choice.argtypes = [i, l, l, l] + [i] * 5 + [d, i]
+    L.probe_resident.argtypes = [i, l, l, l] + [i] * 5 + [d, i] + [p] * 4
+    return L
+
+
+@pytest.fixture(scope="module")
+def probe(probes):
+    return probes.probe_choice
 
 
 def _choose(probe, V, G, N, steps, K, rows, uneven, f32, slab, kept):
@@ -105,3 +113,65 @@ def test_weights_are_shared_where_the_sweep_says_so(probe):
         print("V %d, %d columns, up to %d steps: %.3f (%d)" % (key + (mean, len(x))))
         if len(x) >= 10:
             assert mean < 1.03, (key, mean)
+
+
+def _rows(name):
+    with open(os.path.join(ROOT, "profiles", name)) as f:
+        return list(csv.DictReader(line for line in f if not line.startswith("#")))
+
+
+def _resident(probes, V, G, N, steps, K, rows, uneven, f32, slab, kept, whole):
+    """(taken, shares of a column tile, wavefronts)"""
+    parts, waves, time, other = ctypes.c_int(), ctypes.c_int(), ctypes.c_double(), ctypes.c_double()
+    taken = probes.probe_resident(V, G, N, steps, K, ROWS[rows], uneven, f32, slab, kept, whole, *map(ctypes.byref, (parts, waves, time, other)))
+    return bool(taken), parts.value, waves.value
+
+
+def _mean(x):
+    return math.exp(sum(map(math.log, x)) / len(x))
+
+
+def _hold(name, times, best_share, mean_taken, slower_4, slower_10):
+    """times: (taken, without, with).  What is taken gains on average, few of it lose, and the choice has its share of all the gain there is."""
+    taken = sorted(b / a for t, a, b in times if t)
+    both = _mean([min(1, b / a) for _, a, b in times])
+    chosen = _mean([b / a if t else 1 for t, a, b in times])
+    lost = [sum(x > limit for x in taken) / len(taken) for limit in (1.04, 1.1)]
+    print("%s: %d of %d taken at %.3f, %.1f %% of them 4 %% slower, %.1f %% 10 %%; over all %.3f, the best of both %.3f" % (
+        name, len(taken), len(times), _mean(taken), 100 * lost[0], 100 * lost[1], chosen, both))
+    assert _mean(taken) < mean_taken and lost[0] < slower_4 and lost[1] < slower_10
+    assert math.log(chosen) < best_share * math.log(both)
+
+
+def test_resident_slab_is_taken_where_it_is_faster(probes):
+    """Single measurements of both sides in turn, by which one kernel's differ up to 4 % in one of a hundred."""
+    times = []
+    for r in _rows("resident_sweep.csv"):
+        taken, _, _ = _resident(probes, int(r["V"]), int(r["G"]), int(r["N"]), int(r["steps"]), int(r["K"]), r["rows"], int(r["uniform"]) < 0,
+                                int(r["f32"]), int(r["slab"]), float(r["kept"]), int(r["whole"]))
+        times.append((r, (taken, float(r["other"]), float(r["resident"]))))
+    assert len(times) > 3000
+    _hold("all", [t for _, t in times], .75, .8, .025, .008)
+    for V in ("16", "32", "64"):
+        _hold("V = " + V, [t for r, t in times if r["V"] == V], .25, .9, .08, .04)   # (V = 64: 4 and 2 of 62)
+    _hold("V = 128, no images", [t for r, t in times if r["V"] == "128" and r["rows"] != "images"], .5, .9, .08, .04)
+
+
+@pytest.mark.parametrize("V", [16, 32, 64, 128])
+def test_plans_of_the_resident_slab_are_within_what_its_kernel_takes(probes, V):
+    """The slab, a row of zeros and a counter in 160 KB of LDS, or in 80 where two workgroups share a CU; loads of the copy for every
+    row; fewer than 2^19 workgroups; a share of the groups for each."""
+    for K in (1, 63, 64, 637, 638, 639, 1277, 1278, 1279, 5000):
+        for G in (1, 3, 4, 5, 33, 256, 1023, 1024, 70000, 1 << 20):
+            for N in (1, 8, 64, 65, 4096, 32704, 32768, 40000, 1 << 20, (1 << 25) - 64, 1 << 25, 1 << 30):
+                steps = G * max(1, K // (64 if V == 16 else 32))
+                plans = [_resident(probes, V, G, N, steps, K, rows, 0, 0, 0, .5, whole) for rows in ROWS for whole in (0, 1)]
+                for taken, parts, waves in plans:
+                    if parts == 0:
+                        assert not taken
+                        continue
+                    items = G * (2 if V == 128 else 1)
+                    assert K <= 1278 and G >= 4 and waves in (8, 16) and (V <= 32 or waves == 8)
+                    assert (K + 1) * 128 + 16 <= (80 if waves == 8 and V <= 32 else 160) * 1024
+                    assert (20 if V >= 64 else 10) * 8 * waves >= K
+                    assert 1 <= parts <= items and -(-N // 64) * parts < 1 << 19
