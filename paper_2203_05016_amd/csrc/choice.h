@@ -257,10 +257,13 @@ inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& pla
 
 // Convolutions in runs of 8 (GeomConvRuns): the rows of the unfolded matrix are gathered once per workgroup instead of once per
 // group, or staged and read in single values.  What decides is how often a row is fetched, groups x kept share.  Estimates
-// from 1900 convolutions (3x3, 32 to 128 channels, 7x7 to 56x56, stride 1 and 2, both layouts): 10 to 17 % off, the resident slab's
-// with the copy at 2.1 (NCHW: at any alignment, moved in registers) and 1.6 times that of aligned rows 9 and 13 % (4.1 times with a stride along x).  Over them
-// taking it where its estimate is 10 % lower takes 0.92 of the time of the other kernels (geometric mean, the best of both 0.91);
-// a third of those of V = 16 and 32 take it, us before / now: 55 images of 18x18, 128 -> 1024
+// from 1900 convolutions (3x3, 32 to 128 channels, 7x7 to 56x56, stride 1 and 2, both layouts): 10 to 30 % off, the resident slab's
+// with the copy at 2.1 (NCHW: at any alignment, moved in registers) and 1.6 times that of aligned rows 9 and 13 % (4.1 times with a stride along x).
+// A gathered row that few groups fetch is where they err: there, and where the alternative to a stride along x is a well filled
+// staged box, the margin is wider.  Of 3873 random ones without a
+// stride along x in NCHW, which nothing was fitted to, 2578 take it, at .59 of the other kernels' time, and 30 of these lose more than 4 %, 13 more than 10 %, up to 45 %; of 1403 with one 571 at .45, 3 lose more than 4 %
+// (profiles/resident_conv_sweep.csv).
+// us before / resident: 55 images of 18x18, 128 -> 1024
 // channels at 50 %, V = 16 147.5 / 55.5, 46 of 41x41, 112 -> 240 143.8 / 63.9, 32 of 28x28, 128 -> 512 at 75 %, V = 32 40.1 / 23.0.
 // V >= 64 gains nothing, and 32-bit results were not measured: neither comes here.
 // NCHW with a stride of two along x (GeomConvRuns2): two loads per run.
@@ -278,7 +281,15 @@ inline bool resident_conv_pays(const CutSizes& s, Runs runs, bool gathered, cons
     const Cost& g = GATHERED[(int)runs][v];
     const double other = gathered ? g.start + tiles * s.G * (s.per * g.step + g.item)
                                   : STAGED[v].start + tiles * (s.G * s.per * STAGED[v].step + s.K * STAGED[v].item);
-    return plan.time < .9 * other;
+    double margin = .9;
+    if (runs == Runs::NCHW_BY_2) {
+        margin = .8;
+    } else if (gathered) {
+        margin = runs == Runs::CHWN && s.V == 32 ? .8 : .85;
+        const double fetches = s.G * s.kept;
+        if (fetches < 2.5) margin *= std::sqrt(fetches / 2.5);
+    }
+    return plan.time < margin * other;
 }
 
 // NCHW convolutions with a stride of two along x are gathered but where a kernel larger than 1x1 has many groups that fetch many rows, which

@@ -32,3 +32,13 @@ extern "C" int probe_resident(int V, long G, long N, long steps, int K, int rows
     *parts = plan.parts; *waves = plan.waves; *time = plan.time; *other = cut_time(s, choose_cut(s));
     return resident_worth_a_look(s) && resident_pays(s, whole, plan);
 }
+
+// A convolution in runs (0: NCHW, 1: CHWN, 2: NCHW with a stride of two) likewise; gathered: what it would be otherwise.
+extern "C" int probe_resident_conv(int V, long G, long N, long steps, int K, int uneven, double kept, int whole, int runs, int gathered,
+                                   int* parts, int* waves, double* time)
+{
+    const CutSizes s = sizes_of(V, G, N, steps, K, 1, uneven, 0, 0, kept);
+    const ResidentPlan plan = plan_resident(s, whole, RESIDENT_COPY_RUNS[runs]);
+    *parts = plan.parts; *waves = plan.waves; *time = plan.time;
+    return resident_conv_worth_a_look(V, K, s.tiles()) && resident_conv_pays(s, (Runs)runs, gathered, plan);
+}

@@ -1,6 +1,6 @@
 """The choice between the cuts of the gather kernel and the slab kernel against the timings it was made from
 (profiles/cut_sweep.csv: us of every product in every cut); that of the resident slab against
-profiles/resident_sweep.csv, and the bounds that its kernel rests on.  No GPU."""
+profiles/resident_sweep.csv and resident_conv_sweep.csv, and the bounds that its kernel rests on.  No GPU."""
 import csv
 import ctypes
 import math
@@ -24,6 +24,7 @@ def probes(tmp_path_factory):
     i, l, d, p = ctypes.c_int, ctypes.c_long, ctypes.c_double, ctypes.c_void_p
     L.probe_choice.argtypes = [i, l, l, l] + [i] * 5 + [d, i]
     L.probe_resident.argtypes = [i, l, l, l] + [i] * 5 + [d, i] + [p] * 4
+    L.probe_resident_conv.argtypes = [i, l, l, l, i, i, d, i, i, i] + [p] * 3
     return L
 
 
@@ -127,6 +128,12 @@ def _resident(probes, V, G, N, steps, K, rows, uneven, f32, slab, kept, whole):
     return bool(taken), parts.value, waves.value
 
 
+def _resident_conv(probes, V, G, N, steps, K, uneven, kept, whole, runs, gathered):
+    parts, waves, time = ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
+    taken = probes.probe_resident_conv(V, G, N, steps, K, uneven, kept, whole, runs, gathered, *map(ctypes.byref, (parts, waves, time)))
+    return bool(taken), parts.value, waves.value
+
+
 def _mean(x):
     return math.exp(sum(map(math.log, x)) / len(x))
 
@@ -157,6 +164,17 @@ def test_resident_slab_is_taken_where_it_is_faster(probes):
     _hold("V = 128, no images", [t for r, t in times if r["V"] == "128" and r["rows"] != "images"], .5, .9, .08, .04)
 
 
+def test_resident_slab_is_taken_by_convolutions_where_it_is_faster(probes):
+    RUNS = {"nchw": 0, "chwn": 1, "nchw_by_2": 2}
+    times = []
+    for r in _rows("resident_conv_sweep.csv"):
+        taken, _, _ = _resident_conv(probes, int(r["V"]), int(r["G"]), int(r["N"]), int(r["steps"]), int(r["K"]), int(r["uniform"]) < 0,
+                                     float(r["kept"]), int(r["whole"]), RUNS[r["runs"]], int(r["gathered"]))
+        times.append((r, (taken, float(r["other"]), float(r["resident"]))))
+    for runs in RUNS:
+        _hold(runs, [t for r, t in times if r["runs"] == runs], .6, .75, .04, .025)
+
+
 @pytest.mark.parametrize("V", [16, 32, 64, 128])
 def test_plans_of_the_resident_slab_are_within_what_its_kernel_takes(probes, V):
     """The slab, a row of zeros and a counter in 160 KB of LDS, or in 80 where two workgroups share a CU; loads of the copy for every
@@ -166,6 +184,8 @@ def test_plans_of_the_resident_slab_are_within_what_its_kernel_takes(probes, V):
             for N in (1, 8, 64, 65, 4096, 32704, 32768, 40000, 1 << 20, (1 << 25) - 64, 1 << 25, 1 << 30):
                 steps = G * max(1, K // (64 if V == 16 else 32))
                 plans = [_resident(probes, V, G, N, steps, K, rows, 0, 0, 0, .5, whole) for rows in ROWS for whole in (0, 1)]
+                if V <= 32:
+                    plans += [_resident_conv(probes, V, G, N, steps, K, 0, .5, 0, runs, 1) for runs in (0, 1, 2)]
                 for taken, parts, waves in plans:
                     if parts == 0:
                         assert not taken
