@@ -733,13 +733,15 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         g.stream = streams;
         return true;
     };
+    GeomConvRuns2 by2;
+    bool strided = false;   // by2 holds the convolution, of no more groups than the gather kernel's grid has rows (the staged kernel takes more)
+    const auto gather_strided = [&] { return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st); };
     if (((A->tune_kernel == 0 && A->tune_tile_n == 0) || resident_only) && ydtype != SHFLBW_F32) {
         const auto fill = [&](auto& g, int step) {
             return fill_conv_runs(A, g, in, out, batch, C_in, H, W, R, S, stride_h, stride_w, pad_h, pad_w, Ho, Wo, 2 * (int64_t)batch * C_in * H * W, 2, step);
         };
         GeomConvRuns<true> chwn;
         GeomConvRuns<false> nchw;
-        GeomConvRuns2 by2;
         // (before the geometry is worked out: runs fill at most twice the columns)
         const bool look = resident_only || resident_conv_worth_a_look(A->V, A->K, (N / 32 + 1) * A->G);
         if (layout == SHFLBW_CHWN) {
@@ -747,9 +749,9 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         } else if (stride_w == 2) {
             if (fill(static_cast<GeomConvRuns<false>&>(by2), 2)) {
                 if (try_resident_runs(by2, Runs::NCHW_BY_2)) return status;
-                // (the gather kernel's grid has a row per group; the staged kernel takes more of them)
-                if (!resident_only && A->G <= GATHER_MAX_GROUPS && strided_runs_pay(A->V, A->G, R * S, kept))
-                    return A->dtype == SHFLBW_BF16 ? run_gather_bf16(A, by2, by2.N, st) : run_gather_f16(A, by2, by2.N, st);
+                strided = A->G <= GATHER_MAX_GROUPS;
+                if (!resident_only && strided && strided_runs_pay(A->V, A->G, R * S, kept, (double)((by2.N + 63) / 64) * A->total_steps()))
+                    return gather_strided();
             }
         } else if (look && fill(nchw, 1) && try_resident_runs(nchw, Runs::NCHW)) {
             return status;
@@ -789,6 +791,7 @@ int shflbw_conv2d(const shflbw_matrix* A, const void* in, void* out, int batch, 
         // beyond the LDS the element-wise geometry is hundreds of times dearer than the runs (8 images of 14x14,
         // 2048 -> 128 channels, 3x3, unpruned, V = 32: 3400 us / 64)
         if (!runs_pay && try_runs(&status)) return status;
+        if (strided) return gather_strided();
     }
     GeomConv g;
     g.in = static_cast<const _Float16*>(in);

@@ -292,13 +292,20 @@ inline bool resident_conv_pays(const CutSizes& s, Runs runs, bool gathered, cons
     return plan.time < margin * other;
 }
 
-// NCHW convolutions with a stride of two along x are gathered but where a kernel larger than 1x1 has many groups that fetch many rows, which
-// staging reads once.  2650 random ones (1x1 and 3x3, 64 to 2048 channels, 15x15 to 58x58, 16-bit results): 0.57 of the time of the
-// staged kernel, geometric mean, 1 % of them more than 4 % slower; gathered always 0.57, 4 % slower, up to 4 times (V = 16, 37
-// images of 28x28, 256 -> 560 channels at 50 % 106 staged, 429 gathered).
-inline bool strided_runs_pay(int V, int G, int taps, double kept)
+// NCHW convolutions with a stride of two along x are gathered but where a kernel larger than 1x1 has groups that fetch many rows, which
+// staging reads once; work: tiles x k-steps, small where most CUs would idle on the staged kernel's boxes.  1x1 layers only go back where most
+// is kept.  Of 4164 random ones (1x1 and 3x3, 8 to 60 columns, 16-bit results) that nothing was fitted to 2898 are gathered, at .57 of the staged kernel's time, and 20 of these lose
+// more than 4 %, up to 36 %; of 2287 dear ones 857 at .65, 20 lose as much, up to 45 % (profiles/strided_sweep.csv holds those that the limits came from).
+// Where it does not hold: 52 images of 35x35, 220 -> 896 channels at 50 %, V = 64 107 us staged, 289 gathered; 37 of 28x28, 256 -> 560,
+// V = 16 106 and 429; 19 of 34x33, 231 -> 64 at 30 %, V = 16 19.3 and 37.8; where it does: 37 of 29x29, 241 -> 832 at 85 %, V = 64 45.6 and 25.5.
+inline bool strided_runs_pay(int V, long G, int taps, double kept, double work)
 {
-    return taps == 1 || V == 64 || G * kept < (V <= 32 ? 3 : 2.5);
+    const double fetches = G * kept;
+    if (taps == 1) return V == 128 || kept < (V == 32 ? .81 : .61) || work < (V == 16 ? 6000 : V == 32 ? 8000 : 48000);
+    if (V == 16) return fetches < 3 && (kept < .21 || work < 4000);
+    if (V == 32) return fetches < (work < 8000 ? 3 : 1.5);
+    if (V == 64) return fetches < 1.2 || work < 12000;
+    return fetches < 2.5;
 }
 
 }  // namespace shflbw

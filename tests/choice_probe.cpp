@@ -42,3 +42,6 @@ extern "C" int probe_resident_conv(int V, long G, long N, long steps, int K, int
     *parts = plan.parts; *waves = plan.waves; *time = plan.time;
     return resident_conv_worth_a_look(V, K, s.tiles()) && resident_conv_pays(s, (Runs)runs, gathered, plan);
 }
+
+// Whether a strided convolution in NCHW is gathered.
+extern "C" int probe_strided(int V, long G, int taps, double kept, double work) { return strided_runs_pay(V, G, taps, kept, work); }

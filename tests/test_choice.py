@@ -1,6 +1,6 @@
 """The choice between the cuts of the gather kernel and the slab kernel against the timings it was made from
-(profiles/cut_sweep.csv: us of every product in every cut); that of the resident slab against
-profiles/resident_sweep.csv and resident_conv_sweep.csv, and the bounds that its kernel rests on.  No GPU."""
+(profiles/cut_sweep.csv: us of every product in every cut); that of the resident slab and of the strided gather against theirs
+(profiles/resident_sweep.csv, resident_conv_sweep.csv, strided_sweep.csv), and the bounds that their kernels rest on.  No GPU."""
 import csv
 import ctypes
 import math
@@ -25,6 +25,7 @@ def probes(tmp_path_factory):
     L.probe_choice.argtypes = [i, l, l, l] + [i] * 5 + [d, i]
     L.probe_resident.argtypes = [i, l, l, l] + [i] * 5 + [d, i] + [p] * 4
     L.probe_resident_conv.argtypes = [i, l, l, l, i, i, d, i, i, i] + [p] * 3
+    L.probe_strided.argtypes = [i, l, i, d, d]
     return L
 
 
@@ -173,6 +174,18 @@ def test_resident_slab_is_taken_by_convolutions_where_it_is_faster(probes):
         times.append((r, (taken, float(r["other"]), float(r["resident"]))))
     for runs in RUNS:
         _hold(runs, [t for r, t in times if r["runs"] == runs], .6, .75, .04, .025)
+
+
+def test_strided_convolutions_are_gathered_where_it_is_faster(probes):
+    """Of the dear ones two thirds are drawn, so more lose here than of all."""
+    times = []
+    for r in _rows("strided_sweep.csv"):
+        work = -(-int(r["N"]) // 64) * int(r["steps"])
+        times.append((r, (bool(probes.probe_strided(int(r["V"]), int(r["G"]), int(r["taps"]), float(r["kept"]), work)),
+                          float(r["staged"]), float(r["gathered"]))))
+    _hold("all", [t for _, t in times], .75, .65, .03, .015)
+    for V in ("16", "32", "64", "128"):
+        _hold("V = " + V, [t for r, t in times if r["V"] == V], .7, .7, .04, .02)
 
 
 @pytest.mark.parametrize("V", [16, 32, 64, 128])

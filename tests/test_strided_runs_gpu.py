@@ -27,6 +27,10 @@ pytestmark = pytest.mark.gpu
     (32, 32, 400, 33, 34, 2048, 1, 1, 2, 0, 0.3, "resident"),
     (16, 32, 64, 40, 17, 1024, 3, 3, 2, 1, 0.3, "resident"),
     (32, 16, 256, 28, 28, 512, 3, 3, 2, 1, 0.5, "conv"),     # too long to be resident, many groups that fetch much: staged
+    (64, 6, 120, 39, 39, 512, 3, 3, 2, 1, 0.3, "conv"),      # the same for groups of 64
+    (16, 6, 220, 34, 33, 64, 3, 3, 2, 1, 0.3, "conv"),       # few groups of 16 that keep most of a row
+    (32, 12, 512, 33, 33, 160, 1, 1, 2, 0, 0.0, "conv"),      # 1x1, unpruned
+    (16, 1, 1700, 17, 17, 64, 3, 3, 2, 1, 0.0, "gather"),    # would be staged, if a box of 1700 channels fitted the LDS
 ])
 def test_stride_two_exact(V, batch, C, H, W, M, R, S, stride_h, pad, sparsity, kernel, fmt):
     import torch
