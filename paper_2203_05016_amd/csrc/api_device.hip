@@ -118,6 +118,14 @@ int dispatch_out(const shflbw_matrix* A, const Geom& geom, long N, shflbw_dtype 
     return run_gather_f16(A, geom, N, ydtype, stream);
 }
 
+// The same for linear layers' geometries; cut: their choose_cut where it is known already, else -1.
+template <class Geom>
+int dispatch_linear(const shflbw_matrix* A, const Geom& geom, long N, shflbw_dtype ydtype, hipStream_t stream, int cut)
+{
+    if (A->dtype == SHFLBW_BF16) return run_gather_bf16(A, geom, N, ydtype, stream, cut);
+    return run_gather_f16(A, geom, N, ydtype, stream, cut);
+}
+
 // what stream_stores calls reads
 double reads_of(const shflbw_matrix* A) { return (double)A->nnz / ((double)A->M * A->V); }
 
@@ -129,9 +137,9 @@ int no_resident()
 }
 
 // The slab kernel with a resident slab, where it applies, and pays or is forced: rc is the launch's status.  yelems: from Y's start to
-// its end, in elements.
+// its end, in elements.  cut: the best cut of the other kernels where it was looked for, else untouched.
 template <class Geom>
-bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, int64_t yelems, shflbw_dtype ydtype, hipStream_t stream, int* rc)
+bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, int64_t yelems, shflbw_dtype ydtype, hipStream_t stream, int* rc, int* cut)
 {
     const bool forced = A->tune_kernel == 4;
     if (!forced && (A->tune_kernel != 0 || A->tune_tile_n != 0 || A->K > RESIDENT_K)) return false;
@@ -146,7 +154,11 @@ bool try_resident(const shflbw_matrix* A, const Geom& geom, long N, Rows rows, i
     const CutSizes sizes = cut_sizes(A, N, rows, ydtype == SHFLBW_F32);
     if (!forced && !resident_worth_a_look(sizes)) return false;
     const ResidentPlan plan = plan_resident(sizes, whole, rows == Rows::ALIGNED ? 1 : RESIDENT_COPY_UNALIGNED);
-    if (plan.parts <= 0 || (!forced && !resident_pays(sizes, whole, plan))) return false;
+    if (plan.parts <= 0) return false;
+    if (!forced) {
+        *cut = choose_cut(sizes);
+        if (!resident_pays(sizes, (Cut)*cut, whole, plan)) return false;
+    }
     Geom g = geom;
     g.stream = whole;
     *rc = A->dtype == SHFLBW_BF16 ? run_resident_bf16(A, g, N, plan, (unsigned)ybytes, ydtype, stream)
@@ -169,11 +181,11 @@ int run_rows(const shflbw_matrix* A, const void* X, int64_t ldx, int64_t x_image
     const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
     g.stream = stream_stores(Y, ldy * ob, ob, (double)xbytes, (double)A->M * P * images * ob, reads_of(A), images > 1);
     g.N = (long)images * g.slots * 8;
-    int rc = SHFLBW_OK;
-    if (try_resident(A, g, g.N, images > 1 ? Rows::IMAGES : Rows::ANY, (images - 1) * y_image + (A->M - 1) * ldy + P, ydtype, stream, &rc))
+    int rc = SHFLBW_OK, cut = -1;
+    if (try_resident(A, g, g.N, images > 1 ? Rows::IMAGES : Rows::ANY, (images - 1) * y_image + (A->M - 1) * ldy + P, ydtype, stream, &rc, &cut))
         return rc;
     if (A->tune_kernel == 4) return no_resident();
-    return dispatch_out(A, g, g.N, ydtype, stream);
+    return dispatch_linear(A, g, g.N, ydtype, stream, cut);
 }
 
 // ydtype must be the operand format of the matrix or fp32
@@ -528,21 +540,25 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
     // X behind a buffer descriptor where 24-bit offset arithmetic and a 32-bit range cover it
     const int64_t xbytes = ((int64_t)A->K - 1) * ldx * 2 + N * 2;
     const bool described = A->K < (1 << 24) && ldx * 2 < (1 << 24) && xbytes + 2 * ldx * 2 < ((int64_t)1 << 32) - 64;
+    int cut = -1;   // choose_cut's answer, once it is known
     GeomLinearBuf g;
     if (aligned && described) {
         g.X = static_cast<const _Float16*>(X);
         g.Y = Y;
         g.ldx = (long)ldx; g.ldy = (long)ldy; g.N = (long)N;
         g.xbytes = (unsigned)xbytes;
-        if (try_resident(A, g, (long)N, Rows::ALIGNED, (A->M - 1) * ldy + N, ydtype, st, &rc)) return rc;
+        if (try_resident(A, g, (long)N, Rows::ALIGNED, (A->M - 1) * ldy + N, ydtype, st, &rc, &cut)) return rc;
     }
     if (A->tune_kernel == 4 && (aligned || !described || N < 8)) return no_resident();   // (the others: run_rows)
     bool use_slab = A->tune_kernel == 2;
     if (A->tune_kernel == 0 && slab_possible) {
         // the slab kernel streams all of X whatever the sparsity and its workgroup's groups share it: it pays where
         // enough of each chunk is used, sooner where a gathered byte serves few rows (V = 16, 32)
-        const CutSizes sizes = cut_sizes(A, (long)N, Rows::ALIGNED, ydtype == SHFLBW_F32);
-        use_slab = slab_considered(sizes) && choose_cut(sizes) == SLAB;
+        if (cut < 0) {
+            const CutSizes sizes = cut_sizes(A, (long)N, Rows::ALIGNED, ydtype == SHFLBW_F32);
+            if (slab_considered(sizes)) cut = choose_cut(sizes);
+        }
+        use_slab = cut == SLAB;
     }
     if (use_slab) {
         if (A->dtype == SHFLBW_BF16) {
@@ -558,7 +574,7 @@ int shflbw_spmm(const shflbw_matrix* A, const void* X, int64_t ldx, void* Y, int
         if (described) {
             const int ob = ydtype == SHFLBW_F32 ? 4 : 2;
             g.stream = stream_stores(Y, ldy * ob, ob, 2.0 * A->K * N, (double)ob * A->M * N, reads_of(A));
-            return dispatch_out(A, g, (long)N, ydtype, st);
+            return dispatch_linear(A, g, (long)N, ydtype, st, cut);
         }
         GeomLinear<true> wide{static_cast<const _Float16*>(X), Y, (long)ldx, (long)ldy, (long)N};
         return dispatch_out(A, wide, (long)N, ydtype, st);

@@ -242,7 +242,8 @@ constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
 // and the estimates cost a call of 3 us 0.1.
 inline bool resident_worth_a_look(const CutSizes& s) { return s.K <= RESIDENT_K && s.tiles() >= 1024; }
 inline bool resident_conv_worth_a_look(int V, int K, long tiles) { return V <= 32 && K <= RESIDENT_K && tiles >= 512; }
-inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& plan)
+// cut: choose_cut(s)
+inline bool resident_pays(const CutSizes& s, Cut cut, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
     // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few; then the same of images.  0: never.
@@ -252,7 +253,7 @@ inline bool resident_pays(const CutSizes& s, bool whole, const ResidentPlan& pla
     double margin = MARGINS[s.v()][(s.rows == Rows::IMAGES ? 4 : 0) + (whole ? 2 : 0) + few];
     const double work = (double)s.tiles() * s.per;
     if (few && s.V < 128 && work < 12000) margin *= std::sqrt(std::sqrt(work / 12000));
-    return plan.time < margin * cut_time(s, choose_cut(s));
+    return plan.time < margin * cut_time(s, cut);
 }
 
 // Convolutions in runs of 8 (GeomConvRuns): the rows of the unfolded matrix are gathered once per workgroup instead of once per

@@ -28,19 +28,19 @@ inline CutSizes cut_sizes(const shflbw_matrix* A, long N, Rows rows, bool f32)
 }
 
 int run_gather_f16(const shflbw_matrix* A, const GeomLinear<true>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
-int run_gather_f16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, shflbw_dtype ydtype, hipStream_t stream);
+int run_gather_f16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, shflbw_dtype ydtype, hipStream_t stream, int cut);
 int run_gather_f16(const shflbw_matrix* A, const GeomLinear<false>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_f16(const shflbw_matrix* A, const GeomConv& g, long N, shflbw_dtype ydtype, hipStream_t stream);
-int run_gather_f16(const shflbw_matrix* A, const GeomRows& g, long N, shflbw_dtype ydtype, hipStream_t stream);
+int run_gather_f16(const shflbw_matrix* A, const GeomRows& g, long N, shflbw_dtype ydtype, hipStream_t stream, int cut);
 int run_gather_f16(const shflbw_matrix* A, const GeomNarrow& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_f16(const shflbw_matrix* A, const GeomQuads& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_f16(const shflbw_matrix* A, const GeomConvRuns<false>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_f16(const shflbw_matrix* A, const GeomConvRuns<true>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_bf16(const shflbw_matrix* A, const GeomLinear<true>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
-int run_gather_bf16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, shflbw_dtype ydtype, hipStream_t stream);
+int run_gather_bf16(const shflbw_matrix* A, const GeomLinearBuf& g, long N, shflbw_dtype ydtype, hipStream_t stream, int cut);
 int run_gather_bf16(const shflbw_matrix* A, const GeomLinear<false>& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_bf16(const shflbw_matrix* A, const GeomConv& g, long N, shflbw_dtype ydtype, hipStream_t stream);
-int run_gather_bf16(const shflbw_matrix* A, const GeomRows& g, long N, shflbw_dtype ydtype, hipStream_t stream);
+int run_gather_bf16(const shflbw_matrix* A, const GeomRows& g, long N, shflbw_dtype ydtype, hipStream_t stream, int cut);
 int run_gather_bf16(const shflbw_matrix* A, const GeomNarrow& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_bf16(const shflbw_matrix* A, const GeomQuads& g, long N, shflbw_dtype ydtype, hipStream_t stream);
 int run_gather_bf16(const shflbw_matrix* A, const GeomConvRuns<false>& g, long N, shflbw_dtype ydtype, hipStream_t stream);

@@ -29,8 +29,9 @@ extern "C" int probe_resident(int V, long G, long N, long steps, int K, int rows
 {
     const CutSizes s = sizes_of(V, G, N, steps, K, rows, uneven, f32, slab, kept);
     const ResidentPlan plan = plan_resident(s, whole, rows == 0 ? 1 : RESIDENT_COPY_UNALIGNED);
-    *parts = plan.parts; *waves = plan.waves; *time = plan.time; *other = cut_time(s, choose_cut(s));
-    return resident_worth_a_look(s) && resident_pays(s, whole, plan);
+    const Cut cut = choose_cut(s);
+    *parts = plan.parts; *waves = plan.waves; *time = plan.time; *other = cut_time(s, cut);
+    return resident_worth_a_look(s) && resident_pays(s, cut, whole, plan);
 }
 
 // A convolution in runs (0: NCHW, 1: CHWN, 2: NCHW with a stride of two) likewise; gathered: what it would be otherwise.
