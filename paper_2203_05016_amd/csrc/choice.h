@@ -1,4 +1,5 @@
-// Which kernel a linear layer takes and how its work is cut, from sizes alone.  Host code without HIP.
+// Which kernel a linear layer, a convolution in runs and a LayerNorm-side transposition take and how their work is cut, from sizes alone.
+// Host code without HIP.
 #pragma once
 
 #include <cmath>
@@ -307,6 +308,62 @@ inline bool strided_runs_pay(int V, long G, int taps, double kept, double work)
     if (V == 32) return fetches < (work < 8000 ? 3 : 1.5);
     if (V == 64) return fetches < 1.2 || work < 12000;
     return fetches < 2.5;
+}
+
+// The LayerNorm-side transposition's kernels (layernorm_transpose.hip).  FEW: blocks of 16 or 8 tokens whose features several workgroups share; RESIDENT: 32 or
+// 64 tokens with all their features in the LDS; REGISTER: 32 tokens, 4096 features at a time in registers; STREAM: 64 tokens, any number of features.
+enum class Ln { FEW, RESIDENT, REGISTER, STREAM };
+struct LnChoice { Ln kernel; int tokens; };
+
+// RESIDENT: bytes of LDS for `tokens` tokens, and their pitch in 16-bit units, (pitch / 2) mod 8 as the kernel wants it
+inline long ln_resident_bytes(int tokens, int K, int& pitch)
+{
+    const int want = tokens == 32 ? 2 : 1;
+    int pad = 0;
+    while (((K + pad) / 2) % 8 != want) pad += 2;
+    pitch = K + pad;
+    return (long)tokens * pitch * 2 + 2L * tokens * 4 + 2L * K * 4;
+}
+
+// Few tokens: 16 at a time (up to 2048 features) or 8, the features shared by about 128 workgroups (up to 256 for more
+// than 64 blocks of 8; twice as many cost what their reads of the same rows take).  us by the other kernels / this one: 64 tokens of
+// 256 features 4.1 / 3.7, 1024 5.5 / 3.9, 2048 7.8 / 4.5, 4096 8.3 / 5.1, 16 384 16.5 / 9.4; 552 tokens of 1024
+// 5.9 / 4.3, 2048 8.3 / 5.3, 3584 10.2 / 6.8, 8192 14.5 / 12.3, 16 384 25.0 / 19.5; 2048 of 1024 5.9 / 5.2, of 2048
+// 8.3 / 7.3; 4096 of 1024 6.6 / 6.2; but 4096 of 1600 8.3 / 9.2, 1024 of 4096 8.7 / 9.3, of 8192 13.3 / 15.5, of 16 384 23.3 / 27.3.
+// Blocks of 32 tokens (64-byte row segments, two workgroups per CU) are faster than of 64 while input
+// and output together stay well inside the 256 MB memory-side cache, where the halves of a
+// line still meet; beyond that the 128-byte segments of 64-token blocks win (measured:
+// 26 against 27 us at 134 MB, 53 against 44 us at 201 MB).
+inline LnChoice choose_layernorm(long N, int K, bool normalize)
+{
+    if (normalize && K <= 16384 && N <= (K <= 1024 ? 4096 : K <= 2048 ? 2048 : 768)) return {Ln::FEW, K <= 2048 ? 16 : 8};
+    constexpr long LDS_CAP = 160 * 1024 - 256;
+    int pitch = 0;
+    if (4.0 * (double)N * (double)K > 160e6 && ln_resident_bytes(64, K, pitch) <= LDS_CAP) return {Ln::RESIDENT, 64};
+    if (ln_resident_bytes(32, K, pitch) <= LDS_CAP) return {Ln::RESIDENT, 32};
+    if (K <= 16384) return {Ln::REGISTER, 32};
+    return {Ln::STREAM, 64};
+}
+
+// REGISTER: workgroups that share a token block.
+// Few tokens: the 1024-feature slices of a token block are shared by several workgroups, each of which takes the
+// statistics for itself (its reads of the other slices come from the L2), as long as there is at
+// most one workgroup per CU.  One workgroup per 32 tokens leaves most CUs idle: 848 tokens of 5800
+// features 22.5 -> 16.1 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
+// 15.0 -> 10.1.  (Up to 768 tokens do not come here with a LayerNorm, above.)
+// With a LayerNorm every share reads all slices first: worth it when that at least halves what is left to each
+// (us one / shared: 4000 tokens of 3000 features, 2 of 3 slices each, 12.4 / 14.2; of 5120, 3 of 5, 24.2 / 24.8;
+// 4096 of 4096, 2 of 4, 14.9 / 13.4).  Nor by two where a token has more than 8 slices and the output rows are
+// whole 64-byte blocks (stream; 4096 tokens of 16 384 features 69.5 / 71.8, transposed only 45 / 48; of 8192, 33.6 / 34.0
+// and 24.0 / 22.4)
+inline int ln_register_shares(long N, int K, bool normalize, bool stream)
+{
+    const long blocks = (N + 31) / 32;
+    const int slices = (K + 1023) / 1024;
+    int shares = blocks > 0 && blocks < 256 ? (int)(256 / blocks) : 1;
+    if (shares > slices) shares = slices;
+    if ((normalize && 2 * ((slices + shares - 1) / shares) > slices) || (stream && slices > 8 && shares < 3)) shares = 1;
+    return shares;
 }
 
 }  // namespace shflbw

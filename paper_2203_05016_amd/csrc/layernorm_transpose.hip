@@ -31,6 +31,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "choice.h"
 #include "shflbw.h"
 #include "shflbw_internal.h"
 
@@ -827,13 +828,9 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
     a.normalize = normalize ? 1 : 0;
     a.stream = ((uintptr_t)(ldo * 2) | reinterpret_cast<uintptr_t>(out)) % 64 == 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Few tokens: 16 at a time (up to 2048 features) or 8, the features shared by about 128 workgroups (up to 256 for more
-    // than 64 blocks of 8; twice as many cost what their reads of the same rows take).  us by the other kernels / this one: 64 tokens of
-    // 256 features 4.1 / 3.7, 1024 5.5 / 3.9, 2048 7.8 / 4.5, 4096 8.3 / 5.1, 16 384 16.5 / 9.4; 552 tokens of 1024
-    // 5.9 / 4.3, 2048 8.3 / 5.3, 3584 10.2 / 6.8, 8192 14.5 / 12.3, 16 384 25.0 / 19.5; 2048 of 1024 5.9 / 5.2, of 2048
-    // 8.3 / 7.3; 4096 of 1024 6.6 / 6.2; but 4096 of 1600 8.3 / 9.2, 1024 of 4096 8.7 / 9.3, of 8192 13.3 / 15.5, of 16 384 23.3 / 27.3.
-    if (a.normalize && K <= 16384 && N <= (K <= 1024 ? 4096 : K <= 2048 ? 2048 : 768)) {
-        const int few_tok = K <= 2048 ? 16 : 8;
+    const LnChoice choice = choose_layernorm(a.N, K, a.normalize != 0);
+    if (choice.kernel == Ln::FEW) {
+        const int few_tok = choice.tokens;
         LnFew f;
         f.blocks = (int)((N + few_tok - 1) / few_tok);
         int shares = (few_tok == 8 && f.blocks > 64 ? 256 : 128) / f.blocks;
@@ -864,26 +861,10 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(el));
         return SHFLBW_OK;
     }
-    // LDS-resident variant when a block of tokens with all its features fits
-    auto resident_bytes = [&](int tok, int& pitch) {
-        const int want = tok == 32 ? 2 : 1;             // (pitch / 2) mod 8, see the kernel
-        int pad = 0;
-        while (((K + pad) / 2) % 8 != want) pad += 2;
-        pitch = K + pad;
-        return (size_t)tok * pitch * 2 + 2 * (size_t)tok * 4 + 2 * (size_t)K * 4;
-    };
-    const size_t lds_cap = 160 * 1024 - 256;
-    int pitch = 0;
-    int tok = 0;
-    // Blocks of 32 tokens (64-byte row segments, two workgroups per CU) are faster while input
-    // and output together stay well inside the 256 MB memory-side cache, where the halves of a
-    // line still meet; beyond that the 128-byte segments of 64-token blocks win (measured:
-    // 26 against 27 us at 134 MB, 53 against 44 us at 201 MB).
-    const bool big = 4.0 * (double)N * (double)K > 160e6;
-    if (big && resident_bytes(64, pitch) <= lds_cap) tok = 64;
-    else if (resident_bytes(32, pitch) <= lds_cap) tok = 32;
-    if (tok) {
-        const size_t bytes = resident_bytes(tok, pitch);
+    if (choice.kernel == Ln::RESIDENT) {
+        const int tok = choice.tokens;
+        int pitch = 0;
+        const size_t bytes = (size_t)ln_resident_bytes(tok, K, pitch);
         const int64_t rwgs = (N + tok - 1) / tok;
         if (rwgs > 0x7fffffffLL) return fail(SHFLBW_ERR_BAD_SHAPE, "grid too large");
         typedef void (*resident_fn)(LnArgs, int);
@@ -909,9 +890,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         if (el != hipSuccess) return fail(SHFLBW_ERR_HIP, "kernel launch: %s", hipGetErrorString(el));
         return SHFLBW_OK;
     }
-    if (K <= 16384) {
-        // too wide for the LDS, narrow enough to go through the registers of sixteen wavefronts
-        // in at most four parts
+    if (choice.kernel == Ln::REGISTER) {
         typedef void (*register_fn)(LnArgs);
 #define SHFLBW_LN_REG(P, S) \
     &layernorm_transpose_register_kernel<false, false, P, S>, &layernorm_transpose_register_kernel<false, true, P, S>, \
@@ -923,20 +902,7 @@ extern "C" int shflbw_layernorm_transpose(const void* x, int64_t ldx, const void
         const int parts = (K + 4095) / 4096;
         const int64_t rwgs = (N + 31) / 32;
         if (rwgs > 0x7fffffffLL) return fail(SHFLBW_ERR_BAD_SHAPE, "grid too large");
-        // Few tokens: the slices of a token block are shared by several workgroups, each of which takes the
-        // statistics for itself (its reads of the other slices come from the L2), as long as there is at
-        // most one workgroup per CU.  One workgroup per 32 tokens leaves most CUs idle: 848 tokens of 5800
-        // features 22.5 -> 16.1 us, 1600 of 13 152 47.9 -> 37.0 us, 2048 of 4096
-        // 15.0 -> 10.1.  (Up to 768 tokens do not come here with a LayerNorm, above.)
-        const int slices = (K + 1023) / 1024;
-        int shares = rwgs > 0 && rwgs < 256 ? (int)(256 / rwgs) : 1;
-        if (shares > slices) shares = slices;
-        // with a LayerNorm every share reads all slices first: worth it when that at least halves what is left to each
-        // (us one / shared: 4000 tokens of 3000 features, 2 of 3 slices each, 12.4 / 14.2; of 5120, 3 of 5, 24.2 / 24.8;
-        // 4096 of 4096, 2 of 4, 14.9 / 13.4).  Nor by two where a token has more than 8 slices and the output rows are
-        // whole 64-byte blocks (4096 tokens of 16 384 features 69.5 / 71.8, transposed only 45 / 48; of 8192, 33.6 / 34.0
-        // and 24.0 / 22.4)
-        if ((a.normalize && 2 * ((slices + shares - 1) / shares) > slices) || (a.stream && slices > 8 && shares < 3)) shares = 1;
+        const int slices = (K + 1023) / 1024, shares = ln_register_shares(a.N, K, a.normalize != 0, a.stream != 0);
         a.slices_per_wg = (slices + shares - 1) / shares;
         const unsigned ry = (unsigned)((slices + a.slices_per_wg - 1) / a.slices_per_wg);
         const int which = (ry > 1 ? 16 : 0) + (parts - 1) * 4 + (dtype == SHFLBW_BF16 ? 2 : 0) + (a.normalize ? 1 : 0);

@@ -46,3 +46,14 @@ extern "C" int probe_resident_conv(int V, long G, long N, long steps, int K, int
 
 // Whether a strided convolution in NCHW is gathered.
 extern "C" int probe_strided(int V, long G, int taps, double kept, double work) { return strided_runs_pay(V, G, taps, kept, work); }
+
+// The LayerNorm-side transposition: its kernel; the tokens of a workgroup, the workgroups that share them (register kernel), bytes of LDS (resident kernel).
+extern "C" int probe_layernorm(long N, int K, int normalize, int stream, int* tokens, int* shares, long* bytes)
+{
+    const LnChoice c = choose_layernorm(N, K, normalize);
+    int pitch = 0;
+    *tokens = c.tokens;
+    *shares = c.kernel == Ln::REGISTER ? ln_register_shares(N, K, normalize, stream) : 1;
+    *bytes = c.kernel == Ln::RESIDENT ? ln_resident_bytes(c.tokens, K, pitch) : 0;
+    return (int)c.kernel;
+}

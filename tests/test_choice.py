@@ -1,6 +1,7 @@
 """The choice between the cuts of the gather kernel and the slab kernel against the timings it was made from
 (profiles/cut_sweep.csv: us of every product in every cut); that of the resident slab and of the strided gather against theirs
-(profiles/resident_sweep.csv, resident_conv_sweep.csv, strided_sweep.csv), and the bounds that their kernels rest on.  No GPU."""
+(profiles/resident_sweep.csv, resident_conv_sweep.csv, strided_sweep.csv), and the bounds that their kernels rest on; which kernels the
+LayerNorm tests reach.  No GPU."""
 import csv
 import ctypes
 import math
@@ -26,6 +27,7 @@ def probes(tmp_path_factory):
     L.probe_resident.argtypes = [i, l, l, l] + [i] * 5 + [d, i] + [p] * 4
     L.probe_resident_conv.argtypes = [i, l, l, l, i, i, d, i, i, i] + [p] * 3
     L.probe_strided.argtypes = [i, l, i, d, d]
+    L.probe_layernorm.argtypes = [l, i, i, i] + [p] * 3
     return L
 
 
@@ -208,3 +210,24 @@ def test_plans_of_the_resident_slab_are_within_what_its_kernel_takes(probes, V):
                     assert (K + 1) * 128 + 16 <= (80 if waves == 8 and V <= 32 else 160) * 1024
                     assert (20 if V >= 64 else 10) * 8 * waves >= K
                     assert 1 <= parts <= items and -(-N // 64) * parts < 1 << 19
+
+
+def test_layernorm_tests_reach_every_kernel(probes):
+    from test_layernorm_few_gpu import SHAPES as few
+    from test_layernorm_gpu import HARD_SHAPES, SHAPES
+    from test_stores_gpu import LAYERNORM_SHAPES
+
+    def kernels(shapes, normalize):
+        seen = set()
+        for N, K in shapes:
+            tokens, shares, bytes_ = ctypes.c_int(), ctypes.c_int(), ctypes.c_long()
+            k = probes.probe_layernorm(N, K, normalize, N % 32 == 0, *map(ctypes.byref, (tokens, shares, bytes_)))
+            assert bytes_.value <= 160 * 1024 - 256
+            seen.add((k, tokens.value) if k != 2 else (k, -(-K // 4096), shares.value > 1))
+        return seen
+    every = {(0, 16), (0, 8), (1, 32), (1, 64), (3, 64)} | {(2, parts, shared) for parts in (1, 2, 3, 4) for shared in (True, False)}
+    reached = kernels(SHAPES + LAYERNORM_SHAPES, 1)
+    assert every == reached, every ^ reached
+    assert {k[0] for k in kernels(SHAPES, 1)} == {k[0] for k in kernels(HARD_SHAPES, 1)} == {0, 1, 2, 3}
+    assert {k[0] for k in kernels(LAYERNORM_SHAPES, 0)} == {1, 2}
+    assert {(0, 16), (0, 8), (1, 32), (2, 1, True), (2, 2, True), (2, 4, True)} <= kernels(few, 1)

@@ -1,6 +1,6 @@
 """LayerNorm-side transposition of few tokens (blocks of 16 tokens, or of 8 with two wavefronts per token, whose features are
-shared by several workgroups) at its edges, and of the next larger numbers of tokens, which the other kernels take.  Bounds as in
-test_layernorm_gpu.py."""
+shared by several workgroups) at its edges, and of the next larger numbers of tokens, which the other kernels take
+(test_choice.py holds which).  Bounds as in test_layernorm_gpu.py."""
 import numpy as np
 import pytest
 
@@ -12,13 +12,16 @@ from test_layernorm_gpu import _check, _draw
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("fmt", ["f16", "bf16"])
-@pytest.mark.parametrize("N,K", [
+SHAPES = [
     (8, 8), (16, 16), (24, 72), (40, 504), (40, 520), (136, 1000),   # less than a run of 512 features, a run and a little, ragged slices
     (4096, 1024), (4104, 1024), (2048, 2048), (2056, 2048),          # the most tokens, and the next
     (8, 2056), (512, 2056), (520, 2056), (768, 3584), (776, 3584),   # 8 tokens: 64 blocks and 65, the most tokens and the next
     (8, 16384), (56, 16376), (768, 16384), (776, 16384), (776, 8192), (800, 5000),
-])
+]
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("N,K", SHAPES)
 def test_few_tokens_parity(fmt, N, K):
     announce("layernorm, few tokens", fmt, N, K)
     x, gamma, beta = _draw(N, K, fmt, seed=1800 + N + K, offset=3.0)

@@ -38,25 +38,32 @@ def _check(x, gamma, beta, eps, fmt):
         "max excess %.3e at %r" % (float((err - bound).max()), np.unravel_index(int((err - bound).argmax()), err.shape))
 
 
+# test_choice.py holds that these and those of test_stores_gpu.py reach every kernel
+SHAPES = [(64, 64), (200, 1024), (1000, 328), (8, 8), (72, 4096), (16456, 72),
+          (96, 2264), (96, 2272), (40008, 1024), (200, 3000), (72, 4104), (40, 8192), (24, 8200), (40, 16384), (16, 16392),
+          (4104, 520), (4104, 1000), (776, 2264), (776, 2272), (800, 5000), (800, 9000)]
+HARD_SHAPES = [(128, 512), (4104, 512), (776, 2272), (80, 2272), (80, 16392)]
+
+
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
-@pytest.mark.parametrize("N,K", [(64, 64), (200, 1024), (1000, 328), (8, 8), (72, 4096), (16456, 72),
-                                 (96, 2264), (96, 2272), (40008, 1024), (200, 3000), (72, 4104), (40, 8192), (24, 8200), (40, 16384), (16, 16392)])
+@pytest.mark.parametrize("N,K", SHAPES)
 def test_layernorm_transpose_parity(fmt, N, K):
-    """Shapes for each code path: blocks of 32 tokens held in LDS, blocks of 64
+    """Shapes for each code path: few tokens (16 or 8 to a workgroup, which shares their features with others), blocks of 32 tokens held in LDS, blocks of 64
     (input and output beyond 160 MB, ragged last block), the largest K that
-    still fits, the register-resident kernel beyond it (one to four parts of
-    4096 features, full and partial) and the streaming kernel beyond 16384."""
+    still fits, the register-resident kernel beyond it (one to three parts of
+    4096 features, shared by workgroups) and the streaming kernel beyond 16384."""
     announce("layernorm", fmt, N, K)
     x, gamma, beta = _draw(N, K, fmt, seed=700 + N + K)
     _check(x, gamma, beta, 1e-5, fmt)
     _check(x, None, None, 1e-5, fmt)
 
 
-def test_layernorm_large_mean_small_spread_and_constant_rows():
+@pytest.mark.parametrize("N,K", HARD_SHAPES)
+def test_layernorm_large_mean_small_spread_and_constant_rows(N, K):
     """Tokens sitting far from zero with a small spread (the case a naive
-    sum-of-squares variance loses), and constant tokens (zero variance)."""
-    announce("layernorm hard rows")
-    x, gamma, beta = _draw(128, 512, "f16", seed=711, offset=100.0, scale=0.25)
+    sum-of-squares variance loses), and constant tokens (zero variance), on every kernel."""
+    announce("layernorm hard rows", N, K)
+    x, gamma, beta = _draw(N, K, "f16", seed=711, offset=100.0, scale=0.25)
     _check(x, gamma, beta, 1e-5, "f16")
     x[5, :] = np.float16(3.0)
     x[77, :] = np.float16(-0.5)

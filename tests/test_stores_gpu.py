@@ -22,11 +22,16 @@ def test_rows_of_every_alignment_exact(kernel, V, N, pad_ld, offset):
         assert np.array_equal(got.astype(np.float64), want if dt == "float32" else want.astype(np.float16).astype(np.float64))
 
 
-@pytest.mark.parametrize("N,K", [(40, 5000), (32, 16384), (704, 9000), (1000, 4096), (8, 2504),    # shared by workgroups
-                                 (8200, 2504), (8192, 4104),                                       # one workgroup per block
-                                 (4096, 2560), (2752, 9216),                                       # where sharing by two does not pay
-                                 (264, 1000), (256, 1024),                                         # whole rows in the LDS
-                                 (8, 8), (72, 8), (40, 504), (136, 512), (64, 520)])               # one half of a sweep, and just over
+# With a LayerNorm those of up to 768 tokens (2048 of 2048 features, 4096 of 1024) go to the kernel for few tokens; transposed only, all are as described
+LAYERNORM_SHAPES = [(40, 5000), (32, 16384), (704, 9000), (1000, 4096), (8, 2504),    # shared by workgroups
+                    (776, 9000), (1024, 16384),                                       # the same with a LayerNorm too
+                    (8200, 2504), (8192, 4104), (4104, 12296),                        # one workgroup per block
+                    (4096, 2560), (2752, 9216),                                       # where sharing by two does not pay
+                    (264, 1000), (256, 1024), (4104, 1000), (776, 2264),              # whole rows in the LDS
+                    (8, 8), (72, 8), (40, 504), (136, 512), (64, 520), (4104, 504), (4104, 520)]   # one half of a sweep, and just over
+
+
+@pytest.mark.parametrize("N,K", LAYERNORM_SHAPES)
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
 def test_layernorm_transposition_of_every_sharing(N, K, fmt):
     """Against the definition in 64 bits (torch).  The result is rounded once from 32 bits: half a unit in
