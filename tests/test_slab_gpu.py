@@ -111,19 +111,23 @@ def _bench_rotation(p, out_bytes=2, cache=256 << 20):
     return max(2, min(8, -(-2 * cache // per)))
 
 
-@pytest.mark.parametrize("sparsity", [0.75, 0.0])
-def test_config2_ffn_full_size_every_element_as_the_benchmark_launches_it(sparsity):
+@pytest.mark.parametrize("sparsity,kernel,name", [
+    (0.75, 0, "shflbw_slab_kernel<32,resident in 16 wavefronts"), (0.0, 0, "shflbw_slab_kernel<32,12,"),
+    (0.75, SLAB, "shflbw_slab_kernel<32,12,")])
+def test_config2_ffn_full_size_every_element_as_the_benchmark_launches_it(sparsity, kernel, name):
     """Headline workload (4096 x 1024 by 1024 x 8192, V = 32) at 75 % and its own
     dense run (sparsity 0), every element against the oracle, in the launch
     configuration the benchmark times: automatic kernel choice, the same packed
     matrix launched in turn over the benchmark's rotating (X, Y) pairs; each pair's
-    Y must be the same bits, and the choice must be the shared-slab kernel."""
+    Y must be the same bits, and the choice must be the resident slab at 75 % and the
+    shared-slab kernel unpruned.  The latter at 75 % too, when it is asked for."""
     import torch
     from gpu_util import to_device, to_host
-    announce("config2 full size", sparsity)
+    announce("config2 full size", sparsity, kernel)
     p = synth.config(1, sparsity=sparsity)
     Yr, S = c_oracle.spmm(p.W, p.mask, p.X)
     A = binding.compress(p.W, p.mask, p.perm, p.V).bind_device("cuda:0")
+    A.set_tuning(kernel, 0)
     rot = _bench_rotation(p)
     x0 = to_device(p.X)
     Xs = [x0] + [x0.clone() for _ in range(rot - 1)]
@@ -132,7 +136,7 @@ def test_config2_ffn_full_size_every_element_as_the_benchmark_launches_it(sparsi
         A.spmm(Xs[step % rot], Ys[step % rot])
     torch.cuda.synchronize()
     A.device_status()
-    assert binding.last_kernel().startswith("shflbw_slab_kernel<32,"), binding.last_kernel()
+    assert binding.last_kernel().startswith(name), binding.last_kernel()
     Y0 = to_host(Ys[0])
     assert_within_scaled_tolerance(Y0, Yr, S, what="config2 s=%.2f" % sparsity)
     for j in range(1, rot):

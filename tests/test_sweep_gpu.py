@@ -102,9 +102,11 @@ def test_sweep_of_large_products():
             if kernel == 2:
                 continue
             raise
-        kernels.add(binding.last_kernel().split(",")[0])
+        name = binding.last_kernel()
+        if "resident" not in name:
+            kernels.add(name.split(",")[0])
         Yr, S = c_oracle.spmm(p.W, p.mask, p.X)
         assert_within_scaled_tolerance(Y, Yr, S, what="large product %d" % it)
-    # both kernels, every group size
+    # the ring kernel and the gather kernel, every group size (test_resident_gpu.py is the resident slab's)
     for V in (16, 32, 64, 128):
         assert "shflbw_slab_kernel<%d" % V in kernels and "shflbw_gather_kernel<%d" % V in kernels, kernels
