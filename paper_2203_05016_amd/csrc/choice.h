@@ -230,13 +230,14 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
 
 // Taken where its estimate is below the best cut's by a margin.  Both estimates are low, by 5 to 20 % by V and by how results lie, and neither
 // is better than 13 to 20 %, worst where a group has few steps, or where there are few columns or little work: hence the
-// margins, which are such that few layers get slower, at the price of some that would have gained.  Of 6992 random layers that nothing was fitted
-// to (half of them are profiles/resident_sweep.csv) 2778 take it, at .767 of the other kernels' time (geometric mean; over all .900, the best of both
-// .877): 45 of these lose more than 4 %, 11 more than 10 %, the worst 34 % (1x1, 26 images of 30x30, 1143 -> 1600 channels at 80 %, V = 32).  With one margin for all images and the same for little work
+// margins, which are such that few layers get slower, at the price of some that would have gained.  Of 7363 random layers (half
+// of them are profiles/resident_sweep.csv) 2895 take it, at .766 of the other kernels' time (geometric mean; over all .900, the best of both
+// .877): 51 of these lose more than 4 %, 8 more than 10 %, the worst 14 %.  Two runs of one kernel differ by more than 4 % in .5 % of the layers, V = 64 in 2 %.
+// Margins and limits are not fitted to these, but that few fetches count on images is what their worst showed.  With one margin for all images and the same for little work
 // 6 % of those that took it lost more than 4 %, 3 % more than 10 %, and the gain over all was the same .900.
 // 4096 x 1024, V = 32 at 75 %, us other
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
-// 16.3 / 12.0 to 15.2, by card; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; V = 64 28.3 / 25.2; but 1024 x 1024 by 4096 6.8 / 7.5 and
+// 16.3 / 12.0 to 15.2, by card; V = 16 by 8192 56.5 / 31.6, by 2047 33.1 / 14.6; not taken: V = 64 28.3 / 25.2 to 27.1, unpruned 82 / 76; 1024 x 1024 by 4096 6.8 / 7.5 and
 // 2048 x 1024 by 2048 at 90 %, V = 16 6.0 / 6.9: few groups, or few steps, to share a copy.
 constexpr double RESIDENT_COPY_UNALIGNED = 1.4;
 // Fewer tiles than this gain little (of the layers below it a sixth would take it, and win 1 %), half of those that lose are among them,
@@ -247,13 +248,17 @@ inline bool resident_conv_worth_a_look(int V, int K, long tiles) { return V <= 3
 inline bool resident_pays(const CutSizes& s, Cut cut, bool whole, const ResidentPlan& plan)
 {
     if (plan.parts <= 0) return false;
-    // rows of no whole 64-byte blocks, the same with few steps or columns, rows of whole blocks, the same with few; then the same of images.  0: never.
+    // rows of no whole 64-byte blocks, the same with few steps (4, V = 64 in whole blocks 12) or columns, rows of whole blocks, the same with few; then
+    // the same of images.  0: never.
     static constexpr double MARGINS[4][8] = {{.98, .98, .9, .85, .99, 1.02, .87, .95}, {.98, .86, .85, .74, .94, .94, .87, 0},
-                                             {1.01, .86, .89, .81, .88, .88, .74, 0}, {.93, .8, 1.05, .8, 0, 0, 0, 0}};
-    const int few = s.per <= 4 || s.N < 1024 ? 1 : 0;
+                                             {1.01, .86, .95, .81, .88, .88, .74, 0}, {.93, .8, 1.05, .8, 0, 0, 0, 0}};
+    const int few = s.per <= (s.V == 64 && whole ? 12 : 4) || s.N < 1024 ? 1 : 0;
     double margin = MARGINS[s.v()][(s.rows == Rows::IMAGES ? 4 : 0) + (whole ? 2 : 0) + few];
     const double work = (double)s.tiles() * s.per;
     if (few && s.V < 128 && work < 12000) margin *= std::sqrt(std::sqrt(work / 12000));
+    // images whose rows less than one group fetches (98 of 31x31, 121 -> 64 channels at 90 %, V = 16 11.0 / 14.6)
+    const double fetches = s.G * s.kept;
+    if (s.rows == Rows::IMAGES && fetches < 1 && margin > std::sqrt(std::sqrt(fetches))) margin = std::sqrt(std::sqrt(fetches));
     return plan.time < margin * cut_time(s, cut);
 }
 
@@ -299,7 +304,8 @@ inline bool resident_conv_pays(const CutSizes& s, Runs runs, bool gathered, cons
 // is kept.  Of 4164 random ones (1x1 and 3x3, 8 to 60 columns, 16-bit results) that nothing was fitted to 2898 are gathered, at .57 of the staged kernel's time, and 20 of these lose
 // more than 4 %, up to 36 %; of 2287 dear ones 857 at .65, 20 lose as much, up to 45 % (profiles/strided_sweep.csv holds those that the limits came from).
 // Where it does not hold: 52 images of 35x35, 220 -> 896 channels at 50 %, V = 64 107 us staged, 289 gathered; 37 of 28x28, 256 -> 560,
-// V = 16 106 and 429; 19 of 34x33, 231 -> 64 at 30 %, V = 16 19.3 and 37.8; where it does: 37 of 29x29, 241 -> 832 at 85 %, V = 64 45.6 and 25.5.
+// V = 16 106 and 429; 19 of 34x33, 231 -> 64 at 30 %, V = 16 19.3 and 37.8; where it does: 32 of 56x56, 128 -> 128 at 75 %,
+// V = 32 22.6 and 19.1; 1x1, 6 of 19x19, 1968 -> 96 at 95 % 16.0 and 4.4.
 inline bool strided_runs_pay(int V, long G, int taps, double kept, double work)
 {
     const double fetches = G * kept;
