@@ -224,9 +224,11 @@ int shflbw_spmm_unbound(const shflbw_matrix* A, const void* X, int64_t ldx, void
  *  out  device, ydtype (the matrix's wdtype, or SHFLBW_F32): [batch][C_out][H_out][W_out] or [C_out][H_out][W_out][batch],
  *       H_out = (H + 2*pad_h - R)/stride_h + 1, W_out likewise.
  * Tensors with runs of 8 along the innermost dimension (CHWN: 8 images or more;
- * NCHW: unit stride along x, 8 output columns or more, at most one column of
- * padding) take the per-wave gather kernel; others, and dense or fine-grained
- * NCHW products, a kernel whose workgroups copy the part of the input their
+ * NCHW: a stride of one along x, or of two with 16-bit results and 16 input columns
+ * or more, 8 output columns or more, at most one column of padding) take the per-wave
+ * gather kernel or, with K up to 1278, V up to 32 and 16-bit results, the slab kernel
+ * that holds 64 columns of the unfolded matrix in LDS; others, and products whose groups
+ * fetch many rows each, a kernel whose workgroups copy the part of the input their
  * output positions can touch into LDS once and gather from there.
  * A 1x1 convolution with unit stride and no padding is the linear-layer
  * product itself (CHWN: one matrix; NCHW with H*W of 4, 8 or more: one per
