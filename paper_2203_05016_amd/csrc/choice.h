@@ -231,9 +231,11 @@ inline ResidentPlan plan_resident(const CutSizes& s, bool whole, double copy)
 // Taken where its estimate is below the best cut's by a margin.  Both estimates are low, by 5 to 20 % by V and by how results lie, and neither
 // is better than 13 to 20 %, worst where a group has few steps, or where there are few columns or little work: hence the
 // margins, which are such that few layers get slower, at the price of some that would have gained.  Of 7363 random layers (half
-// of them are profiles/resident_sweep.csv) 2895 take it, at .766 of the other kernels' time (geometric mean; over all .900, the best of both
-// .877): 51 of these lose more than 4 %, 8 more than 10 %, the worst 14 %.  Two runs of one kernel differ by more than 4 % in .5 % of the layers, V = 64 in 2 %.
-// Margins and limits are not fitted to these, but that few fetches count on images is what their worst showed.  With one margin for all images and the same for little work
+// of them are profiles/resident_sweep.csv) 2882 take it, at .765 of the other kernels' time (geometric mean; over all .900, the best of both
+// .877): 49 of these lose more than 4 %, 7 more than 10 %, the worst 14 %.  Two runs of one kernel differ by more than 4 % in .5 % of the layers, V = 64 in 2 %.
+// Margins and limits are not fitted to these, but that few fetches count on images is what their worst showed.
+// Wider ones (6163 layers of 1 to 1278 features, up to 16 384 rows and 200 000 columns), which the last limits below come from: 1771 take it, at .78, 33 lose more than 4 %, 8 more than 10 %, up to 20 %; of 5385 others
+// of these sizes 1596, at .78, 33 and 6, up to 21 %.  With one margin for all images and the same for little work
 // 6 % of those that took it lost more than 4 %, 3 % more than 10 %, and the gain over all was the same .900.
 // 4096 x 1024, V = 32 at 75 %, us other
 // kernels / resident: by 8192 34.9 / 26.8, with 32-bit results 52.6 / 35.0, by 8191 (rows of no alignment) 50.5 / 28.6, by 2047
@@ -253,6 +255,9 @@ inline bool resident_pays(const CutSizes& s, Cut cut, bool whole, const Resident
     static constexpr double MARGINS[4][8] = {{.98, .98, .9, .85, .99, 1.02, .87, .95}, {.98, .86, .85, .74, .94, .94, .87, 0},
                                              {1.01, .86, .95, .81, .88, .88, .74, 0}, {.93, .8, 1.05, .8, 0, 0, 0, 0}};
     const int few = s.per <= (s.V == 64 && whole ? 12 : 4) || s.N < 1024 ? 1 : 0;
+    // not where few groups share a copy (4 x 128 rows, 353 by 73 664 32.5 / 39.3; 80 x 55 by 146 488 at 95 %, V = 16 14.6 / 18.5), the slab is next to nothing
+    // (11 904 x 23 by 11 088, V = 32 86 / 108; V = 16 gains there, .80 of 1043 layers' time, V = 32 with 32-bit results .83 of 107), nor many groups of few steps (16 288 x 299 by 6632 at 80 %, V = 32 78 / 98)
+    if ((s.G < 6 && (s.V == 16 || s.V == 128)) || (s.K < 64 && s.V > 16 && !(s.V == 32 && s.f32)) || (few && s.V == 32 && s.G > 256)) return false;
     double margin = MARGINS[s.v()][(s.rows == Rows::IMAGES ? 4 : 0) + (whole ? 2 : 0) + few];
     const double work = (double)s.tiles() * s.per;
     if (few && s.V < 128 && work < 12000) margin *= std::sqrt(std::sqrt(work / 12000));

@@ -190,6 +190,22 @@ def test_strided_convolutions_are_gathered_where_it_is_faster(probes):
         _hold("V = " + V, [t for r, t in times if r["V"] == V], .7, .7, .04, .02)
 
 
+@pytest.mark.parametrize("V,G,K,N,per,rows,f32,kept,whole,taken", [
+    (32, 128, 1024, 8192, 16, "aligned", 0, .25, 1, True),         # us without / with: 34.9 / 26.8
+    (32, 128, 1024, 2047, 16, "any", 0, .25, 0, True),             # 16.3 / 12.0
+    (64, 18, 160, 9210, 8, "any", 0, .5, 0, False),                # 10.9 / 12.6
+    (16, 485, 184, 216, 4, "aligned", 0, .5, 0, False),            # 4.4 / 4.9
+    (128, 4, 353, 73664, 12, "aligned", 0, .5, 1, False),          # 32.5 / 39.3: few groups
+    (16, 5, 55, 146488, 4, "aligned", 0, .05, 0, False),           # 14.6 / 18.5
+    (32, 372, 23, 11088, 4, "aligned", 0, .22, 0, False),          # 86 / 108: next to no slab
+    (32, 509, 299, 6632, 4, "aligned", 0, .2, 0, False),           # 78 / 98: many groups of few steps
+    (128, 5, 92, 24576, 4, "images", 0, .3, 1, False),             # 9.7 / 13.8
+    (16, 4, 121, 94864, 4, "images", 0, .1, 0, False),             # 11.0 / 14.6: rows that less than one group fetches
+])
+def test_resident_slab_where_it_mattered(probes, V, G, K, N, per, rows, f32, kept, whole, taken):
+    assert _resident(probes, V, G, -(-N // 8) * 8, G * per, K, rows, 0, f32, 0, kept, whole)[0] == taken
+
+
 @pytest.mark.parametrize("V", [16, 32, 64, 128])
 def test_plans_of_the_resident_slab_are_within_what_its_kernel_takes(probes, V):
     """The slab, a row of zeros and a counter in 160 KB of LDS, or in 80 where two workgroups share a CU; loads of the copy for every
