@@ -255,7 +255,7 @@ inline bool resident_pays(const CutSizes& s, Cut cut, bool whole, const Resident
     static constexpr double MARGINS[4][8] = {{.98, .98, .9, .85, .99, 1.02, .87, .95}, {.98, .86, .85, .74, .94, .94, .87, 0},
                                              {1.01, .86, .95, .81, .88, .88, .74, 0}, {.93, .8, 1.05, .8, 0, 0, 0, 0}};
     const int few = s.per <= (s.V == 64 && whole ? 12 : 4) || s.N < 1024 ? 1 : 0;
-    // not where few groups share a copy (4 x 128 rows, 353 by 73 664 32.5 / 39.3; 80 x 55 by 146 488 at 95 %, V = 16 14.6 / 18.5), the slab is next to nothing
+    // not where few groups share a copy (512 x 353 by 73 664 at 50 %, V = 128 32.5 / 39.3; 64 x 55 by 146 488 at 96 %, V = 16 14.6 / 18.5), the slab is next to nothing
     // (11 904 x 23 by 11 088, V = 32 86 / 108; V = 16 gains there, .80 of 1043 layers' time, V = 32 with 32-bit results .83 of 107), nor many groups of few steps (16 288 x 299 by 6632 at 80 %, V = 32 78 / 98)
     if ((s.G < 6 && (s.V == 16 || s.V == 128)) || (s.K < 64 && s.V > 16 && !(s.V == 32 && s.f32)) || (few && s.V == 32 && s.G > 256)) return false;
     double margin = MARGINS[s.v()][(s.rows == Rows::IMAGES ? 4 : 0) + (whole ? 2 : 0) + few];

@@ -196,7 +196,7 @@ def test_strided_convolutions_are_gathered_where_it_is_faster(probes):
     (64, 18, 160, 9210, 8, "any", 0, .5, 0, False),                # 10.9 / 12.6
     (16, 485, 184, 216, 4, "aligned", 0, .5, 0, False),            # 4.4 / 4.9
     (128, 4, 353, 73664, 12, "aligned", 0, .5, 1, False),          # 32.5 / 39.3: few groups
-    (16, 5, 55, 146488, 4, "aligned", 0, .05, 0, False),           # 14.6 / 18.5
+    (16, 4, 55, 146488, 4, "aligned", 0, .04, 0, False),           # 14.6 / 18.5
     (32, 372, 23, 11088, 4, "aligned", 0, .22, 0, False),          # 86 / 108: next to no slab
     (32, 509, 299, 6632, 4, "aligned", 0, .2, 0, False),           # 78 / 98: many groups of few steps
     (128, 5, 92, 24576, 4, "images", 0, .3, 1, False),             # 9.7 / 13.8
